@@ -1,0 +1,260 @@
+// D3Q19 passes of two steps.
+#include "lbm_device.h"
+
+namespace lbm {
+namespace {
+
+// ---------------------------------------------------------------------------
+// S D3Q19 time steps per pass over HBM.
+//
+// The 2-D scheme above one dimension up: a block of MS3_TX x MS3_TY threads
+// owns a tile of (MS3_TX - 2S) x (MS3_TY - 2S) output columns (x, y) plus an
+// S-wide halo, thread (tx, ty) owns one column in every stage, and the block
+// marches along z through a segment of planes.  A row of the tile (fixed y)
+// is one wave, lane tx = column x: the ten populations with e_x != 0 are
+// pulled from lane tx - e_x by DPP lane shifts, as in the D2Q9 passes; the
+// ten with e_y != 0 (the xy edges after their x shift) then go through LDS
+// to row ty + e_y; the three with e_x = e_y = 0 stay in their thread.  Planes
+// are delayed in registers by e_z (0, 1 or 2 iterations).  Register pressure
+// limits S to 2 (190 VGPRs when only the 13 independent populations are
+// loaded, 217 otherwise; two waves per SIMD, so one 512-thread block per
+// CU); each block uses 2 x 10 x 512 doubles of LDS.
+// ---------------------------------------------------------------------------
+__host__ __device__ constexpr int m3_ex(int i) { return Lat<3>::E[i][0]; }
+__host__ __device__ constexpr int m3_ey(int i) { return Lat<3>::E[i][1]; }
+__host__ __device__ constexpr int m3_ez(int i) { return Lat<3>::E[i][2]; }
+// index of population i among those with its e_z
+__host__ __device__ constexpr int m3_zslot(int i) {
+    int s = 0;
+    for (int j = 0; j < i; ++j) s += m3_ez(j) == m3_ez(i);
+    return s;
+}
+constexpr int M3_Z0 = 9, M3_ZP = 5;  // populations with e_z = 0 and with e_z = +1
+constexpr int M3_THREADS = MS3_TX * MS3_TY;
+static_assert(MS3_TX == 64, "a tile row of the D3Q19 pass is one wave (DPP lane shifts along x)");
+
+template <int S>
+struct Ms3State {
+    double pre[19];            // next input plane (prefetched)
+    double z[S][M3_Z0];        // e_z = 0 populations of the previous plane, per stage input
+    double u[2][S][M3_ZP];     // e_z = +1 populations of the planes of each parity
+};
+
+// y-movers (e_y != 0): the 10 populations exchanged through LDS
+__host__ __device__ constexpr bool m3_ymover(int i) { return m3_ey(i) != 0; }
+__host__ __device__ constexpr int m3_yslot(int i) {
+    int s = 0;
+    for (int j = 0; j < i; ++j) s += m3_ymover(j);
+    return s;
+}
+constexpr int M3_YMOVERS = m3_yslot(19);
+static_assert(M3_YMOVERS == 10, "D3Q19 has 10 populations with e_y != 0");
+
+// Whether plane i of a post-collision state (population i, or its twin)
+// holds a population with e_y = ey.
+__host__ __device__ constexpr bool m3_plane_holds(int i, int ey) {
+    for (int p = 0; p < 19; ++p)
+        if (twin<3>(p) == i && m3_ey(p) == ey) return true;
+    return false;
+}
+__host__ __device__ constexpr int m3_planes_holding(int ey) {
+    int n = 0;
+    for (int i = 0; i < 19; ++i) n += twin<3>(i) == i && m3_plane_holds(i, ey);
+    return n;
+}
+static_assert(m3_planes_holding(1) == 5 && m3_planes_holding(-1) == 5,
+              "an edge row of the tile passes on 5 of the 13 independent planes");
+
+// With only the 13 independent populations, one input plane (z-plane zp) of
+// the column col through a buffer resource over that z-plane's chunks
+// (32-bit offsets).  The first tile row passes on only its populations with
+// e_y = +1 and the last only those with e_y = -1; the planes they do not
+// need get an out-of-range offset, so the hardware drops those loads (no
+// memory access, the register reads 0) and every wave still issues the same
+// instructions: the two edge rows fetch 5 of the 13 planes.
+__device__ __forceinline__ void m3_load_plane(double (&pre)[19], const double* src,
+                                              int64_t plane, int zp, int col, int ty) {
+    const int64_t n0 = (int64_t)zp * plane;
+    const int64_t c0 = n0 >> 12, c1 = (n0 + plane - 1) >> 12;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<double*>(src) + c0 * 19 * 4096, (short)0,
+        (int)((c1 - c0 + 1) * 19 * 4096 * 8), 0x00020000);
+    const int64_t kk = n0 + col;
+    const unsigned base = (unsigned)((((kk >> 12) - c0) * 19 * 4096 + (kk & 4095)) * 8);
+#pragma unroll
+    for (int i = 0; i < 19; ++i)
+        if (twin<3>(i) == i) {
+            const bool need = (ty != 0 || m3_plane_holds(i, 1)) &&
+                              (ty != MS3_TY - 1 || m3_plane_holds(i, -1));
+            const unsigned off = need ? base + (unsigned)(i * 4096 * 8) : 0x80000000u;
+            pre[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+        }
+}
+
+// x shift by DPP (pull from lane tx - e_x), then y shift through LDS.  BUF:
+// the input planes come through m3_load_plane (RIN only).
+template <int S, int P, bool RIN, bool WOUT, bool BUF = false>
+__device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
+                                          const double* __restrict__ src, double* __restrict__ dst,
+                                          const Geo& g, int col, int zs, int x0, int y0,
+                                          const FoldedRates& r) {
+    static_assert(!BUF || RIN, "buffer loads serve the reduced state only");
+    // a tile row is one wave: ty is uniform across it, and saying so lets the
+    // per-row choices (edge-row loads, y exchange) compile to scalar selects
+    // and branches instead of lane-masked ones
+    const int tid = threadIdx.x, tx = tid % MS3_TX;
+    const int ty = __builtin_amdgcn_readfirstlane(tid / MS3_TX);
+    const int64_t plane = (int64_t)g.nx * g.ny;
+    double f[19];
+#pragma unroll
+    for (int i = 0; i < 19; ++i) f[i] = st.pre[RIN ? twin<3>(i) : i];
+    if constexpr (BUF) {
+        m3_load_plane(st.pre, src, plane, wrapi(zs - S + k + 1, g.nz), col, ty);
+    } else {
+        const int64_t base = (int64_t)wrapi(zs - S + k + 1, g.nz) * plane + col;
+#pragma unroll
+        for (int i = 0; i < 19; ++i)
+            if (!RIN || twin<3>(i) == i) st.pre[i] = src[slot<19>(i, base)];
+    }
+    // pull along x (every lane takes part; the edge lanes receive zeros,
+    // which reach only halo columns, never a stored output)
+#pragma unroll
+    for (int i = 0; i < 19; ++i)
+        if (m3_ex(i) != 0) f[i] = m3_ex(i) == 1 ? lane_shift<1>(f[i]) : lane_shift<-1>(f[i]);
+#pragma unroll
+    for (int i = 0; i < 19; ++i)
+        if (m3_ymover(i)) {
+            const int cy = ty + m3_ey(i);
+            if (cy >= 0 && cy < MS3_TY) lds[m3_yslot(i) * M3_THREADS + cy * MS3_TX + tx] = f[i];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int j = 1; j <= S; ++j) {
+        double in[19];
+        const double* rd = lds + ((j - 1) & 1) * M3_YMOVERS * M3_THREADS;
+#pragma unroll
+        for (int i = 0; i < 19; ++i) {
+            const double v = m3_ymover(i) ? rd[m3_yslot(i) * M3_THREADS + tid] : f[i];
+            if (m3_ez(i) == -1) {
+                in[i] = v;
+            } else if (m3_ez(i) == 0) {
+                in[i] = st.z[j - 1][m3_zslot(i)];
+                st.z[j - 1][m3_zslot(i)] = v;
+            } else {
+                in[i] = st.u[P][j - 1][m3_zslot(i)];
+                st.u[P][j - 1][m3_zslot(i)] = v;
+            }
+        }
+        if (k >= 2 * j) {
+            collide_d3q19(in, r);
+            if (j < S) {
+                double* wr = lds + (j & 1) * M3_YMOVERS * M3_THREADS;
+#pragma unroll
+                for (int i = 0; i < 19; ++i) {
+                    double v = in[i];
+                    if (m3_ex(i) != 0) v = m3_ex(i) == 1 ? lane_shift<1>(v) : lane_shift<-1>(v);
+                    f[i] = v;
+                    if (m3_ymover(i)) {
+                        const int cy = ty + m3_ey(i);
+                        if (cy >= 0 && cy < MS3_TY) wr[m3_yslot(i) * M3_THREADS + cy * MS3_TX + tx] = v;
+                    }
+                }
+            } else if (tx >= S && tx < MS3_TX - S && ty >= S && ty < MS3_TY - S &&
+                       x0 - S + tx < g.nx && y0 - S + ty < g.ny) {
+                const int64_t kk = (int64_t)wrapi(zs - 2 * S + k, g.nz) * plane +
+                                   (int64_t)(y0 - S + ty) * g.nx + (x0 - S + tx);
+#pragma unroll
+                for (int i = 0; i < 19; ++i)
+                    if (!WOUT || twin<3>(i) == i)
+                        __builtin_nontemporal_store(in[i], dst + slot<19>(i, kk));
+            }
+        }
+        if (j < S) __syncthreads();
+    }
+    if (S & 1) __syncthreads();
+}
+
+template <int S, bool RIN, bool WOUT, bool BUF>
+__global__ void __launch_bounds__(M3_THREADS) k_steps_d3q19(const double* __restrict__ src,
+                                                            double* __restrict__ dst, Geo g,
+                                                            Rates r, int lz, int ntx, int nty) {
+    __shared__ double lds[2 * M3_YMOVERS * M3_THREADS];
+    const unsigned t = xcd_remap(blockIdx.x, gridDim.x);
+    const unsigned ntile = (unsigned)ntx * (unsigned)nty;
+    const int tile = (int)(t % ntile), seg = (int)(t / ntile);
+    const int x0 = (tile % ntx) * tile_width3(S), y0 = (tile / ntx) * tile_height3(S);
+    const int zs = seg * lz, ze = min(zs + lz, g.nz);
+    const int tx = threadIdx.x % MS3_TX;
+    const int ty = __builtin_amdgcn_readfirstlane((int)threadIdx.x / MS3_TX);
+    const int col = wrapi(y0 - S + ty, g.ny) * g.nx + wrapi(x0 - S + tx, g.nx);
+    const int kend = ze - zs + 2 * S - 1;
+    const FoldedRates fr = folded(r);
+    Ms3State<S> st;
+    {
+        const int64_t base = (int64_t)wrapi(zs - S, g.nz) * g.nx * g.ny + col;
+#pragma unroll
+        for (int i = 0; i < 19; ++i)
+            if (!RIN || twin<3>(i) == i) st.pre[i] = src[slot<19>(i, base)];
+    }
+#pragma unroll
+    for (int j = 0; j < S; ++j) {
+#pragma unroll
+        for (int a = 0; a < M3_Z0; ++a) st.z[j][a] = 0.0;
+#pragma unroll
+        for (int a = 0; a < M3_ZP; ++a) st.u[0][j][a] = st.u[1][j][a] = 0.0;
+    }
+    // plane pairs in the loop, a last odd plane after it (as in ms_tile)
+    int k = 0;
+    for (; k + 1 <= kend; k += 2) {
+        ms3_plane<S, 0, RIN, WOUT, BUF>(st, lds, k, src, dst, g, col, zs, x0, y0, fr);
+        ms3_plane<S, 1, RIN, WOUT, BUF>(st, lds, k + 1, src, dst, g, col, zs, x0, y0, fr);
+    }
+    if (k <= kend) ms3_plane<S, 0, RIN, WOUT, BUF>(st, lds, k, src, dst, g, col, zs, x0, y0, fr);
+}
+
+}  // namespace
+
+// Planes per segment of a D3Q19 pass: 64, fewer (at least 16) when the grid
+// would otherwise give under about 1280 blocks, then evened out over the
+// segments.
+template <int S>
+static hipError_t launch_steps3_t(const Geo& g, const Rates& r, const double* src, double* dst,
+                                  hipStream_t st, bool rin, bool wout) {
+    const int ntx = (g.nx + tile_width3(S) - 1) / tile_width3(S);
+    const int nty = (g.ny + tile_height3(S) - 1) / tile_height3(S);
+    int64_t lz = ((int64_t)g.nz * ntx * nty + 1279) / 1280;
+    if (lz > 64) lz = 64;
+    if (lz < 16) lz = 16;
+    if (lz > g.nz) lz = g.nz;
+    // segments of equal length: a short last segment is mostly pipeline fill
+    // (512 x 512 x 64: 58 + 6 planes gave 16.6 GLUPS, 32 + 32 planes 25.6)
+    lz = (g.nz + (g.nz + lz - 1) / lz - 1) / ((g.nz + lz - 1) / lz);
+    const int64_t nseg = (g.nz + lz - 1) / lz;  // every segment non-empty
+    const int64_t nb = (int64_t)ntx * nty * nseg;
+    if (nb > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
+    // buffer loads need the chunks of one z-plane under 2 GiB (planes up to
+    // about 14 M nodes)
+    const int64_t plane = (int64_t)g.nx * g.ny;
+    const bool buf = (plane / 4096 + 2) * 19 * 4096 * 8 < ((int64_t)1 << 31);
+    return dispatch_io(rin, wout, [&](auto ri, auto wo) {
+        constexpr bool RI = decltype(ri)::value, WO = decltype(wo)::value;
+        if (RI && buf)
+            hipLaunchKernelGGL((k_steps_d3q19<S, RI, WO, RI>), dim3((unsigned)nb),
+                               dim3(M3_THREADS), 0, st, src, dst, g, r, (int)lz, ntx, nty);
+        else
+            hipLaunchKernelGGL((k_steps_d3q19<S, RI, WO, false>), dim3((unsigned)nb),
+                               dim3(M3_THREADS), 0, st, src, dst, g, r, (int)lz, ntx, nty);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
+                         hipStream_t st, bool rin, bool wout) {
+    if (g.nw != 1) return hipErrorInvalidValue;
+    switch (nsteps) {
+        case 2: return launch_steps3_t<2>(g, r, src, dst, st, rin, wout);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace lbm
