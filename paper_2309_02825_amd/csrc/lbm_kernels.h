@@ -70,8 +70,8 @@ __host__ __device__ constexpr int tile_width3(int nsteps) { return MS3_TX - 2 * 
 __host__ __device__ constexpr int tile_height3(int nsteps) { return MS3_TY - 2 * nsteps; }
 hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
                          hipStream_t st, bool rin = false, bool wout = false);
-// 1-D grids up to this many nodes run all their steps in one launch with the
-// state in LDS (3 populations x 8 B x 2048 = 48 KiB).
+// 1-D grids up to this many nodes run all their steps in one launch, the state in
+// registers (halos through 3 populations x 8 B x 2048 = 48 KiB of LDS).
 constexpr int RESIDENT_MAX_1D = 2048;
 // walls != NULL: bounded interval (see launch_step_wall1); wall_now holds the
 // boundary theta of the current time and receives the last pair of walls.

@@ -61,7 +61,7 @@ struct Rates {
     double ds1, ds21, ds22, dw0, dw1, dwd;
     double dinv_s1;          // d(1/s1)/deps = 3
     double c;                // dx / dt
-    // D2Q9 / D3Q19 collisions in folded form (collide_d2q9, collide_d3q19)
+    // D1Q3 / D2Q9 / D3Q19 collisions in folded form (collide_d1q3, ...)
     double f_cj;             // (1 - s1) / 2
     double f_cp;             // (1 - s21) / 2
     double f_ct;             // s21 / 6 - 2 (d - 1) w_d
@@ -336,9 +336,32 @@ __device__ __forceinline__ void collide_d3q19(double (&f)[19], const FoldedRates
     f[18] = f[16];
 }
 
+// D1Q3 collision folded the same way: hP = (1 - s21)/2 P + (s21/6) theta with
+// theta = f_0 + P, so hP = h1 P + h0 f_0, f_{+-1} = hP +- (1 - s1)/2 j and
+// f_0 = theta - 2 hP (sum_i f_i = theta up to unbiased rounding).  Eight
+// operations, three of them in a chain (the generic form: nine); a 1-D run is
+// one such chain after another.
+struct FoldedRates1 {
+    double cj, h0, h1;
+};
+__host__ __device__ __forceinline__ FoldedRates1 folded1(const Rates& r) {
+    return FoldedRates1{r.f_cj, r.f_ct, r.f_cp + r.f_ct};
+}
+__device__ __forceinline__ void collide_d1q3(double (&f)[3], const FoldedRates1& r) {
+    const double P = f[1] + f[2], j = f[1] - f[2];
+    const double hP = fma(r.h1, P, r.h0 * f[0]);
+    f[0] = fma(-2.0, hP, f[0] + P);
+    f[1] = fma(r.cj, j, hP);
+    f[2] = fma(-r.cj, j, hP);
+}
+
 // In-place collision f <- C f (Sec. III.A evolution equation, Theorem 2 rates).
 template <int D>
 __device__ __forceinline__ void collide(double (&f)[Lat<D>::Q], const Rates& r) {
+    if constexpr (D == 1) {
+        collide_d1q3(f, folded1(r));
+        return;
+    }
     if constexpr (D == 2) {
         collide_d2q9(f, folded(r));
         return;
