@@ -33,11 +33,13 @@ METRIC = "FP64 MLUPS + HBM GB/s (% roofline); batched and adjoint vs plain step"
 HBM_PEAK_GBS = 8000.0
 # one read and one write of a complete state: 2 q 8 bytes per node
 BYTES_PER_LU = {1: 48, 2: 144, 3: 304, 4: 528}
-# one read and one write of the populations of a post-collision state that
-# are independent (the twin edge populations of every axis pair are equal):
-# 2 x (1 + 2d + 2d(d-1)) x 8 bytes per node; what the passes inside one
-# lb_step call move
-BYTES_PER_NODE_PASS = {1: 48, 2: 112, 3: 208, 4: 336}
+# one read and one write of what the launches inside one lb_step call hand to
+# one another: the passes of D2Q9 and D3Q19 the 1 + 2d + d(d-1)/2 = 6 / 10
+# values that determine a post-collision node, single steps (and D4Q33) its
+# 1 + 2d + 2d(d-1) independent populations (the twin edge populations of every
+# axis pair are equal)
+BYTES_PER_NODE_PASS = {1: 48, 2: 96, 3: 160, 4: 336}
+BYTES_PER_NODE_SINGLE = {1: 48, 2: 112, 3: 208, 4: 336}
 # double-precision operations of one D2Q9 collision (collide_d2q9: 19 add/sub,
 # 2 mul, 10 fma counted twice)
 FLOPS_PER_LU_D2Q9 = 41
@@ -46,9 +48,9 @@ D2_STEPS_PER_PASS = 8
 D3_STEPS_PER_PASS = 2
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_k_step.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2309_02825_amd", "csrc", n)
-                  for n in ("lbm_kernels.hip", "lbm_d1.hip", "lbm_d2q9.hip", "lbm_d2q9_adjoint.hip",
-                            "lbm_d3q19.hip", "lbm_batch.hip", "lbm_device.h", "lbm_march.h",
-                            "lbm_lattice.h", "lbm_kernels.h")]
+                  for n in ("lbm_kernels.hip", "lbm_d1.hip", "lbm_d2q9.hip", "lbm_d2q9_pass.h",
+                            "lbm_d2q9_adjoint.hip", "lbm_d3q19.hip", "lbm_batch.hip",
+                            "lbm_device.h", "lbm_march.h", "lbm_lattice.h", "lbm_kernels.h")]
 
 
 def pass_roofline(d: int, nodes: int, steps_per_launch: int, us_per_step: float,
@@ -56,14 +58,16 @@ def pass_roofline(d: int, nodes: int, steps_per_launch: int, us_per_step: float,
     """Roofline of one launch of a pass kernel.  A pass reads the state of
     every node once and writes it once, whatever the number of time steps it
     advances.  Inside an lb_step call the state is post-collision, so only
-    its independent populations move: 2 x (7, 13, 21) x 8 bytes per node for
-    D2Q9, D3Q19, D4Q33 (`reduced`); those are the pass's algorithmic bytes,
-    and `frac` is a true fraction of the HBM peak.  The same time against a
+    the values that determine it move: 2 x (6, 10) x 8 bytes per node for the
+    passes of D2Q9 and D3Q19, 2 x (7, 13, 21) x 8 for single steps of D2Q9,
+    D3Q19, D4Q33 (`reduced`); those are the launch's algorithmic bytes, and `frac` is a true fraction of the HBM peak.  The same time against a
     complete state (2 q 8 bytes per node) is `complete_state_gbs`, and the
     per-update figure (bytes per lattice update times the steps of a launch)
     is `lu_equivalent_gbs`; neither is a fraction of the peak."""
     launch_s = us_per_step * steps_per_launch * 1e-6
-    per_node = BYTES_PER_NODE_PASS[d] if reduced else BYTES_PER_LU[d]
+    per_node = BYTES_PER_LU[d]
+    if reduced:
+        per_node = (BYTES_PER_NODE_PASS if steps_per_launch > 1 else BYTES_PER_NODE_SINGLE)[d]
     pass_bytes = per_node * nodes
     gbs = pass_bytes / launch_s / 1e9
     return {"bytes_per_launch": pass_bytes, "bytes_per_node": per_node,
@@ -308,13 +312,14 @@ def form_batched(torch, SV, W, dev):
     mlups = nodes * 1000 / (ms / 1e3) / 1e6
     # launches of the graph: passes of S steps in a mode (-S, rows) or
     # (-16-S, rows), the remainder as single steps; the timed call starts
-    # from a post-collision pool, so each launch reads and writes the 7
-    # independent populations of every node (112 B) and the last one also
-    # writes the two twins (16 B)
+    # from a post-collision pool, so each launch reads and writes the 6 values
+    # that determine a node (96 B; one-wave strips) or its 7 independent
+    # populations (112 B; the other modes), and the last one writes all 9
     S = (-tile[0] - 16 if tile[0] < -16 else -tile[0]) if tile[0] < 0 else 1
     launches = 1000 // S + 1000 % S
-    pass_bytes = BYTES_PER_NODE_PASS[2] * nodes
-    graph_bytes = launches * pass_bytes + 16 * nodes
+    per_node = (BYTES_PER_NODE_PASS if tile[0] < -16 else BYTES_PER_NODE_SINGLE)[2]
+    pass_bytes = per_node * nodes
+    graph_bytes = launches * pass_bytes + (72 - per_node // 2) * nodes
     gbs = graph_bytes / (ms / 1e3) / 1e9
     return {"instances": len(insts), "total_nodes": nodes, "lb_steps": 1000,
             "launch": "one hipGraph of tile-table kernels (S steps per launch for tile "
@@ -550,7 +555,7 @@ def main():
     # what the roofline fraction is taken against
     per_launch = {2: D2_STEPS_PER_PASS, 3: D3_STEPS_PER_PASS}.get(d, 1)
     kernel = {2: d2_kernel(D2_STEPS_PER_PASS, V),
-              3: f"k_steps_d3q19<{D3_STEPS_PER_PASS}, true, true, true>"}.get(d, f"k_step<{d}, true, true>")
+              3: f"k_steps_d3q19<{D3_STEPS_PER_PASS}, 2, 2, true>"}.get(d, f"k_step<{d}, true, true>")
     pr = pass_roofline(d, V, per_launch, kms * 1e3)
     launch_us = pr["kernel_us_per_launch"]
     log(f"{mlups:.1f} MLUPS, kernel {launch_us:.2f} us per launch of {per_launch} steps, "
@@ -576,8 +581,8 @@ def main():
                      "lb_steps_per_launch": per_launch,
                      "kernel_us_per_launch": launch_us,
                      "algorithmic_bytes_per_launch": pr["bytes_per_launch"],
-                     "algorithmic_unit": f"node-pass: the {BYTES_PER_NODE_PASS[d] // 16} independent "
-                                         f"populations of a post-collision node read and written "
+                     "algorithmic_unit": f"node-pass: the {BYTES_PER_NODE_PASS[d] // 16} values that "
+                                         f"determine a post-collision node read and written "
                                          f"once ({BYTES_PER_NODE_PASS[d]} B)",
                      "complete_state_gbs": pr["complete_state_gbs"],
                      "lu_equivalent_gbs": pr["lu_equivalent_gbs"],
@@ -624,7 +629,7 @@ def main():
             spl = {2: D2_STEPS_PER_PASS, 3: D3_STEPS_PER_PASS}.get(w2.d, 1)
             forms[name] = {"lattice": {2: "D2Q9", 3: "D3Q19", 4: "D4Q33"}[w2.d],
                            "kernel": {2: d2_kernel(D2_STEPS_PER_PASS, w2.nodes),
-                                      3: f"k_steps_d3q19<{D3_STEPS_PER_PASS}, true, true, true>"}.get(
+                                      3: f"k_steps_d3q19<{D3_STEPS_PER_PASS}, 2, 2, true>"}.get(
                                           w2.d, f"k_step<{w2.d}, true, true>"),
                            "lb_steps_per_launch": spl,
                            "kernel_us_per_step": round(ms * 1e3, 2),

@@ -160,10 +160,12 @@ lb_status lb_theta_from_velocity(lb_solver* s, const double* u0, double* theta0,
  * The relaxation rates of Theorem 2 send the third-order moments to their
  * equilibrium (zero) at rate 1, so after every collision the two opposite
  * edge populations of each pair of axes are equal (f for (-1,-1) equals f for
- * (+1,+1), f for (+1,-1) equals f for (-1,+1)).  Launches inside one call
- * (D2Q9, D3Q19, D4Q33) therefore store only the other populations and read
- * each such twin from its partner's plane; the last launch of the call, and a
- * launch that ends with a check (LB_OPT_CHECK_INTERVAL), store all of them, so
+ * (+1,+1), f for (+1,-1) equals f for (-1,+1)), and a post-collision node is
+ * determined by its density, first and second moments.  Launches inside one call
+ * therefore hand on only the populations that have no such twin (single steps of
+ * D2Q9, D3Q19, D4Q33) or those 6 / 10 values (the passes of D2Q9 and D3Q19), from
+ * which the reader forms the same bits; the last launch of the call, and a
+ * launch that ends with a check (LB_OPT_CHECK_INTERVAL), store all populations, so
  * the current state between calls is always complete.  The first launch of a
  * call reads twins from their partners too unless the state came from lb_init
  * or lb_set_state: a caller that changes the current buffer in place must go
@@ -392,9 +394,9 @@ lb_status lb_batch_autotune(lb_batch* b, int32_t steps_per_trial, int32_t* best_
  * are captured once into a hipGraph (cached per nsteps, starting pool and
  * whether that pool came from lb_batch_init, up to 16 graphs; capturing a 17th
  * first waits for the batch's stream and clears the cache) and replayed with a
- * single hipGraphLaunch.  Launches store twin populations as in lb_step: only
- * the last launch of a call stores all of them, and the first reads them from
- * their partners unless the pool came from lb_batch_init. */
+ * single hipGraphLaunch.  Launches hand the state on as in lb_step: only the last
+ * launch of a call stores all populations, and the first reads twins from their
+ * partners unless the pool came from lb_batch_init. */
 lb_status lb_batch_step(lb_batch* b, int64_t nsteps, int32_t use_graph);
 
 /* theta (packed V_b per instance) and u (packed 2 x V_b per instance, at

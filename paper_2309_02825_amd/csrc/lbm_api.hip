@@ -405,13 +405,14 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
     }
     // Launch plan: on D2Q9 passes of 8, 4 and 2 steps (within the limit),
     // on D3Q19 passes of 2, then single steps, as runs (steps per launch,
-    // launches).  A state written by a collision holds equal twin
-    // populations (twin<D>, lbm_lattice.h), so a launch reads only the
-    // independent ones unless the state came from lb_init or lb_set_state,
-    // and every launch but the last writes only those; the last launch, and
-    // any launch whose state is checked (LB_OPT_CHECK_INTERVAL), writes all
-    // q, so the state a call leaves (the one every other call sees) is
-    // complete.
+    // launches).  Between two launches the buffer holds no more than the
+    // next one needs (FORM_*, lbm_lattice.h): the collision's 6 or 10
+    // quantities before a pass, the independent populations before a single
+    // step.  The last launch, and any launch whose state is checked
+    // (LB_OPT_CHECK_INTERVAL), writes all q, so the state a call leaves (the
+    // one every other call sees) is complete; the first launch of a call
+    // reads the independent populations of it unless the state came from
+    // lb_init or lb_set_state.
     std::vector<std::pair<int, int64_t>> runs;
     {
         int64_t n = 0;
@@ -430,25 +431,35 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
         if (n < nsteps) runs.emplace_back(1, nsteps - n);
     }
     lb_status st = LB_OK;
+    int form = s->twin_ok ? lbm::FORM_TWIN : lbm::FORM_FULL;
     for (size_t ri = 0; ri < runs.size(); ++ri) {
         const int steps = runs[ri].first;
         for (int64_t t = 0; t < runs[ri].second; ++t) {
             const bool last = ri + 1 == runs.size() && t + 1 == runs[ri].second;
             const bool checked =
                 s->check_interval > 0 && s->since_check + steps >= s->check_interval;
-            const bool rin = s->twin_ok;
-            const bool wout = !last && !checked;
+            // what the source holds, and what the next launch reads: single steps
+            // read populations only
+            const int in = form;
+            const bool next_single = t + 1 == runs[ri].second
+                                         ? ri + 1 < runs.size() && runs[ri + 1].first == 1
+                                         : steps == 1;
+            const int out = last || checked ? lbm::FORM_FULL
+                            : next_single   ? lbm::FORM_TWIN
+                                            : lbm::pass_form(s->d, s->g);
             const double* src = s->buf[s->cur];
             double* dst = s->buf[1 - s->cur];
             if (steps == 1)
-                LB_HIP(lbm::launch_step(s->d, s->g, s->r, src, dst, s->stream, rin, wout),
+                LB_HIP(lbm::launch_step(s->d, s->g, s->r, src, dst, s->stream,
+                                        in == lbm::FORM_TWIN, out == lbm::FORM_TWIN),
                        "step launch");
             else if (s->d == 2)
-                LB_HIP(lbm::launch_steps(steps, s->g, s->r, src, dst, s->stream, rin, wout),
+                LB_HIP(lbm::launch_steps(steps, s->g, s->r, src, dst, s->stream, in, out),
                        "multi-step launch");
             else
-                LB_HIP(lbm::launch_steps3(steps, s->g, s->r, src, dst, s->stream, rin, wout),
+                LB_HIP(lbm::launch_steps3(steps, s->g, s->r, src, dst, s->stream, in, out),
                        "multi-step launch");
+            form = out == lbm::FORM_FULL ? lbm::FORM_TWIN : out;
             s->cur ^= 1;
             s->steps += steps;
             s->twin_ok = true;
@@ -1026,35 +1037,40 @@ static lb_status batch_launch_plain(lb_batch* b, int64_t nsteps, hipStream_t st,
                                     int* cur_out) {
     const int64_t total = batch_launches(b, nsteps);
     int64_t launch = 0;
-    auto io = [&](bool* rin, bool* wout) {
-        *rin = launch > 0 || b->twin_ok;
-        *wout = launch + 1 < total;
+    const int in_first = b->twin_ok ? lbm::FORM_TWIN : lbm::FORM_FULL;
+    int in = in_first, out = in_first;
+    // in / out: the forms of the launch; between: what a launch leaves to the next
+    auto io = [&](int between) {
+        in = launch > 0 ? out : in_first;
+        out = launch + 1 < total ? between : lbm::FORM_FULL;
         ++launch;
     };
-    bool rin, wout;
     if (mode_multi_step(b->tx)) {
         const int S = mode_steps(b->tx);
+        const int passes = lbm::batch_form(b->off32, mode_one_wave(b->tx));
         int64_t n = 0;
         for (; n + S <= nsteps; n += S) {
-            io(&rin, &wout);
+            io(n + 2 * S <= nsteps ? passes : lbm::FORM_TWIN);
             LB_HIP(lbm::launch_batch_steps(S, b->d_insts, b->d_tiles, b->ntiles, b->pool[cur],
                                            b->pool[1 - cur], b->off32, mode_one_wave(b->tx), st,
-                                           rin, wout),
+                                           in, out),
                    "batch multi-step launch");
             cur ^= 1;
         }
         for (; n < nsteps; ++n) {
-            io(&rin, &wout);
+            io(lbm::FORM_TWIN);
             LB_HIP(lbm::launch_batch_step(b->d_insts, b->d_lin, b->nlin, 0, 0, b->pool[cur],
-                                          b->pool[1 - cur], st, rin, wout),
+                                          b->pool[1 - cur], st, in == lbm::FORM_TWIN,
+                                          out == lbm::FORM_TWIN),
                    "batch step launch");
             cur ^= 1;
         }
     } else {
         for (int64_t n = 0; n < nsteps; ++n) {
-            io(&rin, &wout);
+            io(lbm::FORM_TWIN);
             LB_HIP(lbm::launch_batch_step(b->d_insts, b->d_tiles, b->ntiles, b->tx, b->ty,
-                                          b->pool[cur], b->pool[1 - cur], st, rin, wout),
+                                          b->pool[cur], b->pool[1 - cur], st,
+                                          in == lbm::FORM_TWIN, out == lbm::FORM_TWIN),
                    "batch step launch");
             cur ^= 1;
         }
@@ -1132,12 +1148,13 @@ lb_status lb_batch_autotune(lb_batch* b, int32_t steps_per_trial, int32_t* best_
         // their partners' planes and not stored), whatever pool[cur] holds:
         // what lands in the scratch pool is never read.  Times are per step.
         const int per_launch = mode_multi_step(c[0]) ? mode_steps(c[0]) : 1;
+        const int form = lbm::batch_form(b->off32, mode_one_wave(c[0]));
         auto trial = [&](int reps) -> lb_status {
             for (int r = 0; r < reps; ++r) {
                 if (mode_multi_step(c[0]))
                     LB_HIP(lbm::launch_batch_steps(per_launch, b->d_insts, b->d_tiles, b->ntiles,
                                                    b->pool[b->cur], b->pool[1 - b->cur], b->off32,
-                                                   mode_one_wave(c[0]), b->stream, true, true),
+                                                   mode_one_wave(c[0]), b->stream, form, form),
                            "batch multi-step launch");
                 else
                     LB_HIP(lbm::launch_batch_step(b->d_insts, b->d_tiles, b->ntiles, b->tx, b->ty,

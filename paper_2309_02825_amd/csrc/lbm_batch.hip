@@ -201,51 +201,64 @@ __global__ void __launch_bounds__(LW_THREADS) k_batch_steps(const BatchInst* __r
                                  t.x0, t.y0, t.pad, lds);
 }
 
-// The same pass with the one-wave march of k_steps_d2q9: tile (inst, x0,
-// y0, y1) = rows [y0, y1) of the strip at x0 (strip_width(S) columns).
-template <int S, bool OFF32, bool RIN, bool WOUT>
+// The same pass with the one-wave march of k_steps_d2q9: tile (inst, x0, y0,
+// y1) = rows [y0, y1) of the strip at x0 (strip_width(S) columns).  IN / OUT:
+// what the pools hold (FORM_*).
+template <int S, bool OFF32, int IN, int OUT>
 __global__ void __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 k_batch_steps_w(const BatchInst* __restrict__ insts, const BatchTile* __restrict__ tiles,
                 const double* __restrict__ src, double* __restrict__ dst) {
     const BatchTile t = tiles[xcd_remap(blockIdx.x, gridDim.x)];
     const BatchInst& in = insts[t.inst];
-    ms_tile<S, false, OFF32, true, RIN, WOUT>(src + in.offset, dst + in.offset, in.nx, in.ny,
-                                              folded(in.r), t.x0, t.y0, t.pad, 0);
+    ms_tile<S, false, OFF32, true, IN, OUT>(src + in.offset, dst + in.offset, in.nx, in.ny,
+                                            folded(in.r), t.x0, t.y0, t.pad, 0);
 }
 
 }  // namespace
 
-template <bool OFF32, bool RIN, bool WOUT>
-static hipError_t launch_batch_steps_t(int nsteps, const BatchInst* insts, const BatchTile* tiles,
+template <int S, bool OFF32>
+static hipError_t launch_batch_steps_t(const BatchInst* insts, const BatchTile* tiles,
                                        int64_t ntiles, const double* src, double* dst,
-                                       bool one_wave, hipStream_t st) {
+                                       bool one_wave, hipStream_t st, int in, int out) {
     const dim3 grid((unsigned)ntiles), block(one_wave ? MS_THREADS : LW_THREADS);
-    switch (nsteps * (one_wave ? -1 : 1)) {
-#define LBM_BATCH_CASE(S)                                                                      \
-    case S: hipLaunchKernelGGL((k_batch_steps<S, OFF32, RIN, WOUT>), grid, block, 0, st, insts, \
-                               tiles, src, dst); break;                                        \
-    case -S: hipLaunchKernelGGL((k_batch_steps_w<S, OFF32, RIN, WOUT>), grid, block, 0, st,    \
-                                insts, tiles, src, dst); break;
-        LBM_BATCH_CASE(2)
-        LBM_BATCH_CASE(4)
-        LBM_BATCH_CASE(8)
-#undef LBM_BATCH_CASE
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
+    return dispatch_form(in, [&](auto fi) {
+        return dispatch_form(out, [&](auto fo) {
+            constexpr int IN = decltype(fi)::value, OUT = decltype(fo)::value;
+            constexpr bool MOM = IN == FORM_MOM || OUT == FORM_MOM;
+            if (one_wave) {
+                if constexpr (OFF32 || !MOM) {
+                    hipLaunchKernelGGL((k_batch_steps_w<S, OFF32, IN, OUT>), grid, block, 0, st,
+                                       insts, tiles, src, dst);
+                    return hipGetLastError();
+                }
+            } else if constexpr (!MOM) {
+                hipLaunchKernelGGL((k_batch_steps<S, OFF32, IN == FORM_TWIN, OUT == FORM_TWIN>), grid,
+                                   block, 0, st, insts, tiles, src, dst);
+                return hipGetLastError();
+            }
+            return hipErrorInvalidValue;  // batch_form
+        });
+    });
+}
+
+template <int S>
+static hipError_t launch_batch_steps_s(const BatchInst* insts, const BatchTile* tiles,
+                                       int64_t ntiles, const double* src, double* dst, bool off32,
+                                       bool one_wave, hipStream_t st, int in, int out) {
+    return off32 ? launch_batch_steps_t<S, true>(insts, tiles, ntiles, src, dst, one_wave, st, in, out)
+                 : launch_batch_steps_t<S, false>(insts, tiles, ntiles, src, dst, one_wave, st, in, out);
 }
 
 hipError_t launch_batch_steps(int nsteps, const BatchInst* insts, const BatchTile* tiles,
                               int64_t ntiles, const double* src, double* dst, bool off32,
-                              bool one_wave, hipStream_t st, bool rin, bool wout) {
+                              bool one_wave, hipStream_t st, int in, int out) {
     if (ntiles <= 0) return hipSuccess;
-    return dispatch_io(rin, wout, [&](auto ri, auto wo) {
-        constexpr bool RI = decltype(ri)::value, WO = decltype(wo)::value;
-        return off32 ? launch_batch_steps_t<true, RI, WO>(nsteps, insts, tiles, ntiles, src, dst,
-                                                          one_wave, st)
-                     : launch_batch_steps_t<false, RI, WO>(nsteps, insts, tiles, ntiles, src, dst,
-                                                           one_wave, st);
-    });
+    switch (nsteps) {
+        case 2: return launch_batch_steps_s<2>(insts, tiles, ntiles, src, dst, off32, one_wave, st, in, out);
+        case 4: return launch_batch_steps_s<4>(insts, tiles, ntiles, src, dst, off32, one_wave, st, in, out);
+        case 8: return launch_batch_steps_s<8>(insts, tiles, ntiles, src, dst, off32, one_wave, st, in, out);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_batch_step(const BatchInst* insts, const BatchTile* tiles, int64_t ntiles,

@@ -18,7 +18,8 @@ k_steps_d2q9_all(const double* __restrict__ src, double* __restrict__ out, int64
     const int strip = (int)(t % (unsigned)nstrips);
     const int seg = (int)(t / (unsigned)nstrips);
     const int ys = seg * ly;
-    ms_tile<S, true, OFF32, true, RIN, WOUT>(src, out + (int64_t)(S - 1) * stride, g.nx, g.ny,
+    ms_tile<S, true, OFF32, true, RIN ? FORM_TWIN : FORM_FULL, WOUT ? FORM_TWIN : FORM_FULL>(
+        src, out + (int64_t)(S - 1) * stride, g.nx, g.ny,
                                              folded(r), strip * strip_width(S), ys,
                                              min(ys + ly, g.ny), stride);
 }

@@ -1,0 +1,97 @@
+// The D2Q9 pass of S steps, compiled for one S per source.
+#pragma once
+
+#include "lbm_march.h"
+
+namespace lbm {
+namespace {
+
+// One strip of a pass.  Odd row segments march up: two neighbouring segments then
+// read the halo rows they share at the same time (both at their ends, or both at
+// their starts), so the second read finds them in the caches (512^2 +2.7 %,
+// 1024^2 +1.3 %, 2048^2 +1.7 %, 4096^2 +0.7 %).
+template <int S, bool OFF32, bool NT, int IN, int OUT>
+__device__ __forceinline__ void ms_strip(const double* __restrict__ src, double* __restrict__ dst,
+                                         const Geo& g, const Rates& r, int ly, int nstrips) {
+    const unsigned t = xcd_remap(blockIdx.x, gridDim.x);
+    const int strip = (int)(t % (unsigned)nstrips);
+    const int seg = (int)(t / (unsigned)nstrips);
+    const int ys = seg * ly, ye = min(ys + ly, g.ny), x0 = strip * strip_width(S);
+    if (seg & 1)
+        ms_tile<S, false, OFF32, NT, IN, OUT, true>(src, dst, g.nx, g.ny, folded(r), x0, ys, ye);
+    else
+        ms_tile<S, false, OFF32, NT, IN, OUT>(src, dst, g.nx, g.ny, folded(r), x0, ys, ye);
+}
+
+// Two waves per SIMD: the register budget (256 per wave) holds S = 8.
+// RIN / WOUT: the source / the result is in the reduced form that the passes of
+// this grid hand to one another (pass_form).  4096^2, 8 steps: 379 us a launch with
+// the 7 planes of FORM_TWIN, 348 us with the 6 of FORM_MOM (1.61 GB algorithmic).
+template <int S, bool OFF32, bool RIN, bool WOUT>
+__global__ void __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
+k_steps_d2q9(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rates r, int ly,
+             int nstrips) {
+    constexpr int REDUCED = OFF32 ? FORM_MOM : FORM_TWIN;
+    ms_strip<S, OFF32, true, RIN ? REDUCED : FORM_FULL, WOUT ? REDUCED : FORM_FULL>(src, dst, g, r,
+                                                                                    ly, nstrips);
+}
+
+// The same pass with cached stores, for grids whose two states fit in the
+// Infinity Cache (the next pass then reads its input from there).
+template <int S, bool OFF32, bool RIN, bool WOUT>
+__global__ void __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
+k_steps_d2q9_cached(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rates r,
+                    int ly, int nstrips) {
+    ms_strip<S, OFF32, false, RIN ? FORM_MOM : FORM_FULL, WOUT ? FORM_MOM : FORM_FULL>(
+        src, dst, g, r, ly, nstrips);
+}
+
+// The passes at the seams, under 4 GiB: the first of a call on a state that an
+// earlier call left (its twins are equal, so 7 planes are read), and the one before
+// a single step, which reads populations.
+template <int S, bool NT, int IN, int OUT>
+__global__ void __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
+k_steps_d2q9_seam(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rates r, int ly,
+                  int nstrips) {
+    ms_strip<S, true, NT, IN, OUT>(src, dst, g, r, ly, nstrips);
+}
+
+}  // namespace
+
+template <int S>
+hipError_t launch_steps_t(const Geo& g, const Rates& r, const double* src, double* dst,
+                          hipStream_t st, int in, int out) {
+    const int w = strip_width(S);
+    const int nstrips = (g.nx + w - 1) / w;
+    const int ly = steps_rows(g, nstrips, kMinRows);
+    const int nseg = (g.ny + ly - 1) / ly;
+    const dim3 grid((unsigned)((int64_t)nstrips * nseg)), block(MS_THREADS);
+    const bool off32 = ms_off32(g), cached = d2q9_cached_stores(g);
+    return dispatch_form(in, [&](auto fi) {
+        return dispatch_form(out, [&](auto fo) {
+            constexpr int IN = decltype(fi)::value, OUT = decltype(fo)::value;
+            constexpr bool RI = IN != FORM_FULL, WO = OUT != FORM_FULL;
+            if (!off32) {
+                if (IN == FORM_MOM || OUT == FORM_MOM) return hipErrorInvalidValue;  // pass_form
+                hipLaunchKernelGGL((k_steps_d2q9<S, false, RI, WO>), grid, block, 0, st, src, dst,
+                                   g, r, ly, nstrips);
+            } else if constexpr (IN == FORM_TWIN || OUT == FORM_TWIN) {
+                if (cached)
+                    hipLaunchKernelGGL((k_steps_d2q9_seam<S, false, IN, OUT>), grid, block, 0, st,
+                                       src, dst, g, r, ly, nstrips);
+                else
+                    hipLaunchKernelGGL((k_steps_d2q9_seam<S, true, IN, OUT>), grid, block, 0, st,
+                                       src, dst, g, r, ly, nstrips);
+            } else if (cached) {  // both states fit in 256 MB, so under 4 GiB
+                hipLaunchKernelGGL((k_steps_d2q9_cached<S, true, RI, WO>), grid, block, 0, st, src,
+                                   dst, g, r, ly, nstrips);
+            } else {
+                hipLaunchKernelGGL((k_steps_d2q9<S, true, RI, WO>), grid, block, 0, st, src, dst,
+                                   g, r, ly, nstrips);
+            }
+            return hipGetLastError();
+        });
+    });
+}
+
+}  // namespace lbm

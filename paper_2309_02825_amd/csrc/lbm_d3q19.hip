@@ -72,6 +72,7 @@ static_assert(m3_planes_holding(1) == 5 && m3_planes_holding(-1) == 5,
 // need get an out-of-range offset, so the hardware drops those loads (no
 // memory access, the register reads 0) and every wave still issues the same
 // instructions: the two edge rows fetch 5 of the 13 planes.
+template <int IN>
 __device__ __forceinline__ void m3_load_plane(double (&pre)[19], const double* src,
                                               int64_t plane, int zp, int col, int ty) {
     const int64_t n0 = (int64_t)zp * plane;
@@ -83,9 +84,13 @@ __device__ __forceinline__ void m3_load_plane(double (&pre)[19], const double* s
     const unsigned base = (unsigned)((((kk >> 12) - c0) * 19 * 4096 + (kk & 4095)) * 8);
 #pragma unroll
     for (int i = 0; i < 19; ++i)
-        if (twin<3>(i) == i) {
-            const bool need = (ty != 0 || m3_plane_holds(i, 1)) &&
-                              (ty != MS3_TY - 1 || m3_plane_holds(i, -1));
+        if (form_holds<3>(IN, i)) {
+            // FORM_MOM: the populations with e_y = +1 or -1 need theta, j_y, hP_y,
+            // P_xy and P_yz
+            const bool edge_plane = i == 0 || i == 2 || i == 5 || i == 7 || i == 9;
+            const bool first = IN == FORM_MOM ? edge_plane : m3_plane_holds(i, 1);
+            const bool last = IN == FORM_MOM ? edge_plane : m3_plane_holds(i, -1);
+            const bool need = (ty != 0 || first) && (ty != MS3_TY - 1 || last);
             const unsigned off = need ? base + (unsigned)(i * 4096 * 8) : 0x80000000u;
             pre[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
         }
@@ -93,12 +98,37 @@ __device__ __forceinline__ void m3_load_plane(double (&pre)[19], const double* s
 
 // x shift by DPP (pull from lane tx - e_x), then y shift through LDS.  BUF:
 // the input planes come through m3_load_plane (RIN only).
-template <int S, int P, bool RIN, bool WOUT, bool BUF = false>
+// The populations of a column from the planes of a buffer in form IN.
+template <int IN>
+__device__ __forceinline__ void m3_populations(const double (&pre)[19], const FoldedRates& r,
+                                               double (&f)[19]) {
+    if constexpr (IN == FORM_MOM) {
+        expand_d3q19(Mom3{pre[0], pre[1], pre[2], pre[3], pre[4], pre[5], pre[6], pre[7], pre[8],
+                          pre[9]}, r, f);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 19; ++i) f[i] = pre[IN == FORM_TWIN ? twin<3>(i) : i];
+    }
+}
+__device__ __forceinline__ void m3_planes(const Mom3& m, double (&p)[19]) {
+    p[0] = m.th;
+    p[1] = m.jx;
+    p[2] = m.jy;
+    p[3] = m.jz;
+    p[4] = m.hPx;
+    p[5] = m.hPy;
+    p[6] = m.hPz;
+    p[7] = m.Pxy;
+    p[8] = m.Pxz;
+    p[9] = m.Pyz;
+}
+
+template <int S, int P, int IN, int OUT, bool BUF = false>
 __device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
                                           const double* __restrict__ src, double* __restrict__ dst,
                                           const Geo& g, int col, int zs, int x0, int y0,
                                           const FoldedRates& r) {
-    static_assert(!BUF || RIN, "buffer loads serve the reduced state only");
+    static_assert(!BUF || IN != FORM_FULL, "buffer loads serve the reduced state only");
     // a tile row is one wave: ty is uniform across it, and saying so lets the
     // per-row choices (edge-row loads, y exchange) compile to scalar selects
     // and branches instead of lane-masked ones
@@ -106,15 +136,14 @@ __device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
     const int ty = __builtin_amdgcn_readfirstlane(tid / MS3_TX);
     const int64_t plane = (int64_t)g.nx * g.ny;
     double f[19];
-#pragma unroll
-    for (int i = 0; i < 19; ++i) f[i] = st.pre[RIN ? twin<3>(i) : i];
+    m3_populations<IN>(st.pre, r, f);
     if constexpr (BUF) {
-        m3_load_plane(st.pre, src, plane, wrapi(zs - S + k + 1, g.nz), col, ty);
+        m3_load_plane<IN>(st.pre, src, plane, wrapi(zs - S + k + 1, g.nz), col, ty);
     } else {
         const int64_t base = (int64_t)wrapi(zs - S + k + 1, g.nz) * plane + col;
 #pragma unroll
         for (int i = 0; i < 19; ++i)
-            if (!RIN || twin<3>(i) == i) st.pre[i] = src[slot<19>(i, base)];
+            if (form_holds<3>(IN, i)) st.pre[i] = src[slot<19>(i, base)];
     }
     // pull along x (every lane takes part; the edge lanes receive zeros,
     // which reach only halo columns, never a stored output)
@@ -146,7 +175,12 @@ __device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
             }
         }
         if (k >= 2 * j) {
-            collide_d3q19(in, r);
+            Mom3 mom;
+            moments_d3q19(in, r, mom);
+            if (j < S || OUT != FORM_MOM)
+                expand_d3q19(mom, r, in);
+            else
+                m3_planes(mom, in);
             if (j < S) {
                 double* wr = lds + (j & 1) * M3_YMOVERS * M3_THREADS;
 #pragma unroll
@@ -165,7 +199,7 @@ __device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
                                    (int64_t)(y0 - S + ty) * g.nx + (x0 - S + tx);
 #pragma unroll
                 for (int i = 0; i < 19; ++i)
-                    if (!WOUT || twin<3>(i) == i)
+                    if (form_holds<3>(OUT, i))
                         __builtin_nontemporal_store(in[i], dst + slot<19>(i, kk));
             }
         }
@@ -174,7 +208,7 @@ __device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
     if (S & 1) __syncthreads();
 }
 
-template <int S, bool RIN, bool WOUT, bool BUF>
+template <int S, int IN, int OUT, bool BUF>
 __global__ void __launch_bounds__(M3_THREADS) k_steps_d3q19(const double* __restrict__ src,
                                                             double* __restrict__ dst, Geo g,
                                                             Rates r, int lz, int ntx, int nty) {
@@ -194,7 +228,7 @@ __global__ void __launch_bounds__(M3_THREADS) k_steps_d3q19(const double* __rest
         const int64_t base = (int64_t)wrapi(zs - S, g.nz) * g.nx * g.ny + col;
 #pragma unroll
         for (int i = 0; i < 19; ++i)
-            if (!RIN || twin<3>(i) == i) st.pre[i] = src[slot<19>(i, base)];
+            if (form_holds<3>(IN, i)) st.pre[i] = src[slot<19>(i, base)];
     }
 #pragma unroll
     for (int j = 0; j < S; ++j) {
@@ -206,10 +240,10 @@ __global__ void __launch_bounds__(M3_THREADS) k_steps_d3q19(const double* __rest
     // plane pairs in the loop, a last odd plane after it (as in ms_tile)
     int k = 0;
     for (; k + 1 <= kend; k += 2) {
-        ms3_plane<S, 0, RIN, WOUT, BUF>(st, lds, k, src, dst, g, col, zs, x0, y0, fr);
-        ms3_plane<S, 1, RIN, WOUT, BUF>(st, lds, k + 1, src, dst, g, col, zs, x0, y0, fr);
+        ms3_plane<S, 0, IN, OUT, BUF>(st, lds, k, src, dst, g, col, zs, x0, y0, fr);
+        ms3_plane<S, 1, IN, OUT, BUF>(st, lds, k + 1, src, dst, g, col, zs, x0, y0, fr);
     }
-    if (k <= kend) ms3_plane<S, 0, RIN, WOUT, BUF>(st, lds, k, src, dst, g, col, zs, x0, y0, fr);
+    if (k <= kend) ms3_plane<S, 0, IN, OUT, BUF>(st, lds, k, src, dst, g, col, zs, x0, y0, fr);
 }
 
 }  // namespace
@@ -219,7 +253,7 @@ __global__ void __launch_bounds__(M3_THREADS) k_steps_d3q19(const double* __rest
 // segments.
 template <int S>
 static hipError_t launch_steps3_t(const Geo& g, const Rates& r, const double* src, double* dst,
-                                  hipStream_t st, bool rin, bool wout) {
+                                  hipStream_t st, int in, int out) {
     const int ntx = (g.nx + tile_width3(S) - 1) / tile_width3(S);
     const int nty = (g.ny + tile_height3(S) - 1) / tile_height3(S);
     int64_t lz = ((int64_t)g.nz * ntx * nty + 1279) / 1280;
@@ -236,23 +270,25 @@ static hipError_t launch_steps3_t(const Geo& g, const Rates& r, const double* sr
     // about 14 M nodes)
     const int64_t plane = (int64_t)g.nx * g.ny;
     const bool buf = (plane / 4096 + 2) * 19 * 4096 * 8 < ((int64_t)1 << 31);
-    return dispatch_io(rin, wout, [&](auto ri, auto wo) {
-        constexpr bool RI = decltype(ri)::value, WO = decltype(wo)::value;
-        if (RI && buf)
-            hipLaunchKernelGGL((k_steps_d3q19<S, RI, WO, RI>), dim3((unsigned)nb),
-                               dim3(M3_THREADS), 0, st, src, dst, g, r, (int)lz, ntx, nty);
-        else
-            hipLaunchKernelGGL((k_steps_d3q19<S, RI, WO, false>), dim3((unsigned)nb),
-                               dim3(M3_THREADS), 0, st, src, dst, g, r, (int)lz, ntx, nty);
-        return hipGetLastError();
+    return dispatch_form(in, [&](auto fi) {
+        return dispatch_form(out, [&](auto fo) {
+            constexpr int IN = decltype(fi)::value, OUT = decltype(fo)::value;
+            if (IN != FORM_FULL && buf)
+                hipLaunchKernelGGL((k_steps_d3q19<S, IN, OUT, IN != FORM_FULL>), dim3((unsigned)nb),
+                                   dim3(M3_THREADS), 0, st, src, dst, g, r, (int)lz, ntx, nty);
+            else
+                hipLaunchKernelGGL((k_steps_d3q19<S, IN, OUT, false>), dim3((unsigned)nb),
+                                   dim3(M3_THREADS), 0, st, src, dst, g, r, (int)lz, ntx, nty);
+            return hipGetLastError();
+        });
     });
 }
 
 hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
-                         hipStream_t st, bool rin, bool wout) {
+                         hipStream_t st, int in, int out) {
     if (g.nw != 1) return hipErrorInvalidValue;
     switch (nsteps) {
-        case 2: return launch_steps3_t<2>(g, r, src, dst, st, rin, wout);
+        case 2: return launch_steps3_t<2>(g, r, src, dst, st, in, out);
         default: return hipErrorInvalidValue;
     }
 }

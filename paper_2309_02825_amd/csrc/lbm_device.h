@@ -174,5 +174,16 @@ hipError_t dispatch_io(bool rin, bool wout, F&& f) {
     return wout ? f(std::false_type{}, std::true_type{}) : f(std::false_type{}, std::false_type{});
 }
 
+// A buffer form (FORM_*) as a template argument.
+template <typename F>
+hipError_t dispatch_form(int form, F&& f) {
+    switch (form) {
+        case FORM_FULL: return f(std::integral_constant<int, FORM_FULL>{});
+        case FORM_TWIN: return f(std::integral_constant<int, FORM_TWIN>{});
+        case FORM_MOM: return f(std::integral_constant<int, FORM_MOM>{});
+        default: return hipErrorInvalidValue;
+    }
+}
+
 }  // namespace
 }  // namespace lbm

@@ -55,8 +55,14 @@ hipError_t launch_step(int d, const Geo& g, const Rates& r, const double* src, d
 constexpr int MS_THREADS = 64;
 constexpr int MAX_STEPS_PER_PASS = 8;
 __host__ __device__ constexpr int strip_width(int nsteps) { return MS_THREADS - 2 * nsteps; }
+// in, out: what the buffers hold (FORM_*, lbm_lattice.h); FORM_MOM only where
+// pass_form allows it.
 hipError_t launch_steps(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
-                        hipStream_t st, bool rin = false, bool wout = false);
+                        hipStream_t st, int in, int out);
+// The form in which the passes of lattice d hand the state to one another: the
+// smallest that the kernels of this grid read (FORM_MOM; FORM_TWIN for D2Q9
+// states of 4 GiB and more, whose passes index with 64 bits, and for D4Q33).
+int pass_form(int d, const Geo& g);
 // The same passes keeping every intermediate state: step j of the pass
 // (1..nsteps) goes to out + (j - 1) stride; the buffers must not overlap src.
 hipError_t launch_steps_all(int nsteps, const Geo& g, const Rates& r, const double* src,
@@ -69,7 +75,7 @@ constexpr int MAX_STEPS_PER_PASS_3D = 2;
 __host__ __device__ constexpr int tile_width3(int nsteps) { return MS3_TX - 2 * nsteps; }
 __host__ __device__ constexpr int tile_height3(int nsteps) { return MS3_TY - 2 * nsteps; }
 hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
-                         hipStream_t st, bool rin = false, bool wout = false);
+                         hipStream_t st, int in, int out);
 // 1-D grids up to this many nodes run all their steps in one launch, the state in
 // registers (halos through 3 populations x 8 B x 2048 = 48 KiB of LDS).
 constexpr int RESIDENT_MAX_1D = 2048;
@@ -169,6 +175,9 @@ __host__ __device__ constexpr int batch_strip_width(int nsteps) { return LW_THRE
 // batch_strip_width(nsteps) columns run by the two-wave LDS routine.
 hipError_t launch_batch_steps(int nsteps, const BatchInst* insts, const BatchTile* tiles,
                               int64_t ntiles, const double* src, double* dst, bool off32,
-                              bool one_wave, hipStream_t st, bool rin = false, bool wout = false);
+                              bool one_wave, hipStream_t st, int in, int out);
+// The form between two passes of a tile mode (FORM_MOM for the one-wave strips of
+// instances under 4 GiB).
+inline int batch_form(bool off32, bool one_wave) { return off32 && one_wave ? FORM_MOM : FORM_TWIN; }
 
 }  // namespace lbm

@@ -44,6 +44,21 @@ namespace lbm {
 template <int D>
 __host__ __device__ constexpr int twin(int i);
 
+// What a state buffer holds between two launches of one call.  FORM_FULL: all q
+// populations.  FORM_TWIN: a state written by a collision without its twins.
+// FORM_MOM (D2Q9, D3Q19): the 6 / 10 quantities that the last collision took from
+// its distribution, theta, j_a, hP_a and P_ab (Mom2, Mom3), in the planes 0..5 /
+// 0..9.  Theorem 2 leaves a post-collision state no more than these: the
+// third-order moments are 0 and the fourth-order ones 4 w_d theta.  A reader
+// forms the populations with the operations the writer would have used
+// (expand_d2q9, expand_d3q19), so every form gives the same bits.
+enum : int { FORM_FULL = 0, FORM_TWIN = 1, FORM_MOM = 2 };
+// Whether plane i of a buffer in `form` holds something.
+template <int D>
+__host__ __device__ constexpr bool form_holds(int form, int i) {
+    return form == FORM_FULL || (form == FORM_TWIN ? twin<D>(i) == i : i < 1 + 2 * D + D * (D - 1) / 2);
+}
+
 // Relaxation rates and weights of Theorem 2 plus the derived constants the
 // kernels use.  Filled on the host (lbm_params.cpp).
 struct Rates {
@@ -270,24 +285,39 @@ __host__ __device__ __forceinline__ FoldedRates folded(const Rates& r) {
     return FoldedRates{r.f_cj, r.f_cp, r.f_ct, r.f_cq, r.wd};
 }
 
-__device__ __forceinline__ void collide_d2q9(double (&f)[9], const FoldedRates& r) {
+// The six quantities that the D2Q9 collision takes from a distribution; the
+// post-collision populations are a function of them (expand_d2q9).
+struct Mom2 {
+    double th, jx, jy, hPx, hPy, Pxy;
+};
+__device__ __forceinline__ void moments_d2q9(const double (&f)[9], const FoldedRates& r, Mom2& m) {
     const double xp = f[1] + f[5] + f[8], xm = f[3] + f[6] + f[7];
     const double yp = f[2] + f[5] + f[6], ym = f[4] + f[7] + f[8];
-    const double jx = xp - xm, Px = xp + xm, jy = yp - ym, Py = yp + ym;
-    const double th = f[0] + (f[2] + f[4]) + Px;
-    const double Pxy = (f[5] + f[7]) - (f[6] + f[8]);
-    const double tt = r.ct * th;
-    const double hPx = fma(r.cp, Px, tt), hPy = fma(r.cp, Py, tt);
-    const double eR = r.wd * th;
-    f[0] = fma(-2.0, hPx + hPy, fma(-4.0, eR, th));
-    f[1] = fma(r.cj, jx, hPx);
-    f[3] = fma(-r.cj, jx, hPx);
-    f[2] = fma(r.cj, jy, hPy);
-    f[4] = fma(-r.cj, jy, hPy);
-    f[5] = fma(r.cq, Pxy, eR);
+    const double Px = xp + xm, Py = yp + ym;
+    m.jx = xp - xm;
+    m.jy = yp - ym;
+    m.th = f[0] + (f[2] + f[4]) + Px;
+    m.Pxy = (f[5] + f[7]) - (f[6] + f[8]);
+    const double tt = r.ct * m.th;
+    m.hPx = fma(r.cp, Px, tt);
+    m.hPy = fma(r.cp, Py, tt);
+}
+__device__ __forceinline__ void expand_d2q9(const Mom2& m, const FoldedRates& r, double (&f)[9]) {
+    const double eR = r.wd * m.th;
+    f[0] = fma(-2.0, m.hPx + m.hPy, fma(-4.0, eR, m.th));
+    f[1] = fma(r.cj, m.jx, m.hPx);
+    f[3] = fma(-r.cj, m.jx, m.hPx);
+    f[2] = fma(r.cj, m.jy, m.hPy);
+    f[4] = fma(-r.cj, m.jy, m.hPy);
+    f[5] = fma(r.cq, m.Pxy, eR);
     f[7] = f[5];
-    f[6] = fma(-r.cq, Pxy, eR);
+    f[6] = fma(-r.cq, m.Pxy, eR);
     f[8] = f[6];
+}
+__device__ __forceinline__ void collide_d2q9(double (&f)[9], const FoldedRates& r) {
+    Mom2 m;
+    moments_d2q9(f, r, m);
+    expand_d2q9(m, r, f);
 }
 
 // D3Q19 collision folded the same way: with hj_a = (1 - s1)/2 j_a and
@@ -297,7 +327,11 @@ __device__ __forceinline__ void collide_d2q9(double (&f)[9], const FoldedRates& 
 // population is (theta - 12 eR) - 2 (hP_x + hP_y + hP_z), which again keeps
 // sum_i f_i = theta up to unbiased rounding.  With the products fused as in
 // collide_d2q9, 69 double operations against about 140 for the generic form.
-__device__ __forceinline__ void collide_d3q19(double (&f)[19], const FoldedRates& r) {
+// The ten quantities that the D3Q19 collision takes from a distribution.
+struct Mom3 {
+    double th, jx, jy, jz, hPx, hPy, hPz, Pxy, Pxz, Pyz;
+};
+__device__ __forceinline__ void moments_d3q19(const double (&f)[19], const FoldedRates& r, Mom3& m) {
     // partial sums over the five velocities with e_a = +1 / -1
     const double xp = (f[1] + f[7]) + (f[10] + f[11]) + f[14];
     const double xm = (f[4] + f[8]) + (f[9] + f[12]) + f[13];
@@ -305,35 +339,45 @@ __device__ __forceinline__ void collide_d3q19(double (&f)[19], const FoldedRates
     const double ym = (f[5] + f[9]) + (f[10] + f[16]) + f[17];
     const double zp = (f[3] + f[11]) + (f[12] + f[15]) + f[16];
     const double zm = (f[6] + f[13]) + (f[14] + f[17]) + f[18];
-    const double jx = xp - xm, Px = xp + xm, jy = yp - ym, Py = yp + ym;
-    const double jz = zp - zm, Pz = zp + zm;
-    const double th =
-        ((f[0] + Px) + (f[2] + f[5])) + ((f[3] + f[6]) + ((f[15] + f[16]) + (f[17] + f[18])));
-    const double Pxy = (f[7] + f[9]) - (f[8] + f[10]);
-    const double Pxz = (f[11] + f[13]) - (f[12] + f[14]);
-    const double Pyz = (f[15] + f[17]) - (f[16] + f[18]);
-    const double tt = r.ct * th;
-    const double hPx = fma(r.cp, Px, tt), hPy = fma(r.cp, Py, tt), hPz = fma(r.cp, Pz, tt);
-    const double eR = r.wd * th;
-    f[0] = fma(-2.0, (hPx + hPy) + hPz, fma(-12.0, eR, th));
-    f[1] = fma(r.cj, jx, hPx);
-    f[4] = fma(-r.cj, jx, hPx);
-    f[2] = fma(r.cj, jy, hPy);
-    f[5] = fma(-r.cj, jy, hPy);
-    f[3] = fma(r.cj, jz, hPz);
-    f[6] = fma(-r.cj, jz, hPz);
-    f[7] = fma(r.cq, Pxy, eR);
+    const double Px = xp + xm, Py = yp + ym, Pz = zp + zm;
+    m.jx = xp - xm;
+    m.jy = yp - ym;
+    m.jz = zp - zm;
+    m.th = ((f[0] + Px) + (f[2] + f[5])) + ((f[3] + f[6]) + ((f[15] + f[16]) + (f[17] + f[18])));
+    m.Pxy = (f[7] + f[9]) - (f[8] + f[10]);
+    m.Pxz = (f[11] + f[13]) - (f[12] + f[14]);
+    m.Pyz = (f[15] + f[17]) - (f[16] + f[18]);
+    const double tt = r.ct * m.th;
+    m.hPx = fma(r.cp, Px, tt);
+    m.hPy = fma(r.cp, Py, tt);
+    m.hPz = fma(r.cp, Pz, tt);
+}
+__device__ __forceinline__ void expand_d3q19(const Mom3& m, const FoldedRates& r, double (&f)[19]) {
+    const double eR = r.wd * m.th;
+    f[0] = fma(-2.0, (m.hPx + m.hPy) + m.hPz, fma(-12.0, eR, m.th));
+    f[1] = fma(r.cj, m.jx, m.hPx);
+    f[4] = fma(-r.cj, m.jx, m.hPx);
+    f[2] = fma(r.cj, m.jy, m.hPy);
+    f[5] = fma(-r.cj, m.jy, m.hPy);
+    f[3] = fma(r.cj, m.jz, m.hPz);
+    f[6] = fma(-r.cj, m.jz, m.hPz);
+    f[7] = fma(r.cq, m.Pxy, eR);
     f[9] = f[7];
-    f[8] = fma(-r.cq, Pxy, eR);
+    f[8] = fma(-r.cq, m.Pxy, eR);
     f[10] = f[8];
-    f[11] = fma(r.cq, Pxz, eR);
+    f[11] = fma(r.cq, m.Pxz, eR);
     f[13] = f[11];
-    f[12] = fma(-r.cq, Pxz, eR);
+    f[12] = fma(-r.cq, m.Pxz, eR);
     f[14] = f[12];
-    f[15] = fma(r.cq, Pyz, eR);
+    f[15] = fma(r.cq, m.Pyz, eR);
     f[17] = f[15];
-    f[16] = fma(-r.cq, Pyz, eR);
+    f[16] = fma(-r.cq, m.Pyz, eR);
     f[18] = f[16];
+}
+__device__ __forceinline__ void collide_d3q19(double (&f)[19], const FoldedRates& r) {
+    Mom3 m;
+    moments_d3q19(f, r, m);
+    expand_d3q19(m, r, f);
 }
 
 // D1Q3 collision folded the same way: hP = (1 - s21)/2 P + (s21/6) theta with

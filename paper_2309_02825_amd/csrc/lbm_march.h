@@ -98,6 +98,27 @@ struct MsState {
     double u[2][S][3];  // e_y = +1 populations of the rows of each parity
 };
 
+// The populations of a node from the planes of a buffer in form IN, and the
+// planes of FORM_MOM.
+template <int IN>
+__device__ __forceinline__ void ms_populations(const double (&pre)[9], const FoldedRates& r,
+                                               double (&f)[9]) {
+    if constexpr (IN == FORM_MOM) {
+        expand_d2q9(Mom2{pre[0], pre[1], pre[2], pre[3], pre[4], pre[5]}, r, f);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) f[i] = pre[IN == FORM_TWIN ? twin<2>(i) : i];
+    }
+}
+__device__ __forceinline__ void ms_planes(const Mom2& m, double (&p)[9]) {
+    p[0] = m.th;
+    p[1] = m.jx;
+    p[2] = m.jy;
+    p[3] = m.hPx;
+    p[4] = m.hPy;
+    p[5] = m.Pxy;
+}
+
 // One iteration k of the march; P = k & 1; stages above ACTIVE are skipped
 // (pipeline fill), stage S stores only when ACTIVE == S.  ALL: stage j < S
 // also stores its rows of [ys, ye) to dst - (S - j) stride (the state after
@@ -105,8 +126,8 @@ struct MsState {
 // writes with non-temporal stores (otherwise through the caches).  UP: the
 // march runs from row ye - 1 + S up to ys - S, so the roles of e_y = +1 and
 // e_y = -1 in the row delays swap (same arithmetic per node).
-template <int S, int P, int ACTIVE, bool ALL, bool OFF32, bool NT = true, bool RIN = false,
-          bool WOUT = false, bool UP = false>
+template <int S, int P, int ACTIVE, bool ALL, bool OFF32, bool NT = true,
+          int IN = FORM_FULL, int OUT = FORM_FULL, bool UP = false>
 __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
                                        const double* __restrict__ src, double* __restrict__ dst,
                                        int nx, int ny, int gx, int ys, int x0, const FoldedRates& r,
@@ -114,8 +135,7 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
     constexpr int W = MS_THREADS - 2 * S;
     const int lane = threadIdx.x;
     double f[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) f[i] = st.pre[RIN ? twin<2>(i) : i];
+    ms_populations<IN>(st.pre, r, f);
     {
         // Prefetch the next input row.  In the last iteration the row is not
         // used (its address is wrapped, so in bounds); loading it anyway
@@ -128,7 +148,7 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
         const MsAddr<OFF32> a(wrapi(row, ny) * nx + gx);
 #pragma unroll
         for (int i = 0; i < 9; ++i)
-            if (!RIN || twin<2>(i) == i) st.pre[i] = a.load(src, i);
+            if (form_holds<2>(IN, i)) st.pre[i] = a.load(src, i);
     }
 #pragma unroll
     for (int j = 1; j <= S; ++j) {
@@ -152,7 +172,12 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
             }
         }
         if (j <= ACTIVE) {
-            collide_d2q9(in, r);
+            Mom2 mom;
+            moments_d2q9(in, r, mom);
+            if (j < S || OUT != FORM_MOM)
+                expand_d2q9(mom, r, in);
+            else
+                ms_planes(mom, in);
 #pragma unroll
             for (int i = 0; i < 9; ++i) f[i] = in[i];
             if (j == S && ACTIVE == S && lane >= S && lane < S + W && x0 - S + lane < nx) {
@@ -160,7 +185,7 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
                 const MsAddr<OFF32> a(wrapi(row, ny) * nx + x0 - S + lane);
 #pragma unroll
                 for (int i = 0; i < 9; ++i) {
-                    if (WOUT && twin<2>(i) != i) continue;
+                    if (!form_holds<2>(OUT, i)) continue;
                     if constexpr (NT)
                         a.store(dst, i, in[i]);
                     else
@@ -189,13 +214,13 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
                             0x00020000);
 #pragma unroll
                         for (int i = 0; i < 9; ++i)
-                            if (!WOUT || twin<2>(i) == i)
+                            if (form_holds<2>(OUT, i))
                                 __builtin_amdgcn_raw_buffer_store_b64(
                                     __builtin_bit_cast(MsU2, in[i]), rs, a.off, i * CHUNK * 8, 2);
                     } else {
 #pragma unroll
                         for (int i = 0; i < 9; ++i)
-                            if (!WOUT || twin<2>(i) == i) a.store(out, i, in[i]);
+                            if (form_holds<2>(OUT, i)) a.store(out, i, in[i]);
                     }
                 }
             }
@@ -203,15 +228,15 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
     }
 }
 
-template <int S, int K, bool ALL, bool OFF32, bool NT = true, bool RIN = false, bool WOUT = false,
-          bool UP = false>
+template <int S, int K, bool ALL, bool OFF32, bool NT = true, int IN = FORM_FULL,
+          int OUT = FORM_FULL, bool UP = false>
 __device__ __forceinline__ void ms_fill(MsState<S>& st, const double* __restrict__ src,
                                         double* __restrict__ dst, int nx, int ny, int gx, int ys,
                                         int x0, const FoldedRates& r, int nrows, int64_t stride) {
     if constexpr (K < 2 * S) {
-        ms_row<S, K & 1, K / 2, ALL, OFF32, NT, RIN, WOUT, UP>(st, K, src, dst, nx, ny, gx, ys, x0,
+        ms_row<S, K & 1, K / 2, ALL, OFF32, NT, IN, OUT, UP>(st, K, src, dst, nx, ny, gx, ys, x0,
                                                                r, nrows, stride);
-        ms_fill<S, K + 1, ALL, OFF32, NT, RIN, WOUT, UP>(st, src, dst, nx, ny, gx, ys, x0, r, nrows,
+        ms_fill<S, K + 1, ALL, OFF32, NT, IN, OUT, UP>(st, src, dst, nx, ny, gx, ys, x0, r, nrows,
                                                          stride);
     }
 }
@@ -220,8 +245,8 @@ __device__ __forceinline__ void ms_fill(MsState<S>& st, const double* __restrict
 // D2Q9 grid by S steps (reads rows ys-S .. ye-1+S and columns x0-S ..
 // x0+63-S, wrapped periodically), marching down the rows or, with UP, up.
 // All 64 lanes of the wave must be active.
-template <int S, bool ALL, bool OFF32, bool NT = true, bool RIN = false, bool WOUT = false,
-          bool UP = false>
+template <int S, bool ALL, bool OFF32, bool NT = true, int IN = FORM_FULL,
+          int OUT = FORM_FULL, bool UP = false>
 __device__ __forceinline__ void ms_tile(const double* __restrict__ src, double* __restrict__ dst,
                                         int nx, int ny, const FoldedRates& r, int x0, int ys,
                                         int ye, int64_t stride = 0) {
@@ -232,14 +257,14 @@ __device__ __forceinline__ void ms_tile(const double* __restrict__ src, double* 
         const MsAddr<OFF32> a(wrapi(UP ? ye - 1 + S : ys - S, ny) * nx + gx);
 #pragma unroll
         for (int i = 0; i < 9; ++i)
-            if (!RIN || twin<2>(i) == i) st.pre[i] = a.load(src, i);
+            if (form_holds<2>(IN, i)) st.pre[i] = a.load(src, i);
     }
 #pragma unroll
     for (int j = 0; j < S; ++j)
 #pragma unroll
         for (int a = 0; a < 3; ++a) st.z[j][a] = st.u[0][j][a] = st.u[1][j][a] = 0.0;
     const int nrows = ye - ys;
-    ms_fill<S, 0, ALL, OFF32, NT, RIN, WOUT, UP>(st, src, dst, nx, ny, gx, ys, x0, r, nrows,
+    ms_fill<S, 0, ALL, OFF32, NT, IN, OUT, UP>(st, src, dst, nx, ny, gx, ys, x0, r, nrows,
                                                  stride);
     // whole row pairs in the loop and a last odd row after it: the loop then
     // has a single path back to its head, and the compiler keeps the row
@@ -247,13 +272,13 @@ __device__ __forceinline__ void ms_tile(const double* __restrict__ src, double* 
     // 37 instead of 52 copies per row pair)
     int k = 2 * S;
     for (; k + 1 <= kend; k += 2) {
-        ms_row<S, 0, S, ALL, OFF32, NT, RIN, WOUT, UP>(st, k, src, dst, nx, ny, gx, ys, x0, r,
+        ms_row<S, 0, S, ALL, OFF32, NT, IN, OUT, UP>(st, k, src, dst, nx, ny, gx, ys, x0, r,
                                                        nrows, stride);
-        ms_row<S, 1, S, ALL, OFF32, NT, RIN, WOUT, UP>(st, k + 1, src, dst, nx, ny, gx, ys, x0, r,
+        ms_row<S, 1, S, ALL, OFF32, NT, IN, OUT, UP>(st, k + 1, src, dst, nx, ny, gx, ys, x0, r,
                                                        nrows, stride);
     }
     if (k <= kend)
-        ms_row<S, 0, S, ALL, OFF32, NT, RIN, WOUT, UP>(st, k, src, dst, nx, ny, gx, ys, x0, r,
+        ms_row<S, 0, S, ALL, OFF32, NT, IN, OUT, UP>(st, k, src, dst, nx, ny, gx, ys, x0, r,
                                                        nrows, stride);
 }
 
