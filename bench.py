@@ -49,7 +49,8 @@ D3_STEPS_PER_PASS = 2
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_k_step.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2309_02825_amd", "csrc", n)
                   for n in ("lbm_kernels.hip", "lbm_d1.hip", "lbm_d2q9.hip", "lbm_d2q9_pass.h",
-                            "lbm_d2q9_adjoint.hip", "lbm_d3q19.hip", "lbm_batch.hip",
+                            "lbm_d2q9_adjoint.hip", "lbm_d3q19.hip",
+                            "lbm_d3q19_march.hip", "lbm_batch.hip",
                             "lbm_device.h", "lbm_march.h", "lbm_lattice.h", "lbm_kernels.h")]
 
 
@@ -555,7 +556,7 @@ def main():
     # what the roofline fraction is taken against
     per_launch = {2: D2_STEPS_PER_PASS, 3: D3_STEPS_PER_PASS}.get(d, 1)
     kernel = {2: d2_kernel(D2_STEPS_PER_PASS, V),
-              3: f"k_steps_d3q19<{D3_STEPS_PER_PASS}, 2, 2, true>"}.get(d, f"k_step<{d}, true, true>")
+              3: "k_march_d3q19<2>"}.get(d, f"k_step<{d}, true, true>")
     pr = pass_roofline(d, V, per_launch, kms * 1e3)
     launch_us = pr["kernel_us_per_launch"]
     log(f"{mlups:.1f} MLUPS, kernel {launch_us:.2f} us per launch of {per_launch} steps, "
@@ -629,7 +630,7 @@ def main():
             spl = {2: D2_STEPS_PER_PASS, 3: D3_STEPS_PER_PASS}.get(w2.d, 1)
             forms[name] = {"lattice": {2: "D2Q9", 3: "D3Q19", 4: "D4Q33"}[w2.d],
                            "kernel": {2: d2_kernel(D2_STEPS_PER_PASS, w2.nodes),
-                                      3: f"k_steps_d3q19<{D3_STEPS_PER_PASS}, 2, 2, true>"}.get(
+                                      3: "k_march_d3q19<2>"}.get(
                                           w2.d, f"k_step<{w2.d}, true, true>"),
                            "lb_steps_per_launch": spl,
                            "kernel_us_per_step": round(ms * 1e3, 2),

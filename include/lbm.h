@@ -190,7 +190,8 @@ lb_status lb_step_bounded(lb_solver* s, int64_t nsteps, const double* walls);
  * strip of columns, neighbouring columns exchange populations by lane shifts
  * and rows are delayed in registers.  D3Q19: passes of 2 steps (x-y tiles
  * marching along z, populations exchanged through LDS) and a single step for
- * an odd remainder, whenever the limit is 2 or more.  Values below 2 make
+ * an odd remainder, when the limit is 2 or more and the grid is large enough
+ * for a pass to take less than two single steps.  Values below 2 make
  * every step a separate launch; others are rounded down to 2, 4 or 8.  D1Q3
  * and D4Q33 take single steps.  Every grouping gives bitwise the result of
  * single steps.  Unknown options are LB_ERR_INVALID_ARG.

@@ -404,7 +404,7 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
         return after_steps(s, nsteps);
     }
     // Launch plan: on D2Q9 passes of 8, 4 and 2 steps (within the limit),
-    // on D3Q19 passes of 2, then single steps, as runs (steps per launch,
+    // on D3Q19 passes of 2 where passes3 has them, then single steps, as runs (steps per launch,
     // launches).  Between two launches the buffer holds no more than the
     // next one needs (FORM_*, lbm_lattice.h): the collision's 6 or 10
     // quantities before a pass, the independent populations before a single
@@ -422,7 +422,8 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
                 if (k > 0) runs.emplace_back(pass, k);
                 n += k * pass;
             }
-        } else if (s->d == 3 && s->steps_per_pass >= lbm::MAX_STEPS_PER_PASS_3D) {
+        } else if (s->d == 3 && s->steps_per_pass >= lbm::MAX_STEPS_PER_PASS_3D &&
+                   lbm::passes3(s->g)) {
             const int pass = lbm::MAX_STEPS_PER_PASS_3D;
             const int64_t k = (nsteps - n) / pass;
             if (k > 0) runs.emplace_back(pass, k);

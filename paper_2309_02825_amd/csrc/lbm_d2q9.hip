@@ -13,25 +13,24 @@ namespace lbm {
 // exceed 512 rows.  Measured minimum (MLUPS at 8 steps per pass): 512^2
 // 47,500 at 24 rows, 70,200 at 8; 1024^2 132,000 and 148,300; 2048^2 and
 // 4096^2 unchanged (their segments are longer).
-// Blocks of k_steps_d2q9 one round holds on the current device (8 per CU),
-// looked up once per device.
-static int round_slots() {
+// Compute units of the current device, looked up once per device.
+int compute_units() {
     constexpr int kMaxDevices = 64;
     static std::atomic<int> cached[kMaxDevices] = {};
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0) dev = 0;
     const int d = dev < kMaxDevices ? dev : kMaxDevices - 1;
-    int slots = cached[d].load(std::memory_order_relaxed);
-    if (slots == 0) {
-        int cus = 0;
+    int cus = cached[d].load(std::memory_order_relaxed);
+    if (cus == 0) {
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             cus <= 0)
             cus = 256;
-        slots = 8 * cus;
-        cached[d].store(slots, std::memory_order_relaxed);
+        cached[d].store(cus, std::memory_order_relaxed);
     }
-    return slots;
+    return cus;
 }
+// Blocks of k_steps_d2q9 one round holds (8 per CU).
+static int round_slots() { return 8 * compute_units(); }
 
 int steps_rows(const Geo& g, int nstrips, int min_rows) {
     const int slots = round_slots();
@@ -49,7 +48,7 @@ int steps_rows(const Geo& g, int nstrips, int min_rows) {
 }
 
 int pass_form(int d, const Geo& g) {
-    return d == 2 ? (ms_off32(g) ? FORM_MOM : FORM_TWIN) : d == 3 ? FORM_MOM : FORM_TWIN;
+    return (d == 2 && ms_off32(g)) || (d == 3 && march3_fits(g)) ? FORM_MOM : FORM_TWIN;
 }
 
 extern template hipError_t launch_steps_t<2>(const Geo&, const Rates&, const double*, double*,

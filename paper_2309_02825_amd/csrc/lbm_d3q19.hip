@@ -1,4 +1,7 @@
 // D3Q19 passes of two steps.
+#include <algorithm>
+#include <cmath>
+
 #include "lbm_device.h"
 
 namespace lbm {
@@ -72,7 +75,6 @@ static_assert(m3_planes_holding(1) == 5 && m3_planes_holding(-1) == 5,
 // need get an out-of-range offset, so the hardware drops those loads (no
 // memory access, the register reads 0) and every wave still issues the same
 // instructions: the two edge rows fetch 5 of the 13 planes.
-template <int IN>
 __device__ __forceinline__ void m3_load_plane(double (&pre)[19], const double* src,
                                               int64_t plane, int zp, int col, int ty) {
     const int64_t n0 = (int64_t)zp * plane;
@@ -84,32 +86,16 @@ __device__ __forceinline__ void m3_load_plane(double (&pre)[19], const double* s
     const unsigned base = (unsigned)((((kk >> 12) - c0) * 19 * 4096 + (kk & 4095)) * 8);
 #pragma unroll
     for (int i = 0; i < 19; ++i)
-        if (form_holds<3>(IN, i)) {
-            // FORM_MOM: the populations with e_y = +1 or -1 need theta, j_y, hP_y,
-            // P_xy and P_yz
-            const bool edge_plane = i == 0 || i == 2 || i == 5 || i == 7 || i == 9;
-            const bool first = IN == FORM_MOM ? edge_plane : m3_plane_holds(i, 1);
-            const bool last = IN == FORM_MOM ? edge_plane : m3_plane_holds(i, -1);
-            const bool need = (ty != 0 || first) && (ty != MS3_TY - 1 || last);
+        if (form_holds<3>(FORM_TWIN, i)) {
+            const bool need = (ty != 0 || m3_plane_holds(i, 1)) &&
+                              (ty != MS3_TY - 1 || m3_plane_holds(i, -1));
             const unsigned off = need ? base + (unsigned)(i * 4096 * 8) : 0x80000000u;
             pre[i] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
         }
 }
 
 // x shift by DPP (pull from lane tx - e_x), then y shift through LDS.  BUF:
-// the input planes come through m3_load_plane (RIN only).
-// The populations of a column from the planes of a buffer in form IN.
-template <int IN>
-__device__ __forceinline__ void m3_populations(const double (&pre)[19], const FoldedRates& r,
-                                               double (&f)[19]) {
-    if constexpr (IN == FORM_MOM) {
-        expand_d3q19(Mom3{pre[0], pre[1], pre[2], pre[3], pre[4], pre[5], pre[6], pre[7], pre[8],
-                          pre[9]}, r, f);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 19; ++i) f[i] = pre[IN == FORM_TWIN ? twin<3>(i) : i];
-    }
-}
+// the input planes come through m3_load_plane (FORM_TWIN only).
 __device__ __forceinline__ void m3_planes(const Mom3& m, double (&p)[19]) {
     p[0] = m.th;
     p[1] = m.jx;
@@ -128,7 +114,7 @@ __device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
                                           const double* __restrict__ src, double* __restrict__ dst,
                                           const Geo& g, int col, int zs, int x0, int y0,
                                           const FoldedRates& r) {
-    static_assert(!BUF || IN != FORM_FULL, "buffer loads serve the reduced state only");
+    static_assert(IN != FORM_MOM && (!BUF || IN == FORM_TWIN), "buffer loads serve the reduced state only");
     // a tile row is one wave: ty is uniform across it, and saying so lets the
     // per-row choices (edge-row loads, y exchange) compile to scalar selects
     // and branches instead of lane-masked ones
@@ -136,9 +122,10 @@ __device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
     const int ty = __builtin_amdgcn_readfirstlane(tid / MS3_TX);
     const int64_t plane = (int64_t)g.nx * g.ny;
     double f[19];
-    m3_populations<IN>(st.pre, r, f);
+#pragma unroll
+    for (int i = 0; i < 19; ++i) f[i] = st.pre[IN == FORM_TWIN ? twin<3>(i) : i];
     if constexpr (BUF) {
-        m3_load_plane<IN>(st.pre, src, plane, wrapi(zs - S + k + 1, g.nz), col, ty);
+        m3_load_plane(st.pre, src, plane, wrapi(zs - S + k + 1, g.nz), col, ty);
     } else {
         const int64_t base = (int64_t)wrapi(zs - S + k + 1, g.nz) * plane + col;
 #pragma unroll
@@ -248,49 +235,92 @@ __global__ void __launch_bounds__(M3_THREADS) k_steps_d3q19(const double* __rest
 
 }  // namespace
 
-// Planes per segment of a D3Q19 pass: 64, fewer (at least 16) when the grid
-// would otherwise give under about 1280 blocks, then evened out over the
-// segments.
+// Planes per segment of a D3Q19 pass over `tiles` (x, y) tiles: a block marches its
+// planes one after the other, four more than it stores, and the chip runs one block
+// per CU at a time, so the cost of a choice is rounds x (planes + 4), with whole
+// rounds while there are few.  At most 64 planes (512^3: 64 planes 2,797 us a step,
+// 128 2,829).  100^3, 12 planes (one round) against the 16 of a rule without rounds:
+// 24.7 and 30.1 us a step.
+static int segment_planes(int nz, int64_t tiles, double* plane_rounds = nullptr) {
+    const int cus = compute_units();
+    int best = nz;
+    double best_cost = 1e300;
+    for (int nseg = (nz + 63) / 64; nseg <= nz; ++nseg) {
+        const int lz = (nz + nseg - 1) / nseg;
+        if (nseg > 1 && lz < 4) break;
+        double rounds = (double)(tiles * ((nz + lz - 1) / lz)) / cus;
+        if (rounds < 8.0) rounds = std::ceil(rounds);
+        const double cost = rounds * (lz + 4);
+        if (cost < best_cost * 0.999) {
+            best_cost = cost;
+            best = lz;
+        }
+    }
+    if (plane_rounds) *plane_rounds = best_cost;
+    return best;
+}
+
+bool march3_fits(const Geo& g) {
+    // buffer addressing needs the chunks of one z-plane under 2 GiB (planes up to
+    // about 14 M nodes)
+    return ((int64_t)g.nx * g.ny / CHUNK + 2) * 19 * CHUNK * 8 < ((int64_t)1 << 31);
+}
+
 template <int S>
 static hipError_t launch_steps3_t(const Geo& g, const Rates& r, const double* src, double* dst,
                                   hipStream_t st, int in, int out) {
     const int ntx = (g.nx + tile_width3(S) - 1) / tile_width3(S);
     const int nty = (g.ny + tile_height3(S) - 1) / tile_height3(S);
-    int64_t lz = ((int64_t)g.nz * ntx * nty + 1279) / 1280;
-    if (lz > 64) lz = 64;
-    if (lz < 16) lz = 16;
-    if (lz > g.nz) lz = g.nz;
-    // segments of equal length: a short last segment is mostly pipeline fill
-    // (512 x 512 x 64: 58 + 6 planes gave 16.6 GLUPS, 32 + 32 planes 25.6)
-    lz = (g.nz + (g.nz + lz - 1) / lz - 1) / ((g.nz + lz - 1) / lz);
+    const int lz = segment_planes(g.nz, (int64_t)ntx * nty);
     const int64_t nseg = (g.nz + lz - 1) / lz;  // every segment non-empty
     const int64_t nb = (int64_t)ntx * nty * nseg;
     if (nb > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
-    // buffer loads need the chunks of one z-plane under 2 GiB (planes up to
-    // about 14 M nodes)
-    const int64_t plane = (int64_t)g.nx * g.ny;
-    const bool buf = (plane / 4096 + 2) * 19 * 4096 * 8 < ((int64_t)1 << 31);
-    return dispatch_form(in, [&](auto fi) {
-        return dispatch_form(out, [&](auto fo) {
-            constexpr int IN = decltype(fi)::value, OUT = decltype(fo)::value;
-            if (IN != FORM_FULL && buf)
-                hipLaunchKernelGGL((k_steps_d3q19<S, IN, OUT, IN != FORM_FULL>), dim3((unsigned)nb),
-                                   dim3(M3_THREADS), 0, st, src, dst, g, r, (int)lz, ntx, nty);
-            else
-                hipLaunchKernelGGL((k_steps_d3q19<S, IN, OUT, false>), dim3((unsigned)nb),
-                                   dim3(M3_THREADS), 0, st, src, dst, g, r, (int)lz, ntx, nty);
-            return hipGetLastError();
-        });
+    const bool buf = march3_fits(g);
+    const dim3 grid((unsigned)nb), block(M3_THREADS);
+    return dispatch_form(out, [&](auto fo) {
+        constexpr int OUT = decltype(fo)::value;
+        if (in == FORM_FULL)
+            hipLaunchKernelGGL((k_steps_d3q19<S, FORM_FULL, OUT, false>), grid, block, 0, st, src,
+                               dst, g, r, lz, ntx, nty);
+        else if (buf)
+            hipLaunchKernelGGL((k_steps_d3q19<S, FORM_TWIN, OUT, true>), grid, block, 0, st, src,
+                               dst, g, r, lz, ntx, nty);
+        else
+            hipLaunchKernelGGL((k_steps_d3q19<S, FORM_TWIN, OUT, false>), grid, block, 0, st, src,
+                               dst, g, r, lz, ntx, nty);
+        return hipGetLastError();
     });
 }
 
+static int64_t march3_tiles(const Geo& g) {
+    return (int64_t)((g.nx + MARCH3_W - 1) / MARCH3_W) * ((g.ny + MARCH3_H - 1) / MARCH3_H);
+}
+
+// Two steps: from FORM_MOM, the passes of a run, on the taller tiles of
+// k_march_d3q19; the first launch of a call, which reads 19 or 13 planes, and every
+// launch on z-planes of 2 GiB on the 8-row tiles.
 hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
                          hipStream_t st, int in, int out) {
-    if (g.nw != 1) return hipErrorInvalidValue;
-    switch (nsteps) {
-        case 2: return launch_steps3_t<2>(g, r, src, dst, st, in, out);
-        default: return hipErrorInvalidValue;
+    if (g.nw != 1 || nsteps != 2) return hipErrorInvalidValue;
+    if (in == FORM_MOM) {
+        if (!march3_fits(g)) return hipErrorInvalidValue;  // pass_form
+        return launch_march3(g, r, src, dst, st, segment_planes(g.nz, march3_tiles(g)), out);
     }
+    return launch_steps3_t<2>(g, r, src, dst, st, in, out);
+}
+
+// Whether a run on this grid takes passes of two steps: below some 200 thousand
+// nodes a pass is a few blocks that march eight planes each, and two launches of
+// one step take less.  In us: a pass 5 and 1.95 for a plane of the march (a block
+// alone on its CU); a single step one per 18 thousand nodes or 40 thousand threads
+// of its launch grid, the larger (40^3: 5.2 a step in single steps, 10.4 in passes;
+// 64^3 12.6 and 10.8).
+bool passes3(const Geo& g) {
+    double planes;
+    (void)segment_planes(g.nz, march3_tiles(g), &planes);
+    const double threads = (double)launch_shape(3, g).nblocks * 256.0;
+    const double single = std::max((double)g.V / 18000.0, threads / 40000.0);
+    return 5.0 + 1.95 * planes < 2.0 * single;
 }
 
 }  // namespace lbm

@@ -61,8 +61,9 @@ hipError_t launch_steps(int nsteps, const Geo& g, const Rates& r, const double* 
                         hipStream_t st, int in, int out);
 // The form in which the passes of lattice d hand the state to one another: the
 // smallest that the kernels of this grid read (FORM_MOM; FORM_TWIN for D2Q9
-// states of 4 GiB and more, whose passes index with 64 bits, and for D4Q33).
+// states of 4 GiB and D3Q19 z-planes of 2 GiB and more, and for D4Q33).
 int pass_form(int d, const Geo& g);
+int compute_units();  // of the current device
 // The same passes keeping every intermediate state: step j of the pass
 // (1..nsteps) goes to out + (j - 1) stride; the buffers must not overlap src.
 hipError_t launch_steps_all(int nsteps, const Geo& g, const Rates& r, const double* src,
@@ -76,6 +77,13 @@ __host__ __device__ constexpr int tile_width3(int nsteps) { return MS3_TX - 2 * 
 __host__ __device__ constexpr int tile_height3(int nsteps) { return MS3_TY - 2 * nsteps; }
 hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
                          hipStream_t st, int in, int out);
+bool passes3(const Geo& g);  // whether runs on this grid take passes of two steps
+// The same two steps from FORM_MOM on taller tiles, segments of lz planes; z-planes
+// under 2 GiB.
+constexpr int MARCH3_W = 60, MARCH3_H = 8;
+bool march3_fits(const Geo& g);
+hipError_t launch_march3(const Geo& g, const Rates& r, const double* src, double* dst,
+                         hipStream_t st, int lz, int out);
 // 1-D grids up to this many nodes run all their steps in one launch, the state in
 // registers (halos through 3 populations x 8 B x 2048 = 48 KiB of LDS).
 constexpr int RESIDENT_MAX_1D = 2048;

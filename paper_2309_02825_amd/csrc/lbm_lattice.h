@@ -327,7 +327,10 @@ __device__ __forceinline__ void collide_d2q9(double (&f)[9], const FoldedRates& 
 // population is (theta - 12 eR) - 2 (hP_x + hP_y + hP_z), which again keeps
 // sum_i f_i = theta up to unbiased rounding.  With the products fused as in
 // collide_d2q9, 69 double operations against about 140 for the generic form.
-// The ten quantities that the D3Q19 collision takes from a distribution.
+// The ten quantities that the D3Q19 collision takes from a distribution.  Every sum
+// takes the populations with e_z = +1 and 0 before those with e_z = -1: a march
+// along z then keeps nine partial sums of a plane instead of 14 populations while
+// it waits for the next one (k_march_d3q19).
 struct Mom3 {
     double th, jx, jy, jz, hPx, hPy, hPz, Pxy, Pxz, Pyz;
 };
@@ -343,10 +346,11 @@ __device__ __forceinline__ void moments_d3q19(const double (&f)[19], const Folde
     m.jx = xp - xm;
     m.jy = yp - ym;
     m.jz = zp - zm;
-    m.th = ((f[0] + Px) + (f[2] + f[5])) + ((f[3] + f[6]) + ((f[15] + f[16]) + (f[17] + f[18])));
+    const double T = (f[0] + (f[2] + f[5])) + (f[3] + (f[15] + f[16]));
+    m.th = (T + (f[6] + (f[17] + f[18]))) + Px;
     m.Pxy = (f[7] + f[9]) - (f[8] + f[10]);
-    m.Pxz = (f[11] + f[13]) - (f[12] + f[14]);
-    m.Pyz = (f[15] + f[17]) - (f[16] + f[18]);
+    m.Pxz = (f[11] - f[12]) + (f[13] - f[14]);
+    m.Pyz = (f[15] - f[16]) + (f[17] - f[18]);
     const double tt = r.ct * m.th;
     m.hPx = fma(r.cp, Px, tt);
     m.hPy = fma(r.cp, Py, tt);

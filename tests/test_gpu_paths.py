@@ -58,3 +58,29 @@ def test_1d_run_equals_single_steps(n):
             s.close()
         assert bool(torch.isfinite(states[0]).all())
         assert torch.equal(states[0], states[1]), (n, bounded)
+
+
+@pytest.mark.parametrize("grid", [(60, 48, 40), (61, 49, 90), (121, 17, 129), (64, 64, 64),
+                                  (300, 24, 67), (59, 200, 33), (12, 300, 150), (64, 64, 63)])
+@pytest.mark.parametrize("steps", [2, 6, 7])
+def test_d3q19_march_equals_single_steps(grid, steps):
+    """Runs that take the tall-tile passes (and grids next to the line where single
+    steps are taken instead), whole and split, odd and even, against
+    lb_step_buffers single steps, bit for bit; edges of tiles and segments."""
+    _say("D3Q19 march", grid, steps)
+    s, ref = _solver(grid, 0.11), _solver(grid, 0.11)
+    th0 = _rough(grid, 5)
+    s.init(th0, None)
+    ref.init(th0, None)
+    cur = 0
+    for n in (steps, steps + 3):
+        s.step(n)
+        for _ in range(n):
+            ref.step_buffers(ref.bufs[cur], ref.bufs[1 - cur])
+            cur ^= 1
+        if cur:
+            ref.bufs[0].copy_(ref.bufs[1])
+            cur = 0
+        assert torch.equal(s.get_state(), ref.get_state()), (grid, n)
+    s.close()
+    ref.close()
