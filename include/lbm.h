@@ -185,8 +185,10 @@ lb_status lb_step_bounded(lb_solver* s, int64_t nsteps, const double* walls);
 /* Options of a solver (lb_set_option).
  * LB_OPT_STEPS_PER_PASS (default 8): the most time steps lb_step advances with
  * one pass over the state in HBM (temporal blocking: the intermediate steps
- * stay on chip).  D2Q9: a run of nsteps is split greedily into passes of 8,
- * 4 and 2 steps (within the limit) and single steps; one wave marches down a
+ * stay on chip).  D2Q9: where one workgroup per CU holds the grid in register
+ * tiles, a run of nsteps is split into the fewest passes within the limit, of
+ * equal lengths; on larger grids greedily into passes of 8, 4 and 2 steps
+ * (within the limit) and single steps, where one wave marches down a
  * strip of columns, neighbouring columns exchange populations by lane shifts
  * and rows are delayed in registers.  D3Q19: passes of 2 steps (x-y tiles
  * marching along z, populations exchanged through LDS) and a single step for

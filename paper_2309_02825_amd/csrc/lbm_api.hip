@@ -403,8 +403,9 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
         s->steps += nsteps;
         return after_steps(s, nsteps);
     }
-    // Launch plan: on D2Q9 passes of 8, 4 and 2 steps (within the limit),
-    // on D3Q19 passes of 2 where passes3 has them, then single steps, as runs (steps per launch,
+    // Launch plan: on D2Q9 grids of one round of tiles (tile_rows) the fewest
+    // passes within the limit, of equal lengths; on larger D2Q9 grids passes
+    // of 8, 4 and 2 steps (within the limit); on D3Q19 passes of 2 where passes3 has them, then single steps, as runs (steps per launch,
     // launches).  Between two launches the buffer holds no more than the
     // next one needs (FORM_*, lbm_lattice.h): the collision's 6 or 10
     // quantities before a pass, the independent populations before a single
@@ -414,9 +415,17 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
     // reads the independent populations of it unless the state came from
     // lb_init or lb_set_state.
     std::vector<std::pair<int, int64_t>> runs;
+    const bool tiles = s->d == 2 && s->steps_per_pass > 1 && lbm::tile_rows(s->g) > 0;
     {
         int64_t n = 0;
-        if (s->d == 2) {
+        if (tiles) {
+            const int64_t passes = (nsteps + s->steps_per_pass - 1) / s->steps_per_pass;
+            const int64_t k = passes > 0 ? nsteps % passes : 0;  // passes of one step more
+            const int each = passes > 0 ? (int)(nsteps / passes) : 0;
+            if (k > 0) runs.emplace_back(each + 1, k);
+            if (passes > k) runs.emplace_back(each, passes - k);
+            n = nsteps;
+        } else if (s->d == 2) {
             for (int pass = s->steps_per_pass; pass >= 2; pass /= 2) {
                 const int64_t k = (nsteps - n) / pass;
                 if (k > 0) runs.emplace_back(pass, k);
@@ -454,6 +463,9 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
                 LB_HIP(lbm::launch_step(s->d, s->g, s->r, src, dst, s->stream,
                                         in == lbm::FORM_TWIN, out == lbm::FORM_TWIN),
                        "step launch");
+            else if (tiles)
+                LB_HIP(lbm::launch_tile(steps, s->g, s->r, src, dst, s->stream, in, out),
+                       "multi-step launch");
             else if (s->d == 2)
                 LB_HIP(lbm::launch_steps(steps, s->g, s->r, src, dst, s->stream, in, out),
                        "multi-step launch");

@@ -64,6 +64,11 @@ hipError_t launch_steps(int nsteps, const Geo& g, const Rates& r, const double* 
 // states of 4 GiB and D3Q19 z-planes of 2 GiB and more, and for D4Q33).
 int pass_form(int d, const Geo& g);
 int compute_units();  // of the current device
+// nsteps (1..8) D2Q9 steps in one pass of workgroup tiles held in registers, on
+// grids with tile_rows(g) > 0; bitwise equal too.
+int tile_rows(const Geo& g);
+hipError_t launch_tile(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
+                       hipStream_t st, int in, int out);
 // The same passes keeping every intermediate state: step j of the pass
 // (1..nsteps) goes to out + (j - 1) stride; the buffers must not overlap src.
 hipError_t launch_steps_all(int nsteps, const Geo& g, const Rates& r, const double* src,

@@ -84,3 +84,31 @@ def test_d3q19_march_equals_single_steps(grid, steps):
         assert torch.equal(s.get_state(), ref.get_state()), (grid, n)
     s.close()
     ref.close()
+
+
+@pytest.mark.parametrize("grid", [(1, 1), (2, 3), (5, 1), (1, 40), (48, 17), (49, 16), (47, 300),
+                                  (96, 95), (255, 257), (513, 511), (620, 640), (700, 700),
+                                  (12000, 3)])
+@pytest.mark.parametrize("limit", [2, 8])
+def test_d2q9_tiles_equal_single_steps(grid, limit):
+    """Runs of every length around the pass limit on grids that go by register
+    tiles (and the first sizes beyond them), against lb_step_buffers single steps,
+    bit for bit, from the initial state and from the states that calls leave."""
+    _say("D2Q9 tiles", grid, limit)
+    s, ref = _solver(grid, 0.31), _solver(grid, 0.31)
+    s.set_steps_per_pass(limit)
+    th0 = _rough(grid, 6)
+    s.init(th0, None)
+    ref.init(th0, None)
+    cur = 0
+    for n in (7, 1, 8, 2, 9, 17, 3, 5):
+        s.step(n)
+        for _ in range(n):
+            ref.step_buffers(ref.bufs[cur], ref.bufs[1 - cur])
+            cur ^= 1
+        if cur:
+            ref.bufs[0].copy_(ref.bufs[1])
+            cur = 0
+        assert torch.equal(s.get_state(), ref.get_state()), (grid, limit, n)
+    s.close()
+    ref.close()
