@@ -209,6 +209,7 @@ struct lb_solver {
     double* wall_now;    // bounded: theta at the two end nodes at the current time
     double* seg_partials;  // lb_adjoint_segment: one partials table per launch
     int64_t seg_cap;       // doubles seg_partials holds
+    double* potential;     // lb_theta_from_velocity's workspace, allocated by its first call
     double* scratch;       // this device's copy of `scratch` (lb_adjoint_segment_static)
 };
 
@@ -298,6 +299,7 @@ lb_status lb_create(const lb_config* cfg, void* hip_stream, double* f_a, double*
     s->wall_now = nullptr;
     s->seg_partials = nullptr;
     s->seg_cap = 0;
+    s->potential = nullptr;
     s->scratch = nullptr;
     // set-up of lb_adjoint_segment_static: the device copy of the scratch
     // array of the device current at creation (the solver's device)
@@ -325,6 +327,7 @@ lb_status lb_destroy(lb_solver* s) {
     if (s->flag) (void)hipFree(s->flag);
     if (s->wall_now) (void)hipFree(s->wall_now);
     if (s->seg_partials) (void)hipFree(s->seg_partials);
+    if (s->potential) (void)hipFree(s->potential);
     delete s;
     return LB_OK;
 }
@@ -607,13 +610,13 @@ lb_status lb_theta_from_velocity(lb_solver* s, const double* u0, double* theta0,
     if (!s || !u0 || !theta0) return fail(LB_ERR_INVALID_ARG, "NULL argument");
     lb_status st = not_bounded(s, "lb_theta_from_velocity is periodic only");
     if (st != LB_OK) return st;
-    const int64_t nw = lbm::potential_workspace(s->d, s->g);
-    double* work = nullptr;
-    LB_HIP(hipMalloc((void**)&work, sizeof(double) * (size_t)nw), "hipMalloc potential workspace");
-    hipError_t e = lbm::launch_theta_from_velocity(s->d, s->g, s->cfg.dx, s->cfg.nu, u0, work,
-                                                   theta0, grad, s->stream);
+    if (!s->potential)  // kept for the next call, freed with the solver
+        LB_HIP(hipMalloc((void**)&s->potential,
+                         sizeof(double) * (size_t)lbm::potential_workspace(s->d, s->g)),
+               "hipMalloc potential workspace");
+    hipError_t e = lbm::launch_theta_from_velocity(s->d, s->g, s->cfg.dx, s->cfg.nu, u0,
+                                                   s->potential, theta0, grad, s->stream);
     hipError_t e2 = hipStreamSynchronize(s->stream);
-    (void)hipFree(work);
     if (e != hipSuccess) return hip_fail(e, "theta_from_velocity launch");
     if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
     return LB_OK;

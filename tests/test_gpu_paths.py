@@ -112,3 +112,27 @@ def test_d2q9_tiles_equal_single_steps(grid, limit):
         assert torch.equal(s.get_state(), ref.get_state()), (grid, limit, n)
     s.close()
     ref.close()
+
+
+@pytest.mark.parametrize("grid", [(1,), (2,), (3,), (17,), (257,), (5, 3), (64, 65), (1, 300),
+                                  (300, 1), (4097, 18), (16, 33, 17), (3, 4, 5, 6), (1, 1, 70)])
+def test_theta_from_velocity_segments(grid):
+    """The front end's path integral in segments against the oracle's walk along
+    each line, on periodic fields of any shape (random values: no cancellation to
+    hide an error); the sums round differently, so to 1e-14 of the largest
+    potential, whose exponential theta0 is."""
+    from oracle import oracle as O
+    _say("theta from velocity", grid)
+    nu = 0.05
+    dx = 1.0 / max(grid)
+    rng = np.random.default_rng(3)
+    u0 = rng.uniform(-0.05, 0.1, size=(len(grid),) + tuple(reversed(grid)))
+    want, want_grad = O.theta_from_velocity(u0, dx, nu)
+    from paper_2309_02825_amd import solver as SV
+    s = SV.Solver(grid, dx, 0.1 * dx * dx / nu, nu, device=_dev())
+    for _ in range(2):  # the second call reuses the workspace
+        th, gr = s.theta_from_velocity(torch.from_numpy(u0).to(_dev()))
+        # |phi| / (2 nu) stays below 0.1 * 4 / 0.1 = 4: theta within e^4 of 1
+        assert np.max(np.abs(th.cpu().numpy() / want - 1.0)) <= 4 * 4 * max(grid) * 2.3e-16 + 1e-14
+        assert np.max(np.abs(gr.cpu().numpy() - want_grad)) <= 1e-12 * np.max(np.abs(want_grad))
+    s.close()
