@@ -123,7 +123,7 @@ k_tile_d2q9(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rat
     TileRows<R, TWINS> a;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-        const MsAddr<true> at(wrapi(y0 - S + top + q, g.ny) * g.nx + gx);
+        const MsAddr<true, form_planes<2>(IN)> at(wrapi(y0 - S + top + q, g.ny) * g.nx + gx);
 #pragma unroll
         for (int i = 0; i < 9; ++i)
             if (form_holds<2>(IN, i)) a.f[q][i] = at.load(src, i);
@@ -168,7 +168,7 @@ k_tile_d2q9(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rat
         for (int q = 0; q < R; ++q) {
             const int row = top + q;
             if (row >= S && row < rin - S) {
-                const MsAddr<true> at((y0 - S + row) * g.nx + x);
+                const MsAddr<true, form_planes<2>(OUT)> at((y0 - S + row) * g.nx + x);
 #pragma unroll
                 for (int i = 0; i < 9; ++i)
                     if (form_holds<2>(OUT, i)) at.store_cached(dst, i, b.f[q][twin<2>(i)]);

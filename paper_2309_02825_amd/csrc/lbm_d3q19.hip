@@ -187,7 +187,7 @@ __device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
 #pragma unroll
                 for (int i = 0; i < 19; ++i)
                     if (form_holds<3>(OUT, i))
-                        __builtin_nontemporal_store(in[i], dst + slot<19>(i, kk));
+                        __builtin_nontemporal_store(in[i], dst + slot<form_planes<3>(OUT)>(i, kk));
             }
         }
         if (j < S) __syncthreads();

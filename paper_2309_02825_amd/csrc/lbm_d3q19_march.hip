@@ -123,6 +123,7 @@ __device__ __forceinline__ void march_stage(MarchSums& s, const MarchPops& p, co
 
 // One z-plane of a chunked D3Q19 buffer as a buffer resource, and the byte offset of
 // population 0 of a node of it.
+template <int Q>
 struct MarchPlane {
     __amdgpu_buffer_rsrc_t rs;
     int64_t n0, c0;
@@ -130,12 +131,12 @@ struct MarchPlane {
         n0 = (int64_t)z * plane;
         c0 = n0 >> LOG2_CHUNK;
         const int64_t c1 = (n0 + plane - 1) >> LOG2_CHUNK;
-        rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(buf) + c0 * 19 * CHUNK, (short)0,
-                                               (int)((c1 - c0 + 1) * 19 * CHUNK * 8), 0x00020000);
+        rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(buf) + c0 * Q * CHUNK, (short)0,
+                                               (int)((c1 - c0 + 1) * Q * CHUNK * 8), 0x00020000);
     }
     __device__ __forceinline__ unsigned offset(int col) const {
         const int kk = (int)(n0 - (c0 << LOG2_CHUNK)) + col;  // node within the plane's chunks
-        return (unsigned)(((kk >> LOG2_CHUNK) * 19 * (int)CHUNK + (kk & ((int)CHUNK - 1))) * 8);
+        return (unsigned)(((kk >> LOG2_CHUNK) * Q * (int)CHUNK + (kk & ((int)CHUNK - 1))) * 8);
     }
 };
 typedef unsigned int MarchU2 __attribute__((__vector_size__(8)));  // a double as buffer data
@@ -170,7 +171,7 @@ k_march_d3q19(const double* __restrict__ src, double* __restrict__ dst, Geo g, R
     // e_y = +1 and -1, which need theta, j_y, hP_y, P_xy and P_yz: the other five
     // planes get an out-of-range offset, which reads nothing.
     auto load = [&](int z) {
-        const MarchPlane pl(src, plane, wrapi(z, g.nz));
+        const MarchPlane<form_planes<3>(FORM_MOM)> pl(src, plane, wrapi(z, g.nz));
         const unsigned off = pl.offset(col), trim = edge ? 0x80000000u : off;
         auto get = [&](unsigned o, int i) {
             return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
@@ -210,7 +211,7 @@ k_march_d3q19(const double* __restrict__ src, double* __restrict__ dst, Geo g, R
             __syncthreads();
             march_stage(s2, p, up + BUF, dn + BUF, r, m);
             if constexpr (decltype(stores)::value) {
-                const MarchPlane pl(dst, plane, max(zs + k - 4, zs));
+                const MarchPlane<form_planes<3>(OUT)> pl(dst, plane, max(zs + k - 4, zs));
                 const unsigned off = own && k >= 4 ? pl.offset(y * g.nx + x) : 0x80000000u;
                 auto put = [&](int i, double v) {
                     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(MarchU2, v), pl.rs,

@@ -59,6 +59,12 @@ __host__ __device__ constexpr bool form_holds(int form, int i) {
     return form == FORM_FULL || (form == FORM_TWIN ? twin<D>(i) == i : i < 1 + 2 * D + D * (D - 1) / 2);
 }
 
+// Planes of a buffer in `form`.
+template <int D>
+__host__ __device__ constexpr int form_planes(int form) {
+    return form == FORM_MOM ? 1 + 2 * D + D * (D - 1) / 2 : 1 + 2 * D * D;
+}
+
 // Relaxation rates and weights of Theorem 2 plus the derived constants the
 // kernels use.  Filled on the host (lbm_params.cpp).
 struct Rates {

@@ -49,12 +49,12 @@ __device__ __forceinline__ GChar* wave_base(const double* p) {
     const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
     return (GChar*)(((unsigned long long)hi << 32) | lo);
 }
-template <bool OFF32> struct MsAddr;
+template <bool OFF32, int Q = 9> struct MsAddr;  // Q: planes of the buffer
 typedef unsigned int MsU2 __attribute__((__vector_size__(8)));  // a double as buffer data
-template <> struct MsAddr<true> {
+template <int Q> struct MsAddr<true, Q> {
     unsigned off;
     __device__ __forceinline__ explicit MsAddr(int k)
-        : off((unsigned)((((k >> 12) * 9) << 12) | (k & (CHUNK - 1))) * 8u) {}
+        : off((unsigned)((((k >> 12) * Q) << 12) | (k & (CHUNK - 1))) * 8u) {}
     __device__ __forceinline__ double load(const double* p, int i) const {
         return *(GDouble*)(wave_base(p + (int64_t)i * CHUNK) + off);
     }
@@ -65,15 +65,15 @@ template <> struct MsAddr<true> {
         *(GDouble*)(wave_base(p + (int64_t)i * CHUNK) + off) = v;
     }
 };
-template <> struct MsAddr<false> {
+template <int Q> struct MsAddr<false, Q> {
     int k;
     __device__ __forceinline__ explicit MsAddr(int k_) : k(k_) {}
-    __device__ __forceinline__ double load(const double* p, int i) const { return p[slot<9>(i, k)]; }
+    __device__ __forceinline__ double load(const double* p, int i) const { return p[slot<Q>(i, k)]; }
     __device__ __forceinline__ void store(double* p, int i, double v) const {
-        __builtin_nontemporal_store(v, p + slot<9>(i, k));
+        __builtin_nontemporal_store(v, p + slot<Q>(i, k));
     }
     __device__ __forceinline__ void store_cached(double* p, int i, double v) const {
-        p[slot<9>(i, k)] = v;
+        p[slot<Q>(i, k)] = v;
     }
 };
 // Whether a D2Q9 state buffer of g allows MsAddr<true>.
@@ -145,7 +145,7 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
         // stores of stage S still make that wait cover the previous row's
         // stores; two waves per SIMD hide it.
         const int row = UP ? ys + nrows - 1 + S - (k + 1) : ys - S + k + 1;
-        const MsAddr<OFF32> a(wrapi(row, ny) * nx + gx);
+        const MsAddr<OFF32, form_planes<2>(IN)> a(wrapi(row, ny) * nx + gx);
 #pragma unroll
         for (int i = 0; i < 9; ++i)
             if (form_holds<2>(IN, i)) st.pre[i] = a.load(src, i);
@@ -182,7 +182,7 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
             for (int i = 0; i < 9; ++i) f[i] = in[i];
             if (j == S && ACTIVE == S && lane >= S && lane < S + W && x0 - S + lane < nx) {
                 const int row = UP ? ys + nrows - 1 + 2 * S - k : ys - 2 * S + k;
-                const MsAddr<OFF32> a(wrapi(row, ny) * nx + x0 - S + lane);
+                const MsAddr<OFF32, form_planes<2>(OUT)> a(wrapi(row, ny) * nx + x0 - S + lane);
 #pragma unroll
                 for (int i = 0; i < 9; ++i) {
                     if (!form_holds<2>(OUT, i)) continue;
@@ -254,7 +254,7 @@ __device__ __forceinline__ void ms_tile(const double* __restrict__ src, double* 
     const int kend = ye - ys + 2 * S - 1;  // >= 2S
     MsState<S> st;
     {
-        const MsAddr<OFF32> a(wrapi(UP ? ye - 1 + S : ys - S, ny) * nx + gx);
+        const MsAddr<OFF32, form_planes<2>(IN)> a(wrapi(UP ? ye - 1 + S : ys - S, ny) * nx + gx);
 #pragma unroll
         for (int i = 0; i < 9; ++i)
             if (form_holds<2>(IN, i)) st.pre[i] = a.load(src, i);
