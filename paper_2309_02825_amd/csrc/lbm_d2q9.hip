@@ -1,18 +1,11 @@
 // D2Q9 passes of several steps: eight per pass, and the choice of a pass.
+#include <algorithm>
 #include <atomic>
 
 #include "lbm_d2q9_pass.h"
 
 namespace lbm {
 
-// Rows per segment of an S-step launch.  A one-wave block of k_steps_d2q9
-// holds about 240 VGPRs, so a CU runs 8 of them at once: the segments are
-// cut so that all blocks fit in one round of 8 x (number of CUs) (fewer,
-// longer segments amortise the 2S-row pipeline fill; a partial second round
-// costs far more), at least 8 rows, and in more rounds when a segment would
-// exceed 512 rows.  Measured minimum (MLUPS at 8 steps per pass): 512^2
-// 47,500 at 24 rows, 70,200 at 8; 1024^2 132,000 and 148,300; 2048^2 and
-// 4096^2 unchanged (their segments are longer).
 // Compute units of the current device, looked up once per device.
 int compute_units() {
     constexpr int kMaxDevices = 64;
@@ -31,6 +24,27 @@ int compute_units() {
 }
 // Blocks of k_steps_d2q9 one round holds (8 per CU).
 static int round_slots() { return 8 * compute_units(); }
+
+// Rows per segment of an S-step launch.  A one-wave block of k_steps_d2q9
+// holds about 250 VGPRs, so a CU runs 8 of them at once: the segments are
+// cut so that all blocks fit in one round of 8 x (number of CUs) (fewer,
+// longer segments amortise the 2S-row pipeline fill; a partial second round
+// costs far more), at least min_rows, and in more rounds when a segment would
+// exceed 512 rows.  Half a round, one wave per SIMD, is taken instead where it is
+// faster: a row then takes 0.90 us against 1.47 with two waves on the SIMD, and a
+// segment of ly rows costs ly + S of them (its fill computes half of 2S rows), so
+// that halving the fill wins below 14 rows at eight steps (us a step, 2,048 and 1,024
+// slots: 800^2 3.36 and 2.97, 1000 x 700 3.44 and 3.07, 1024^2 4.14 and 4.06; 1280^2,
+// 18 rows, 5.33 and 5.42).
+int pass_rows(const Geo& g, int nstrips, int min_rows, int nsteps) {
+    const int two = steps_rows(g, nstrips, min_rows);
+    const int64_t nseg = std::max(1, 4 * compute_units() / nstrips);
+    const int one = (int)std::min<int64_t>(g.ny, (g.ny + nseg - 1) / nseg);
+    return one > two && nseg * nstrips <= 4 * compute_units() &&
+                   0.90 * (one + nsteps) < 1.47 * (two + nsteps)
+               ? one
+               : two;
+}
 
 int steps_rows(const Geo& g, int nstrips, int min_rows) {
     const int slots = round_slots();

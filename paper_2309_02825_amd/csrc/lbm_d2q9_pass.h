@@ -63,7 +63,7 @@ hipError_t launch_steps_t(const Geo& g, const Rates& r, const double* src, doubl
                           hipStream_t st, int in, int out) {
     const int w = strip_width(S);
     const int nstrips = (g.nx + w - 1) / w;
-    const int ly = steps_rows(g, nstrips, kMinRows);
+    const int ly = pass_rows(g, nstrips, kMinRows, S);
     const int nseg = (g.ny + ly - 1) / ly;
     const dim3 grid((unsigned)((int64_t)nstrips * nseg)), block(MS_THREADS);
     const bool off32 = ms_off32(g), cached = d2q9_cached_stores(g);

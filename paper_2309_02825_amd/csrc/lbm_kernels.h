@@ -36,6 +36,15 @@ struct Geo {
     int64_t V;          // nx * ny * nz * nw
 };
 
+// Whether both state buffers fit in the 256 MB Infinity Cache: the next launch then
+// finds what a launch stored through the caches there; otherwise non-temporal stores
+// are faster.
+constexpr uint64_t kInfinityCacheBytes = 256ull << 20;
+inline bool states_fit_cache(int d, const Geo& g) {
+    return 2ull * (1 + 2 * d * d) * (uint64_t)chunks_of(g.V) * CHUNK * sizeof(double) <=
+           kInfinityCacheBytes;
+}
+
 // Launch shape of the per-node kernels for one grid.
 struct Launch {
     dim3 grid, block;
@@ -127,7 +136,7 @@ hipError_t launch_theta_from_velocity(int d, const Geo& g, double dx, double nu,
                                       double* work, double* theta, double* grad,
                                       hipStream_t st);
 hipError_t launch_check_theta(const double* theta, int64_t n, int* flag, hipStream_t st);
-// Sets *flag (atomic OR) if theta = sum_i f_i is not finite and positive at some node.
+// Sets *flag (host memory) if theta = sum_i f_i is not finite and positive at some node.
 hipError_t launch_check_state(int d, const Geo& g, const double* state, int* flag,
                               hipStream_t st);
 

@@ -29,7 +29,7 @@ namespace {
 // the plane of the population it equals (twin<D>); WOUT: the twins are not
 // stored (dst then holds a state that only a RIN read may use).  Both leave
 // the arithmetic, and so the result, bitwise unchanged.
-template <int D, bool RIN = false, bool WOUT = false>
+template <int D, bool RIN = false, bool WOUT = false, bool NT = true>
 __global__ void __launch_bounds__(256) k_step(const double* __restrict__ src,
                                               double* __restrict__ dst, Geo g, Rates r) {
     constexpr int Q = Lat<D>::Q;
@@ -43,7 +43,12 @@ __global__ void __launch_bounds__(256) k_step(const double* __restrict__ src,
     const int k = node_index(g, c);
 #pragma unroll
     for (int i = 0; i < Q; ++i)
-        if (!WOUT || twin<D>(i) == i) __builtin_nontemporal_store(f[i], dst + slot<Q>(i, k));
+        if (!WOUT || twin<D>(i) == i) {
+            if constexpr (NT)
+                __builtin_nontemporal_store(f[i], dst + slot<Q>(i, k));
+            else
+                dst[slot<Q>(i, k)] = f[i];
+        }
 }
 
 // ---------------------------------------------------------------------------
@@ -72,7 +77,7 @@ __device__ double fd4(const double* __restrict__ th, const Geo& g, const int (&c
 // axis: 128^3 128 us; now 74, 2048^2 140 and 65; 512^3, 25 GB, 9.3 and 8.4 ms, held by
 // the rate of its 19 write streams).
 // Otherwise g is the fourth-order difference of theta0.
-template <int D, bool GRAD>
+template <int D, bool GRAD, bool NT>
 __global__ void __launch_bounds__(256) k_init(const double* __restrict__ th0,
                                               const double* __restrict__ grad,
                                               double* __restrict__ dst, Geo g, Rates r) {
@@ -106,7 +111,11 @@ __global__ void __launch_bounds__(256) k_init(const double* __restrict__ th0,
             if (nnz<D>(i) == 1) ax = e == 1 ? ga : -ga;
         }
         const double w = weight<D>(i, r);
-        __builtin_nontemporal_store(w * t - r.dx * w * eg - corr * ax, dst + slot<Q>(i, k));
+        const double f0 = w * t - r.dx * w * eg - corr * ax;
+        if constexpr (NT)
+            __builtin_nontemporal_store(f0, dst + slot<Q>(i, k));
+        else
+            dst[slot<Q>(i, k)] = f0;
     }
 }
 
@@ -193,9 +202,9 @@ __global__ void __launch_bounds__(256) k_layout_to_dense(const double* __restric
     for (int i = 0; i < Q; ++i) dense[(int64_t)i * g.V + k] = buf[slot<Q>(i, k)];
 }
 
-// Sets *flag when theta = sum_i f_i of some node of the state is not finite
-// and positive (a diverged or corrupted run: u = -2 nu grad theta / theta
-// needs theta > 0).
+// Sets *flag (pinned host memory: a plain store of 1 from whichever waves find one)
+// when theta = sum_i f_i of some node of the state is not finite and positive (a
+// diverged or corrupted run: u = -2 nu grad theta / theta needs theta > 0).
 template <int D>
 __global__ void __launch_bounds__(256) k_check_state(const double* __restrict__ src, int* flag,
                                                      Geo g) {
@@ -206,7 +215,7 @@ __global__ void __launch_bounds__(256) k_check_state(const double* __restrict__ 
     double th = 0.0;
 #pragma unroll
     for (int i = 0; i < Q; ++i) th += src[slot<Q>(i, pull_index<D>(nb, i))];
-    if (!(th > 0.0) || !isfinite(th)) atomicOr(flag, 1);
+    if (!(th > 0.0) || !isfinite(th)) *(volatile int*)flag = 1;
 }
 
 __global__ void __launch_bounds__(256) k_check_theta(const double* __restrict__ th, int64_t n,
@@ -559,14 +568,21 @@ hipError_t launch_step(int d, const Geo& g, const Rates& r, const double* src, d
     return dispatch(d, [&](auto dc) {
         constexpr int DD = decltype(dc)::value;
         const Launch L = launch_shape(DD, g);
+        const bool nt = !states_fit_cache(DD, g);
         if constexpr (DD == 1) {  // D1Q3 has no twins
-            hipLaunchKernelGGL((k_step<1>), L.grid, L.block, 0, st, src, dst, g, r);
-            return hipGetLastError();
+            return dispatch_io(nt, false, [&](auto n, auto) {
+                hipLaunchKernelGGL((k_step<1, false, false, decltype(n)::value>), L.grid, L.block,
+                                   0, st, src, dst, g, r);
+                return hipGetLastError();
+            });
         } else {
             return dispatch_io(rin, wout, [&](auto ri, auto wo) {
-                hipLaunchKernelGGL((k_step<DD, decltype(ri)::value, decltype(wo)::value>), L.grid,
-                                   L.block, 0, st, src, dst, g, r);
-                return hipGetLastError();
+                return dispatch_io(nt, false, [&](auto n, auto) {
+                    hipLaunchKernelGGL((k_step<DD, decltype(ri)::value, decltype(wo)::value,
+                                               decltype(n)::value>),
+                                       L.grid, L.block, 0, st, src, dst, g, r);
+                    return hipGetLastError();
+                });
             });
         }
     });
@@ -577,11 +593,11 @@ hipError_t launch_init(int d, const Geo& g, const Rates& r, const double* theta0
     return dispatch(d, [&](auto dc) {
         constexpr int DD = decltype(dc)::value;
         const Launch L = launch_shape(DD, g);
-        if (grad)
-            hipLaunchKernelGGL((k_init<DD, true>), L.grid, L.block, 0, st, theta0, grad, dst, g, r);
-        else
-            hipLaunchKernelGGL((k_init<DD, false>), L.grid, L.block, 0, st, theta0, grad, dst, g, r);
-        return hipGetLastError();
+        return dispatch_io(grad != nullptr, !states_fit_cache(DD, g), [&](auto gr, auto nt) {
+            hipLaunchKernelGGL((k_init<DD, decltype(gr)::value, decltype(nt)::value>), L.grid,
+                               L.block, 0, st, theta0, grad, dst, g, r);
+            return hipGetLastError();
+        });
     });
 }
 

@@ -81,15 +81,10 @@ __host__ __device__ inline bool ms_off32(const Geo& g) {
     return (uint64_t)9 * (uint64_t)chunks_of(g.V) * CHUNK * sizeof(double) <= 0xffffffffull;
 }
 
-// Whether the plain D2Q9 passes write with cached stores: both state buffers
-// fit in the 256 MB Infinity Cache, so the next pass finds its input there.
-// Otherwise non-temporal stores are faster (8 steps per pass, GLUPS
-// non-temporal / cached: 1024^2 196 / 207, 1280^2 216 / 247, 1448^2
-// (288 MiB) 215 / 220, 1600^2 (352 MiB) 231 / 223, 4096^2 280 / 266).
-constexpr uint64_t kInfinityCacheBytes = 256ull << 20;
-inline bool d2q9_cached_stores(const Geo& g) {
-    return 2ull * 9ull * (uint64_t)chunks_of(g.V) * CHUNK * sizeof(double) <= kInfinityCacheBytes;
-}
+// Whether the plain D2Q9 passes write with cached stores (states_fit_cache): 8 steps
+// per pass, GLUPS non-temporal / cached: 1024^2 196 / 207, 1280^2 216 / 247, 1448^2
+// (288 MiB) 215 / 220, 1600^2 (352 MiB) 231 / 223, 4096^2 280 / 266.
+inline bool d2q9_cached_stores(const Geo& g) { return states_fit_cache(2, g); }
 
 template <int S>
 struct MsState {
@@ -292,5 +287,7 @@ constexpr int kMinRows = 8;
 constexpr int kMinRowsSegment = 3;
 
 int steps_rows(const Geo& g, int nstrips, int min_rows);
+// The same for a plain pass of nsteps, which may leave half of the round empty.
+int pass_rows(const Geo& g, int nstrips, int min_rows, int nsteps);
 
 }  // namespace lbm
