@@ -84,12 +84,12 @@ def log(*a):
 
 
 def d2_kernel(steps: int, nodes: int) -> str:
-    """Name of the D2Q9 pass kernel as the trace shows it: the variant with
-    cached stores runs when both state buffers fit in the 256 MB Infinity
-    Cache, the one with 32-bit offsets when a state buffer is under 4 GiB.
-    The launches between the first and the last of an lb_step call read and
-    write only the independent populations (the last two template
-    arguments)."""
+    """Name of the D2Q9 pass kernel: the variant with cached stores runs when both
+    state buffers fit in the 256 MB Infinity Cache, the one with 32-bit offsets
+    when a state buffer is under 4 GiB.  The launches between the first and the
+    last of an lb_step call read and write only the values that determine a node
+    (the last two template arguments).  Mid-size grids run the same march with one
+    wave per SIMD, which the trace shows as k_steps_d2q9_half."""
     state_bytes = 9 * ((nodes + 4095) // 4096) * 4096 * 8
     if 2 * state_bytes <= 256 << 20:
         return f"k_steps_d2q9_cached<{steps}, true, true, true>"

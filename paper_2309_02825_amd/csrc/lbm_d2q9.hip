@@ -31,19 +31,21 @@ static int round_slots() { return 8 * compute_units(); }
 // longer segments amortise the 2S-row pipeline fill; a partial second round
 // costs far more), at least min_rows, and in more rounds when a segment would
 // exceed 512 rows.  Half a round, one wave per SIMD, is taken instead where it is
-// faster: a row then takes 0.90 us against 1.47 with two waves on the SIMD, and a
-// segment of ly rows costs ly + S of them (its fill computes half of 2S rows), so
-// that halving the fill wins below 14 rows at eight steps (us a step, 2,048 and 1,024
-// slots: 800^2 3.36 and 2.97, 1000 x 700 3.44 and 3.07, 1024^2 4.14 and 4.06; 1280^2,
-// 18 rows, 5.33 and 5.42).
-int pass_rows(const Geo& g, int nstrips, int min_rows, int nsteps) {
+// faster: a row then takes 0.83 us (k_steps_d2q9_half) against 1.47 with two waves on
+// the SIMD, and a segment of ly rows costs ly + S of them (its fill computes half of
+// 2S rows), so that halving the fill wins below 27 rows at eight steps (us a step,
+// 2,048 and 1,024 slots: 800^2 3.36 and 2.82, 1000 x 700 3.44 and 2.92, 1280^2 5.56
+// and 5.40, 1448^2 7.08 and 6.92; 1800^2, 34 rows, 10.16 and 10.23).  Shorter passes
+// only where the state stays in the Infinity Cache (4 steps: 1024^2 5.21 and 4.88,
+// 1448^2 11.0 and 11.1).
+int pass_rows(const Geo& g, int nstrips, int min_rows, int nsteps, bool* half) {
     const int two = steps_rows(g, nstrips, min_rows);
     const int64_t nseg = std::max(1, 4 * compute_units() / nstrips);
     const int one = (int)std::min<int64_t>(g.ny, (g.ny + nseg - 1) / nseg);
-    return one > two && nseg * nstrips <= 4 * compute_units() &&
-                   0.90 * (one + nsteps) < 1.47 * (two + nsteps)
-               ? one
-               : two;
+    *half = one > two && nseg * nstrips <= 4 * compute_units() &&
+            0.83 * (one + nsteps) < 1.47 * (two + nsteps) &&
+            (nsteps == MAX_STEPS_PER_PASS || states_fit_cache(2, g));
+    return *half ? one : two;
 }
 
 int steps_rows(const Geo& g, int nstrips, int min_rows) {

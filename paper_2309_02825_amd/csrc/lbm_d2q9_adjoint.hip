@@ -117,12 +117,12 @@ __device__ __forceinline__ void as_row(AsState<S>& st, double& ge, int k,
     const bool own = lane >= S && lane < S + W && x < nx;
     double f[9];
 #pragma unroll
-    for (int i = 0; i < 9; ++i) f[i] = st.pre[i];
+    for (int i = 0; i < 9; ++i) f[i] = st.pre[0][i];
     {
         // next lambda row (unused in the last iteration, as in ms_row)
         const int base = wrapi(ys - S + k + 1, ny) * nx + gx;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) st.pre[i] = src[slot<9>(i, base)];
+        for (int i = 0; i < 9; ++i) st.pre[0][i] = src[slot<9>(i, base)];
     }
 #pragma unroll
     for (int j = 1; j <= S; ++j) {
@@ -208,7 +208,7 @@ k_adjoint_steps_d2q9(const double* __restrict__ src, double* __restrict__ dst,
     {
         const int base = wrapi(ys - S, ny) * nx + gx;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) st.pre[i] = src[slot<9>(i, base)];
+        for (int i = 0; i < 9; ++i) st.pre[0][i] = src[slot<9>(i, base)];
     }
 #pragma unroll
     for (int j = 0; j < S; ++j) {

@@ -10,7 +10,7 @@ namespace {
 // read the halo rows they share at the same time (both at their ends, or both at
 // their starts), so the second read finds them in the caches (512^2 +2.7 %,
 // 1024^2 +1.3 %, 2048^2 +1.7 %, 4096^2 +0.7 %).
-template <int S, bool OFF32, bool NT, int IN, int OUT>
+template <int S, bool OFF32, bool NT, int IN, int OUT, int DEPTH = 1>
 __device__ __forceinline__ void ms_strip(const double* __restrict__ src, double* __restrict__ dst,
                                          const Geo& g, const Rates& r, int ly, int nstrips) {
     const unsigned t = xcd_remap(blockIdx.x, gridDim.x);
@@ -18,9 +18,9 @@ __device__ __forceinline__ void ms_strip(const double* __restrict__ src, double*
     const int seg = (int)(t / (unsigned)nstrips);
     const int ys = seg * ly, ye = min(ys + ly, g.ny), x0 = strip * strip_width(S);
     if (seg & 1)
-        ms_tile<S, false, OFF32, NT, IN, OUT, true>(src, dst, g.nx, g.ny, folded(r), x0, ys, ye);
+        ms_tile<S, false, OFF32, NT, IN, OUT, true, DEPTH>(src, dst, g.nx, g.ny, folded(r), x0, ys, ye);
     else
-        ms_tile<S, false, OFF32, NT, IN, OUT>(src, dst, g.nx, g.ny, folded(r), x0, ys, ye);
+        ms_tile<S, false, OFF32, NT, IN, OUT, false, DEPTH>(src, dst, g.nx, g.ny, folded(r), x0, ys, ye);
 }
 
 // Two waves per SIMD: the register budget (256 per wave) holds S = 8.
@@ -46,6 +46,15 @@ k_steps_d2q9_cached(const double* __restrict__ src, double* __restrict__ dst, Ge
         src, dst, g, r, ly, nstrips);
 }
 
+// Half a round (pass_rows): one wave per SIMD, which has to hide the latency of its
+// loads alone and has the registers to load two rows ahead.
+template <int S, bool NT, int IN, int OUT>
+__global__ void __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
+k_steps_d2q9_half(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rates r, int ly,
+                  int nstrips) {
+    ms_strip<S, true, NT, IN, OUT, 2>(src, dst, g, r, ly, nstrips);
+}
+
 // The passes at the seams, under 4 GiB: the first of a call on a state that an
 // earlier call left (its twins are equal, so 7 planes are read), and the one before
 // a single step, which reads populations.
@@ -63,7 +72,8 @@ hipError_t launch_steps_t(const Geo& g, const Rates& r, const double* src, doubl
                           hipStream_t st, int in, int out) {
     const int w = strip_width(S);
     const int nstrips = (g.nx + w - 1) / w;
-    const int ly = pass_rows(g, nstrips, kMinRows, S);
+    bool half;
+    const int ly = pass_rows(g, nstrips, kMinRows, S, &half);
     const int nseg = (g.ny + ly - 1) / ly;
     const dim3 grid((unsigned)((int64_t)nstrips * nseg)), block(MS_THREADS);
     const bool off32 = ms_off32(g), cached = d2q9_cached_stores(g);
@@ -75,6 +85,12 @@ hipError_t launch_steps_t(const Geo& g, const Rates& r, const double* src, doubl
                 if (IN == FORM_MOM || OUT == FORM_MOM) return hipErrorInvalidValue;  // pass_form
                 hipLaunchKernelGGL((k_steps_d2q9<S, false, RI, WO>), grid, block, 0, st, src, dst,
                                    g, r, ly, nstrips);
+            } else if (half && cached) {
+                hipLaunchKernelGGL((k_steps_d2q9_half<S, false, IN, OUT>), grid, block, 0, st, src,
+                                   dst, g, r, ly, nstrips);
+            } else if (half && S == MAX_STEPS_PER_PASS) {
+                hipLaunchKernelGGL((k_steps_d2q9_half<MAX_STEPS_PER_PASS, true, IN, OUT>), grid, block, 0, st, src,
+                                   dst, g, r, ly, nstrips);
             } else if constexpr (IN == FORM_TWIN || OUT == FORM_TWIN) {
                 if (cached)
                     hipLaunchKernelGGL((k_steps_d2q9_seam<S, false, IN, OUT>), grid, block, 0, st,

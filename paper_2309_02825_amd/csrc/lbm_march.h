@@ -86,9 +86,9 @@ __host__ __device__ inline bool ms_off32(const Geo& g) {
 // (288 MiB) 215 / 220, 1600^2 (352 MiB) 231 / 223, 4096^2 280 / 266.
 inline bool d2q9_cached_stores(const Geo& g) { return states_fit_cache(2, g); }
 
-template <int S>
+template <int S, int DEPTH = 1>
 struct MsState {
-    double pre[9];      // next input row (prefetched)
+    double pre[DEPTH][9];  // next input rows (prefetched DEPTH rows ahead)
     double z[S][3];     // e_y = 0 populations of the previous row, per stage input
     double u[2][S][3];  // e_y = +1 populations of the rows of each parity
 };
@@ -122,15 +122,15 @@ __device__ __forceinline__ void ms_planes(const Mom2& m, double (&p)[9]) {
 // march runs from row ye - 1 + S up to ys - S, so the roles of e_y = +1 and
 // e_y = -1 in the row delays swap (same arithmetic per node).
 template <int S, int P, int ACTIVE, bool ALL, bool OFF32, bool NT = true,
-          int IN = FORM_FULL, int OUT = FORM_FULL, bool UP = false>
-__device__ __forceinline__ void ms_row(MsState<S>& st, int k,
+          int IN = FORM_FULL, int OUT = FORM_FULL, bool UP = false, int DEPTH = 1>
+__device__ __forceinline__ void ms_row(MsState<S, DEPTH>& st, int k,
                                        const double* __restrict__ src, double* __restrict__ dst,
                                        int nx, int ny, int gx, int ys, int x0, const FoldedRates& r,
                                        int nrows, int64_t stride) {
     constexpr int W = MS_THREADS - 2 * S;
     const int lane = threadIdx.x;
     double f[9];
-    ms_populations<IN>(st.pre, r, f);
+    ms_populations<IN>(st.pre[P % DEPTH], r, f);
     {
         // Prefetch the next input row.  In the last iteration the row is not
         // used (its address is wrapped, so in bounds); loading it anyway
@@ -139,11 +139,11 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
         // widened by a missing load (512^2: 90 -> 106 GLUPS).  The masked
         // stores of stage S still make that wait cover the previous row's
         // stores; two waves per SIMD hide it.
-        const int row = UP ? ys + nrows - 1 + S - (k + 1) : ys - S + k + 1;
+        const int row = UP ? ys + nrows - 1 + S - (k + DEPTH) : ys - S + k + DEPTH;
         const MsAddr<OFF32, form_planes<2>(IN)> a(wrapi(row, ny) * nx + gx);
 #pragma unroll
         for (int i = 0; i < 9; ++i)
-            if (form_holds<2>(IN, i)) st.pre[i] = a.load(src, i);
+            if (form_holds<2>(IN, i)) st.pre[P % DEPTH][i] = a.load(src, i);
     }
 #pragma unroll
     for (int j = 1; j <= S; ++j) {
@@ -224,42 +224,44 @@ __device__ __forceinline__ void ms_row(MsState<S>& st, int k,
 }
 
 template <int S, int K, bool ALL, bool OFF32, bool NT = true, int IN = FORM_FULL,
-          int OUT = FORM_FULL, bool UP = false>
-__device__ __forceinline__ void ms_fill(MsState<S>& st, const double* __restrict__ src,
+          int OUT = FORM_FULL, bool UP = false, int DEPTH = 1>
+__device__ __forceinline__ void ms_fill(MsState<S, DEPTH>& st, const double* __restrict__ src,
                                         double* __restrict__ dst, int nx, int ny, int gx, int ys,
                                         int x0, const FoldedRates& r, int nrows, int64_t stride) {
     if constexpr (K < 2 * S) {
-        ms_row<S, K & 1, K / 2, ALL, OFF32, NT, IN, OUT, UP>(st, K, src, dst, nx, ny, gx, ys, x0,
+        ms_row<S, K & 1, K / 2, ALL, OFF32, NT, IN, OUT, UP, DEPTH>(st, K, src, dst, nx, ny, gx, ys, x0,
                                                                r, nrows, stride);
-        ms_fill<S, K + 1, ALL, OFF32, NT, IN, OUT, UP>(st, src, dst, nx, ny, gx, ys, x0, r, nrows,
+        ms_fill<S, K + 1, ALL, OFF32, NT, IN, OUT, UP, DEPTH>(st, src, dst, nx, ny, gx, ys, x0, r, nrows,
                                                          stride);
     }
 }
 
+// DEPTH (1 or 2, the period of the row pairs): input rows loaded ahead.
 // Advance rows [ys, ye) (ye > ys) of the columns [x0, x0 + 64 - 2S) of one
 // D2Q9 grid by S steps (reads rows ys-S .. ye-1+S and columns x0-S ..
 // x0+63-S, wrapped periodically), marching down the rows or, with UP, up.
 // All 64 lanes of the wave must be active.
 template <int S, bool ALL, bool OFF32, bool NT = true, int IN = FORM_FULL,
-          int OUT = FORM_FULL, bool UP = false>
+          int OUT = FORM_FULL, bool UP = false, int DEPTH = 1>
 __device__ __forceinline__ void ms_tile(const double* __restrict__ src, double* __restrict__ dst,
                                         int nx, int ny, const FoldedRates& r, int x0, int ys,
                                         int ye, int64_t stride = 0) {
     const int gx = wrapi(x0 - S + (int)threadIdx.x, nx);
     const int kend = ye - ys + 2 * S - 1;  // >= 2S
-    MsState<S> st;
-    {
-        const MsAddr<OFF32, form_planes<2>(IN)> a(wrapi(UP ? ye - 1 + S : ys - S, ny) * nx + gx);
+    MsState<S, DEPTH> st;
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+        const MsAddr<OFF32, form_planes<2>(IN)> a(wrapi(UP ? ye - 1 + S - d : ys - S + d, ny) * nx + gx);
 #pragma unroll
         for (int i = 0; i < 9; ++i)
-            if (form_holds<2>(IN, i)) st.pre[i] = a.load(src, i);
+            if (form_holds<2>(IN, i)) st.pre[d][i] = a.load(src, i);
     }
 #pragma unroll
     for (int j = 0; j < S; ++j)
 #pragma unroll
         for (int a = 0; a < 3; ++a) st.z[j][a] = st.u[0][j][a] = st.u[1][j][a] = 0.0;
     const int nrows = ye - ys;
-    ms_fill<S, 0, ALL, OFF32, NT, IN, OUT, UP>(st, src, dst, nx, ny, gx, ys, x0, r, nrows,
+    ms_fill<S, 0, ALL, OFF32, NT, IN, OUT, UP, DEPTH>(st, src, dst, nx, ny, gx, ys, x0, r, nrows,
                                                  stride);
     // whole row pairs in the loop and a last odd row after it: the loop then
     // has a single path back to its head, and the compiler keeps the row
@@ -267,13 +269,13 @@ __device__ __forceinline__ void ms_tile(const double* __restrict__ src, double* 
     // 37 instead of 52 copies per row pair)
     int k = 2 * S;
     for (; k + 1 <= kend; k += 2) {
-        ms_row<S, 0, S, ALL, OFF32, NT, IN, OUT, UP>(st, k, src, dst, nx, ny, gx, ys, x0, r,
+        ms_row<S, 0, S, ALL, OFF32, NT, IN, OUT, UP, DEPTH>(st, k, src, dst, nx, ny, gx, ys, x0, r,
                                                        nrows, stride);
-        ms_row<S, 1, S, ALL, OFF32, NT, IN, OUT, UP>(st, k + 1, src, dst, nx, ny, gx, ys, x0, r,
+        ms_row<S, 1, S, ALL, OFF32, NT, IN, OUT, UP, DEPTH>(st, k + 1, src, dst, nx, ny, gx, ys, x0, r,
                                                        nrows, stride);
     }
     if (k <= kend)
-        ms_row<S, 0, S, ALL, OFF32, NT, IN, OUT, UP>(st, k, src, dst, nx, ny, gx, ys, x0, r,
+        ms_row<S, 0, S, ALL, OFF32, NT, IN, OUT, UP, DEPTH>(st, k, src, dst, nx, ny, gx, ys, x0, r,
                                                        nrows, stride);
 }
 
@@ -288,6 +290,6 @@ constexpr int kMinRowsSegment = 3;
 
 int steps_rows(const Geo& g, int nstrips, int min_rows);
 // The same for a plain pass of nsteps, which may leave half of the round empty.
-int pass_rows(const Geo& g, int nstrips, int min_rows, int nsteps);
+int pass_rows(const Geo& g, int nstrips, int min_rows, int nsteps, bool* half);
 
 }  // namespace lbm

@@ -136,3 +136,30 @@ def test_theta_from_velocity_segments(grid):
         assert np.max(np.abs(th.cpu().numpy() / want - 1.0)) <= 4 * 4 * max(grid) * 2.3e-16 + 1e-14
         assert np.max(np.abs(gr.cpu().numpy() - want_grad)) <= 1e-12 * np.max(np.abs(want_grad))
     s.close()
+
+
+@pytest.mark.parametrize("grid", [(721, 720), (1000, 700), (1153, 643), (49, 13000), (2000, 33),
+                                  (1408, 1409), (13000, 40)])
+@pytest.mark.parametrize("limit", [4, 8])
+def test_d2q9_half_rounds_equal_single_steps(grid, limit):
+    """Marches of one wave per SIMD that load two rows ahead (mid-size grids, with
+    cached and with non-temporal stores, segments of odd and even length), against
+    lb_step_buffers single steps, bit for bit."""
+    _say("D2Q9 half rounds", grid, limit)
+    s, ref = _solver(grid, 0.31), _solver(grid, 0.31)
+    s.set_steps_per_pass(limit)
+    th0 = _rough(grid, 8)
+    s.init(th0, None)
+    ref.init(th0, None)
+    cur = 0
+    for n in (limit, 2 * limit + 1, 3 * limit):
+        s.step(n)
+        for _ in range(n):
+            ref.step_buffers(ref.bufs[cur], ref.bufs[1 - cur])
+            cur ^= 1
+        if cur:
+            ref.bufs[0].copy_(ref.bufs[1])
+            cur = 0
+        assert torch.equal(s.get_state(), ref.get_state()), (grid, limit, n)
+    s.close()
+    ref.close()
