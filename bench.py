@@ -335,8 +335,19 @@ def form_batched(torch, SV, W, dev):
             "lu_equivalent_gbs": round(mlups * 144 / 1e3, 1)}
 
 
+def d2_tile_adjoint_steps(grid, cus: int, spp: int = D2_STEPS_PER_PASS) -> int:
+    """Adjoint steps of a register-tile pass on this grid, 0 where the segment goes by
+    the march (tile_rows and tile_adjoint_steps of lbm_d2q9_tile.hip)."""
+    strips = -(-grid[0] // 48)
+    if strips > cus:
+        return 0
+    rows = max(2, -(-grid[1] // (cus // strips)))
+    steps = min(spp, (6 * 8 - rows) // 2)
+    return steps if rows <= 48 and steps > 1 else 0
+
+
 def adjoint_backward_bytes(V: int, starts, nsteps: int, spp: int = D2_STEPS_PER_PASS,
-                           max_reverse: int = 4) -> int:
+                           max_reverse: int = 4, tile_steps: int = 0) -> int:
     """Algorithmic HBM bytes of the D2Q9 backward sweep, following the launch
     plan of lb_adjoint_segment.  A checkpoint and lambda are complete (9
     populations, 72 B per node); the recomputed states are post-collision
@@ -345,14 +356,21 @@ def adjoint_backward_bytes(V: int, starts, nsteps: int, spp: int = D2_STEPS_PER_
     of a segment) and writes all S states; a reverse pass of S steps reads
     and writes lambda once and reads the S states it needs; single steps read
     one state and write one, single adjoint steps read one state and lambda
-    and write lambda.  The seed (lb_macro_adjoint: state and g_u read,
-    lambda written) and the adjoint of the initialisation (lambda read,
-    theta0 read, g_theta0 written) are included."""
+    and write lambda.  With tile_steps > 0 the segment goes by register tiles:
+    passes of equal lengths of up to spp recomputed and tile_steps adjoint steps,
+    the last reverse pass with the checkpoint.  The seed (lb_macro_adjoint:
+    state and g_u read, lambda written) and the adjoint of the initialisation
+    (lambda read, theta0 read, g_theta0 written) are included."""
     full, red = 72 * V, 56 * V
     total = full + 16 * V + full
     ends = list(starts[1:]) + [nsteps]
     for b, e in zip(starts, ends):
         m = e - b
+        if tile_steps > 0:
+            passes = -(-(m - 1) // spp)
+            total += (full + red * (passes - 1) if passes else 0) + red * (m - 1)
+            total += 2 * full * -(-m // tile_steps) + red * (m - 1) + full
+            continue
         j = 1
         p = spp
         while p >= 2:
@@ -425,7 +443,9 @@ def form_adjoint(torch, SV, W, dev, n: int = 512, lb_steps: int = 2000):
     t_f, t_fb, t_b = tf.total_ms() / 1e3, tfb.total_ms() / 1e3, tb.total_ms() / 1e3
     V = gue.nodes
     starts = SV.checkpoint_segments(N)
-    bwd_bytes = adjoint_backward_bytes(V, starts, N)
+    cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    bwd_bytes = adjoint_backward_bytes(V, starts, N,
+                                       tile_steps=d2_tile_adjoint_steps(gue.grid, cus))
     bwd_gbs = bwd_bytes / t_b / 1e9
     counted = traffic_for(f"adjoint_{n}", N)
     return {"grid": list(gue.grid), "lb_steps": N, "checkpoints": len(starts),

@@ -293,11 +293,12 @@ lb_status lb_adjoint_step(lb_solver* s, const double* state_n, const double* lam
  * the adjoint steps for n = n0+m-1 down to n0.  lambda holds dL/df^{n0+m}
  * on entry and dL/df^{n0} on return; lambda_tmp is a second state buffer
  * used as the ping-pong partner.  lambda on return is bitwise that of m
- * lb_adjoint_step calls.  On D2Q9 the reverse sweep runs in passes of up to
- * min(4, LB_OPT_STEPS_PER_PASS) adjoint steps (the forward passes' one-wave
- * march with every velocity reversed); each wave sums the eps parts of its
- * nodes in a fixed order, so *g_eps is deterministic but rounded differently
- * from the single calls.  Other lattices take one adjoint step per launch
+ * lb_adjoint_step calls.  On D2Q9 the reverse sweep runs in passes: where the
+ * grid goes by register tiles, of up to LB_OPT_STEPS_PER_PASS adjoint steps
+ * (fewer where a tile of that many does not fit), else of up to
+ * min(4, LB_OPT_STEPS_PER_PASS) (the forward passes' one-wave march with every
+ * velocity reversed); the eps parts are summed in a fixed order, so *g_eps is
+ * deterministic but rounded differently from the single calls.  Other lattices take one adjoint step per launch
  * and *g_eps is bitwise that of the single calls.  None of the buffers may
  * overlap.  Errors: NULL pointers, m < 0, a bounded solver,
  * LB_ERR_HIP if the partials table cannot grow to m tables. */
@@ -317,7 +318,8 @@ lb_status lb_adjoint_segment(lb_solver* s, const double* ckpt, int64_t m, double
  * strips times row segments) and the per-node kernels' block count B, and nt
  * is the number of reverse launches, at most ceil((m-1)/4) + 2 with the
  * default LB_OPT_STEPS_PER_PASS (m when it is 1); on the other lattices
- * T = B and nt = m.  A segment needing more returns
+ * T = B and nt = m.  (Tiles that would need more where this fits give way to
+ * the march, here and in lb_adjoint_segment.)  A segment needing more returns
  * LB_ERR_INVALID_ARG before anything is launched (use lb_adjoint_segment or
  * shorter segments).  Every entry of the tables is written before it is
  * read, so nothing needs clearing between calls.  All solvers on one GPU

@@ -661,12 +661,14 @@ lb_status lb_adjoint_step(lb_solver* s, const double* state_n, const double* lam
 // the partials tables they write (one table per launch plus one sum each).
 struct SegmentPlan {
     std::vector<int> reverse;  // D2Q9: adjoint steps per launch, in launch order
+    bool tiles = false;        // D2Q9: the launches are register tiles
     int64_t T = 0;             // doubles per table
     int64_t ntables = 0;
     int64_t doubles() const { return ntables * (T + 1); }
 };
 
-static SegmentPlan segment_plan(const lb_solver* s, int64_t m) {
+// Passes by the march or by single steps.
+static SegmentPlan march_plan(const lb_solver* s, int64_t m) {
     SegmentPlan p;
     if (s->d == 2) {
         // reverse sweep in passes of up to steps_per_pass (at most 4) adjoint
@@ -685,6 +687,23 @@ static SegmentPlan segment_plan(const lb_solver* s, int64_t m) {
     return p;
 }
 
+// `march` is march_plan(s, m).  Where the grid goes by tiles, all m steps go in the
+// fewest tile passes, of equal lengths, unless their tables would not fit the fixed
+// scratch array and the march's do: the two entry points then choose alike.
+static SegmentPlan segment_plan(const lb_solver* s, int64_t m, const SegmentPlan& march) {
+    const int most = s->d == 2 ? lbm::tile_adjoint_steps(s->g, s->steps_per_pass) : 0;
+    if (most == 0) return march;
+    SegmentPlan p;
+    p.tiles = true;
+    p.T = lbm::tile_adjoint_table(s->g);
+    p.ntables = (m + most - 1) / most;
+    if (p.doubles() > LB_SEGMENT_SCRATCH_DOUBLES && march.doubles() <= LB_SEGMENT_SCRATCH_DOUBLES)
+        return march;
+    for (int64_t k = 0; k < p.ntables; ++k)
+        p.reverse.push_back((int)(m / p.ntables + (k < m % p.ntables ? 1 : 0)));
+    return p;
+}
+
 // One checkpoint segment (lb_adjoint_segment); `tables` holds plan.doubles()
 // doubles, every one of which the launches write before it is read.
 static lb_status run_segment(lb_solver* s, const SegmentPlan& plan, const double* ckpt, int64_t m,
@@ -699,7 +718,18 @@ static lb_status run_segment(lb_solver* s, const SegmentPlan& plan, const double
     // any state and is read whole.
     const double* prev = ckpt;
     int64_t j = 1;  // next state to produce
-    if (s->d == 2) {
+    if (plan.tiles) {
+        const int64_t passes = (m - 1 + s->steps_per_pass - 1) / s->steps_per_pass;
+        for (int64_t k = 0; k < passes; ++k) {
+            const int64_t pass = (m - 1) / passes + (k < (m - 1) % passes ? 1 : 0);
+            double* out = work + (j - 1) * se;
+            LB_HIP(lbm::launch_tile_all((int)pass, s->g, s->r, prev, out, se, s->stream,
+                                        prev != ckpt),
+                   "multi-step launch");
+            prev = out + (pass - 1) * se;
+            j += pass;
+        }
+    } else if (s->d == 2) {
         for (int pass = s->steps_per_pass; pass >= 2; pass /= 2) {
             for (; j + pass <= m; j += pass) {
                 double* out = work + (j - 1) * se;
@@ -726,7 +756,12 @@ static lb_status run_segment(lb_solver* s, const SegmentPlan& plan, const double
         for (int64_t t = 0; t < nt; ++t) {
             const double* ftop = N == 1 ? ckpt : work + (N - 2) * se;  // f^{n0+N-1}
             const int steps = plan.reverse[(size_t)t];
-            if (steps == 1)
+            if (plan.tiles)  // the last launch ends with the step at the checkpoint
+                LB_HIP(lbm::launch_tile_adjoint(steps, s->g, s->r, lin, lout, ftop, se,
+                                                steps == N ? ckpt : nullptr, tables + t * T, T,
+                                                s->stream),
+                       "adjoint tile launch");
+            else if (steps == 1)
                 LB_HIP(lbm::launch_adjoint_step(2, s->g, s->r, ftop, lin, lout, tables + t * T, T,
                                                 s->stream, N != 1),
                        "adjoint_step launch");
@@ -775,7 +810,7 @@ lb_status lb_adjoint_segment(lb_solver* s, const double* ckpt, int64_t m, double
     if (st != LB_OK) return st;
     if (m > 1 && !work) return fail(LB_ERR_INVALID_ARG, "work is NULL");
     if (m == 0) return LB_OK;
-    const SegmentPlan plan = segment_plan(s, m);
+    const SegmentPlan plan = segment_plan(s, m, march_plan(s, m));
     st = reserve_seg_partials(s, plan.doubles());
     if (st != LB_OK) return st;
     return run_segment(s, plan, ckpt, m, work, lambda, lambda_tmp, g_eps, s->seg_partials);
@@ -786,16 +821,16 @@ lb_status lb_adjoint_segment_static(lb_solver* s, const double* ckpt, int64_t m,
     lb_status st = check_segment_args(s, ckpt, m, lambda, lambda_tmp, g_eps);
     if (st != LB_OK) return st;
     if (m == 0) return LB_OK;
-    const SegmentPlan plan = segment_plan(s, m);
-    if (plan.doubles() > LB_SEGMENT_SCRATCH_DOUBLES)
+    const SegmentPlan march = march_plan(s, m);
+    if (march.doubles() > LB_SEGMENT_SCRATCH_DOUBLES)
         return fail(LB_ERR_INVALID_ARG,
-                    "segment needs " + std::to_string(plan.doubles()) +
+                    "segment needs " + std::to_string(march.doubles()) +
                         " doubles of partials, more than the fixed scratch array holds (" +
                         std::to_string((long long)LB_SEGMENT_SCRATCH_DOUBLES) +
                         "): use lb_adjoint_segment or a shorter segment");
     if (m > 1 && !work) return fail(LB_ERR_INVALID_ARG, "work is NULL");
     if (!s->scratch) return fail(LB_ERR_STATE, "no scratch address for this solver's device");
-    return run_segment(s, plan, ckpt, m, work, lambda, lambda_tmp, g_eps, s->scratch);
+    return run_segment(s, segment_plan(s, m, march), ckpt, m, work, lambda, lambda_tmp, g_eps, s->scratch);
 }
 
 lb_status lb_init_adjoint(lb_solver* s, const double* theta0, const double* grad_theta0,

@@ -26,6 +26,7 @@ namespace {
 // not overlap the steps.
 // ---------------------------------------------------------------------------
 constexpr int TILE_MAX_WAVES = 8;
+constexpr int TILE_ADJOINT_ROWS = 6;  // rows a wave holds of lambda and f (242 VGPRs)
 constexpr int TILE_ROW = 66;  // a row of 64 doubles in LDS and one to each side
 
 template <int R, bool TWINS>
@@ -177,6 +178,218 @@ k_tile_d2q9(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rat
     }
 }
 
+// The same tile keeping every state: step s to out + (s - 1) stride, without the
+// twins (the adjoint's recomputation of a checkpoint segment).  Cached stores: the
+// reverse sweep reads the states from the Infinity Cache (512^2, 8 steps: 23.3 us,
+// 34 us with non-temporal ones, the march 31).
+template <int R, int IN>
+__global__ void __launch_bounds__(64 * TILE_MAX_WAVES)
+k_tile_d2q9_all(const double* __restrict__ src, double* __restrict__ out, int64_t stride, Geo g,
+                Rates r, int S, int rows, int nstrips) {
+    extern __shared__ double xch[];  // [2][waves][6][TILE_ROW]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int waves = (int)blockDim.x >> 6;
+    const unsigned t = xcd_remap(blockIdx.x, gridDim.x);
+    const int x0 = (int)(t % (unsigned)nstrips) * (64 - 2 * S);
+    const int y0 = (int)(t / (unsigned)nstrips) * rows;
+    const int gx = wrapi(x0 - S + lane, g.nx);
+    const int top = wave * R;
+    const int rin = min(rows, g.ny - y0) + 2 * S;
+    const FoldedRates fr = folded(r);
+    constexpr bool TWINS = IN != FORM_FULL;
+    TileRows<R, TWINS> a;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const MsAddr<true> at(wrapi(y0 - S + top + q, g.ny) * g.nx + gx);
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            if (form_holds<2>(IN, i)) a.f[q][i] = at.load(src, i);
+    }
+    TileRows<R, true> b;
+    const int half = waves * 6 * TILE_ROW;
+    const int x = x0 - S + lane;
+    const bool own = lane >= S && lane < 64 - S && x < g.nx;
+    auto needed = [&](int s) { return top + R > s && top < rin - s; };
+    auto keep = [&](int s) {
+        double* dst = out + (int64_t)(s - 1) * stride;
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+            if (top + q >= S && top + q < rin - S && own) {
+                const MsAddr<true> at((y0 - S + top + q) * g.nx + x);
+#pragma unroll
+                for (int i = 0; i < 7; ++i) at.store_cached(dst, i, b.f[q][i]);
+            }
+    };
+    tile_publish<R, TWINS>(a, xch, wave);
+    __syncthreads();
+    if (needed(1)) {
+        tile_step<R, TWINS, false>(a, b, xch, wave, waves, fr);
+        tile_publish<R, true>(b, xch + half, wave);
+        keep(1);
+    }
+    for (int s = 2; s <= S; ++s) {
+        __syncthreads();
+        if (needed(s)) {
+            tile_step<R, true, false>(b, b, xch + ((s & 1) ? 0 : half), wave, waves, fr);
+            tile_publish<R, true>(b, xch + ((s & 1) ? half : 0), wave);
+            keep(s);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// S adjoint steps of one tile (the reverse sweep of a checkpoint segment on the
+// grids of tile_rows): lambda^{N-S} from lambda^N, the forward tile with every
+// velocity reversed and C^T in place of C, and the eps parts <mu, (dC/deps) f^{N-j}>
+// of the nodes the block owns.
+//
+// f^{N-j} is read from its state buffer at each lane's own column, the rows of the
+// next step while this one is computed, and pulled along x by lane shifts; f_7 and
+// f_8 come from the planes p7 and p8 (5 and 6 in a state written by a collision, 7
+// and 8 in the checkpoint, which may be any state).  Every lane sums the parts of its
+// nodes over steps and rows, a block its lanes, in a fixed order.
+//
+// Bounds: FP64 issue at two waves a SIMD (about 190 vector instructions a row and
+// step), then the first loads and the last stores, which no other block hides.  512^2:
+// 41 us for 7.5 steps, the march 6.5 us a step; with the loads of f behind a branch,
+// and so waited for in their own step, 44.
+// ---------------------------------------------------------------------------
+template <int R>
+__global__ void __launch_bounds__(64 * TILE_MAX_WAVES)
+k_tile_adjoint_d2q9(const double* __restrict__ src, double* __restrict__ dst,
+                    const double* __restrict__ ftop, int64_t stride,
+                    const double* __restrict__ ckpt, double* __restrict__ partials, int ntab,
+                    Geo g, Rates r, int S, int rows, int nstrips) {
+    extern __shared__ double xch[];  // [2][waves][6][TILE_ROW]
+    __shared__ double sums[TILE_MAX_WAVES];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int waves = (int)blockDim.x >> 6;
+    const unsigned t = xcd_remap(blockIdx.x, gridDim.x);
+    const int x0 = (int)(t % (unsigned)nstrips) * (64 - 2 * S);
+    const int y0 = (int)(t / (unsigned)nstrips) * rows;
+    const int gx = wrapi(x0 - S + lane, g.nx);
+    const int top = wave * R;
+    const int rin = min(rows, g.ny - y0) + 2 * S;
+    const int x = x0 - S + lane;
+    const bool own = lane >= S && lane < 64 - S && x < g.nx;
+    // byte offsets of the rows top - 1 .. top + R at the lane's column
+    unsigned at[R + 2];
+#pragma unroll
+    for (int q = 0; q < R + 2; ++q)
+        at[q] = MsAddr<true>(wrapi(y0 - S + top + q - 1, g.ny) * g.nx + gx).off;
+    auto get = [&](const double* p, int plane, unsigned off) {
+        return *(GDouble*)(wave_base(p + (int64_t)plane * CHUNK) + off);
+    };
+    double lam[R][9];
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+#pragma unroll
+        for (int i = 0; i < 9; ++i) lam[q][i] = get(src, i, at[q + 1]);
+    auto owned = [&](int q) { return top + q >= S && top + q < rin - S; };
+    // f^{N-j} of row q, before the lane shifts.  A row that the block does not own
+    // gets an empty buffer, which reads nothing: behind a branch the loads of the next
+    // step would be waited for where the branch ends.
+    double f[R][9];
+    const unsigned bytes = (unsigned)(9 * CHUNK * 8 * ((g.nx * g.ny + CHUNK - 1) / CHUNK));
+    auto load_f = [&](int j, int q) {
+        const bool last = j == S && ckpt != nullptr;
+        const double* fs = last ? ckpt : ftop - (int64_t)(j - 1) * stride;
+        const int p7 = last ? 7 : 5, p8 = last ? 8 : 6;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<double*>(fs), (short)0, j <= S && owned(q) ? (int)bytes : 0, 0x00020000);
+        auto fetch = [&](int plane, unsigned off) {
+            return __builtin_bit_cast(
+                double, __builtin_amdgcn_raw_buffer_load_b64(rs, off, plane * (int)CHUNK * 8, 0));
+        };
+        f[q][0] = fetch(0, at[q + 1]);
+        f[q][1] = fetch(1, at[q + 1]);
+        f[q][3] = fetch(3, at[q + 1]);
+        f[q][2] = fetch(2, at[q]);
+        f[q][5] = fetch(5, at[q]);
+        f[q][6] = fetch(6, at[q]);
+        f[q][4] = fetch(4, at[q + 2]);
+        f[q][7] = fetch(p7, at[q + 2]);
+        f[q][8] = fetch(p8, at[q + 2]);
+    };
+#pragma unroll
+    for (int q = 0; q < R; ++q) load_f(1, q);
+    const int half = waves * 6 * TILE_ROW;
+    double ge = 0.0;
+    for (int j = 1; j <= S; ++j) {
+        double* buf = xch + ((j & 1) ? 0 : half);
+        {
+            double* line = buf + wave * 6 * TILE_ROW + 1 + lane;
+            line[0 * TILE_ROW] = lam[R - 1][4];
+            line[1 * TILE_ROW] = lam[R - 1][7];
+            line[2 * TILE_ROW] = lam[R - 1][8];
+            line[3 * TILE_ROW] = lam[0][2];
+            line[4 * TILE_ROW] = lam[0][5];
+            line[5 * TILE_ROW] = lam[0][6];
+        }
+        __syncthreads();
+        // step j needs rows j .. rin - 1 - j (as k_tile_d2q9)
+        if (!(top + R > j && top < rin - j)) continue;
+        const double* up = buf + max(wave - 1, 0) * 6 * TILE_ROW + 1 + lane;
+        const double* dn = buf + min(wave + 1, waves - 1) * 6 * TILE_ROW + 1 + lane;
+        double m4 = up[0], m7 = up[1 * TILE_ROW - 1], m8 = up[2 * TILE_ROW + 1];
+        const double e2 = dn[3 * TILE_ROW], e5 = dn[4 * TILE_ROW + 1], e6 = dn[5 * TILE_ROW - 1];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int n = q < R - 1 ? q + 1 : q;
+            double mu[9];
+            mu[0] = lam[q][0];
+            mu[1] = lane_shift<-1>(lam[q][1]);
+            mu[3] = lane_shift<1>(lam[q][3]);
+            mu[4] = m4;
+            mu[7] = m7;
+            mu[8] = m8;
+            mu[2] = q < R - 1 ? lam[n][2] : e2;
+            mu[5] = q < R - 1 ? lane_shift<-1>(lam[n][5]) : e5;
+            mu[6] = q < R - 1 ? lane_shift<1>(lam[n][6]) : e6;
+            m4 = lam[q][4];
+            m7 = lane_shift<1>(lam[q][7]);
+            m8 = lane_shift<-1>(lam[q][8]);
+            const Dual2 du = dual_d2q9(mu);
+            collide_adjoint_d2q9(du, r, lam[q]);  // as collide_adjoint<2>
+            if (owned(q)) {
+                double fn[9];
+                fn[0] = f[q][0];
+                fn[2] = f[q][2];
+                fn[4] = f[q][4];
+                fn[1] = lane_shift<1>(f[q][1]);
+                fn[3] = lane_shift<-1>(f[q][3]);
+                fn[5] = lane_shift<1>(f[q][5]);
+                fn[6] = lane_shift<-1>(f[q][6]);
+                fn[7] = lane_shift<-1>(f[q][7]);
+                fn[8] = lane_shift<1>(f[q][8]);
+                const double part = eps_part_d2q9(du, fn, r);
+                ge += own ? part : 0.0;
+            }
+            load_f(j + 1, q);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+        if (owned(q) && own) {
+            const MsAddr<true> to((y0 - S + top + q) * g.nx + x);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) to.store_cached(dst, i, lam[q][i]);
+        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ge += __shfl_xor(ge, o, 64);
+    if (lane == 0) sums[wave] = ge;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+        for (int w = 0; w < waves; ++w) s += sums[w];
+        partials[blockIdx.x] = s;
+        for (int i = (int)gridDim.x + (int)blockIdx.x; i < ntab; i += (int)gridDim.x)
+            partials[i] = 0.0;
+    }
+}
+
 }  // namespace
 
 // Rows of a tile where a run on this grid goes by tiles, 0 where it goes by the
@@ -196,24 +409,37 @@ int tile_rows(const Geo& g) {
     return rows <= kMaxRows ? rows : 0;
 }
 
+// Tile shape of a launch: rows per wave, waves and blocks.
+struct TileShape {
+    int R, waves, nstrips;
+    dim3 grid, block;
+    size_t lds;
+};
+static TileShape tile_shape(const Geo& g, int rows, int nsteps) {
+    TileShape s;
+    const int w = 64 - 2 * nsteps;
+    s.nstrips = (g.nx + w - 1) / w;
+    s.R = (rows + 2 * nsteps + TILE_MAX_WAVES - 1) / TILE_MAX_WAVES;
+    s.waves = (rows + 2 * nsteps + s.R - 1) / s.R;
+    s.grid = dim3((unsigned)(s.nstrips * ((g.ny + rows - 1) / rows)));
+    s.block = dim3(64 * s.waves);
+    s.lds = (size_t)2 * s.waves * 6 * TILE_ROW * sizeof(double);  // at most 51 KB
+    return s;
+}
+
 hipError_t launch_tile(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
                        hipStream_t st, int in, int out) {
     const int rows = tile_rows(g);
     if (nsteps < 1 || nsteps > MAX_STEPS_PER_PASS || rows == 0) return hipErrorInvalidValue;
-    const int w = 64 - 2 * nsteps;
-    const int nstrips = (g.nx + w - 1) / w, nseg = (g.ny + rows - 1) / rows;
-    const int R = (rows + 2 * nsteps + TILE_MAX_WAVES - 1) / TILE_MAX_WAVES;
-    const int waves = (rows + 2 * nsteps + R - 1) / R;
-    const dim3 grid((unsigned)(nstrips * nseg)), block(64 * waves);
-    const size_t lds = (size_t)2 * waves * 6 * TILE_ROW * sizeof(double);  // at most 51 KB
+    const TileShape s = tile_shape(g, rows, nsteps);
     return dispatch_form(in, [&](auto fi) {
         return dispatch_form(out, [&](auto fo) {
             constexpr int IN = decltype(fi)::value, OUT = decltype(fo)::value;
-            switch (R) {
-#define LBM_TILE(RR)                                                                         \
-    case RR:                                                                                 \
-        hipLaunchKernelGGL((k_tile_d2q9<RR, IN, OUT>), grid, block, lds, st, src, dst, g, r, \
-                           nsteps, rows, nstrips);                                           \
+            switch (s.R) {
+#define LBM_TILE(RR)                                                                            \
+    case RR:                                                                                    \
+        hipLaunchKernelGGL((k_tile_d2q9<RR, IN, OUT>), s.grid, s.block, s.lds, st, src, dst, g, \
+                           r, nsteps, rows, s.nstrips);                                         \
         break;
                 LBM_TILE(1)
                 LBM_TILE(2)
@@ -229,6 +455,78 @@ hipError_t launch_tile(int nsteps, const Geo& g, const Rates& r, const double* s
             return hipGetLastError();
         });
     });
+}
+
+hipError_t launch_tile_all(int nsteps, const Geo& g, const Rates& r, const double* src,
+                           double* out, int64_t stride, hipStream_t st, bool rin) {
+    const int rows = tile_rows(g);
+    if (nsteps < 1 || nsteps > MAX_STEPS_PER_PASS || rows == 0) return hipErrorInvalidValue;
+    const TileShape s = tile_shape(g, rows, nsteps);
+    return dispatch_io(rin, false, [&](auto ri, auto) {
+        constexpr int IN = decltype(ri)::value ? FORM_TWIN : FORM_FULL;
+        switch (s.R) {
+#define LBM_TILE(RR)                                                                              \
+    case RR:                                                                                      \
+        hipLaunchKernelGGL((k_tile_d2q9_all<RR, IN>), s.grid, s.block, s.lds, st, src, out,       \
+                           stride, g, r, nsteps, rows, s.nstrips);                                \
+        break;
+            LBM_TILE(1)
+            LBM_TILE(2)
+            LBM_TILE(3)
+            LBM_TILE(4)
+            LBM_TILE(5)
+            LBM_TILE(6)
+            LBM_TILE(7)
+            LBM_TILE(8)
+#undef LBM_TILE
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    });
+}
+
+// Wherever the grid goes by tiles and TILE_ADJOINT_ROWS rows a wave hold at least two
+// steps: us a step of forward and backward, march and tiles of up to 8 steps: 40^2
+// 6.60 and 4.04, 256^2 8.15 and 5.92, 512^2 15.85 and 12.75, 600^2 19.8 and 16.0; at
+// 700^2, where three steps fit, 27.5 and 24.8.
+int tile_adjoint_steps(const Geo& g, int limit) {
+    const int rows = tile_rows(g);
+    if (rows == 0) return 0;
+    int most = limit < MAX_STEPS_PER_PASS ? limit : MAX_STEPS_PER_PASS;
+    while (most > 1 && tile_shape(g, rows, most).R > TILE_ADJOINT_ROWS) --most;
+    return most > 1 ? most : 0;
+}
+
+int64_t tile_adjoint_table(const Geo& g) {
+    const int rows = tile_rows(g);
+    return rows == 0 ? 0 : (int64_t)tile_shape(g, rows, MAX_STEPS_PER_PASS).grid.x;
+}
+
+hipError_t launch_tile_adjoint(int nsteps, const Geo& g, const Rates& r, const double* lam_in,
+                               double* lam_out, const double* ftop, int64_t stride,
+                               const double* ckpt, double* partials, int64_t ntab,
+                               hipStream_t st) {
+    const int rows = tile_rows(g);
+    if (nsteps < 1 || nsteps > MAX_STEPS_PER_PASS || rows == 0) return hipErrorInvalidValue;
+    const TileShape s = tile_shape(g, rows, nsteps);
+    if ((int64_t)s.grid.x > ntab || ntab > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+    switch (s.R) {
+#define LBM_TILE(RR)                                                                             \
+    case RR:                                                                                     \
+        hipLaunchKernelGGL((k_tile_adjoint_d2q9<RR>), s.grid, s.block, s.lds, st, lam_in,        \
+                           lam_out, ftop, stride, ckpt, partials, (int)ntab, g, r, nsteps, rows, \
+                           s.nstrips);                                                           \
+        break;
+        LBM_TILE(1)
+        LBM_TILE(2)
+        LBM_TILE(3)
+        LBM_TILE(4)
+        LBM_TILE(5)
+        LBM_TILE(6)
+#undef LBM_TILE
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 }  // namespace lbm

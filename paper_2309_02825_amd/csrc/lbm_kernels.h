@@ -83,6 +83,21 @@ hipError_t launch_tile(int nsteps, const Geo& g, const Rates& r, const double* s
 hipError_t launch_steps_all(int nsteps, const Geo& g, const Rates& r, const double* src,
                             double* out, int64_t stride, hipStream_t st, bool rin = false,
                             bool wout = false);
+// The same tiles keeping every state: step j to out + (j - 1) stride without its
+// twins; rin: src holds a state written by a collision.
+hipError_t launch_tile_all(int nsteps, const Geo& g, const Rates& r, const double* src,
+                           double* out, int64_t stride, hipStream_t st, bool rin);
+// nsteps adjoint steps by tiles: lam_out = lambda^{N-nsteps} from lam_in = lambda^N,
+// with f^{N-j} at ftop - (j-1) stride (twins in their partners' planes) or, for
+// j = nsteps, whole at ckpt if that is not NULL; writes ntab eps partials, at least
+// tile_adjoint_table(g).  tile_adjoint_steps: the most steps of a pass within `limit`,
+// 0 where the grid does not go by tiles.
+int tile_adjoint_steps(const Geo& g, int limit);
+int64_t tile_adjoint_table(const Geo& g);
+hipError_t launch_tile_adjoint(int nsteps, const Geo& g, const Rates& r, const double* lam_in,
+                               double* lam_out, const double* ftop, int64_t stride,
+                               const double* ckpt, double* partials, int64_t ntab,
+                               hipStream_t st);
 // nsteps (2) D3Q19 steps in one pass; a block of MS3_TX x MS3_TY threads
 // produces a tile of tile_width3 x tile_height3 columns and marches along z.
 constexpr int MS3_TX = 64, MS3_TY = 8;

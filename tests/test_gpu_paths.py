@@ -163,3 +163,43 @@ def test_d2q9_half_rounds_equal_single_steps(grid, limit):
         assert torch.equal(s.get_state(), ref.get_state()), (grid, limit, n)
     s.close()
     ref.close()
+
+
+@pytest.mark.parametrize("grid", [(1, 1), (2, 3), (5, 1), (1, 40), (48, 17), (49, 16), (47, 300),
+                                  (255, 257), (513, 511), (620, 640), (700, 700), (721, 720),
+                                  (12000, 3)])
+@pytest.mark.parametrize("limit,m", [(2, 5), (4, 9), (8, 1), (8, 2), (8, 8), (8, 19)])
+def test_d2q9_adjoint_tiles_equal_single_steps(grid, limit, m):
+    """Checkpoint segments on grids that go by register tiles (and the first sizes
+    beyond them) against single steps and single adjoint steps: the recomputed states
+    and lambda bit for bit, the planes of the twins untouched; the eps gradient, a sum
+    of m V random products in another order, to 1e-12 of its value or of 1."""
+    _say("D2Q9 adjoint tiles", grid, limit, m)
+    s = _solver(grid, 0.31)
+    gen = torch.Generator().manual_seed(5 + m)
+    shape = (9,) + tuple(reversed(grid))
+    s.set_state((1 + 0.1 * torch.randn(shape, generator=gen, dtype=torch.float64)).to(_dev()), 0)
+    lam = torch.randn(shape, generator=gen, dtype=torch.float64).to(_dev())
+    ckpt = s.current().clone()
+    st = [ckpt]
+    for _ in range(1, m):
+        st.append(s.new_state())
+        s.step_buffers(st[-2], st[-1])
+    ge_ref = torch.full((1,), 0.25, dtype=torch.float64, device=_dev())
+    cur, other = s.to_layout(lam), s.new_state()
+    for n in range(m - 1, -1, -1):
+        s.adjoint_step(st[n], cur, other, ge_ref)
+        cur, other = other, cur
+    s.set_steps_per_pass(limit)
+    ge = torch.full((1,), 0.25, dtype=torch.float64, device=_dev())
+    got = s.to_layout(lam)
+    work = torch.full((max(m - 1, 1) * s.state_elems,), float("nan"), dtype=torch.float64,
+                      device=_dev())
+    s.adjoint_segment(ckpt, m, work, got, s.new_state(), ge)
+    assert torch.equal(s.from_layout(got), s.from_layout(cur))
+    assert abs(ge.item() - ge_ref.item()) <= 1e-12 * max(abs(ge_ref.item()), 1.0)
+    for j in range(1, m):
+        w = s.from_layout(work[(j - 1) * s.state_elems: j * s.state_elems])
+        assert torch.equal(w[:7], s.from_layout(st[j])[:7]), j
+        assert bool(torch.isnan(w[7:]).all()), j
+    s.close()
