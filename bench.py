@@ -48,7 +48,7 @@ D2_STEPS_PER_PASS = 8
 D3_STEPS_PER_PASS = 2
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_k_step.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2309_02825_amd", "csrc", n)
-                  for n in ("lbm_kernels.hip", "lbm_d1.hip", "lbm_d2q9.hip", "lbm_d2q9_pass.h",
+                  for n in ("lbm_kernels.hip", "lbm_d1.hip", "lbm_d2q9.hip", "lbm_d2q9_pass.h", "lbm_pair.h",
                             "lbm_d2q9_tile.hip",
                             "lbm_d2q9_adjoint.hip", "lbm_d3q19.hip",
                             "lbm_d3q19_march.hip", "lbm_batch.hip",

@@ -48,8 +48,8 @@ int pass_rows(const Geo& g, int nstrips, int min_rows, int nsteps, bool* half) {
     return *half ? one : two;
 }
 
-int steps_rows(const Geo& g, int nstrips, int min_rows) {
-    const int slots = round_slots();
+int steps_rows(const Geo& g, int nstrips, int min_rows, int slots) {
+    if (slots == 0) slots = round_slots();
     int64_t per_round = slots / nstrips;
     if (per_round < 1) per_round = 1;
     int64_t nseg = per_round;

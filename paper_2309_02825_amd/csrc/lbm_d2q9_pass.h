@@ -1,7 +1,7 @@
 // The D2Q9 pass of S steps, compiled for one S per source.
 #pragma once
 
-#include "lbm_march.h"
+#include "lbm_pair.h"
 
 namespace lbm {
 namespace {
@@ -23,15 +23,47 @@ __device__ __forceinline__ void ms_strip(const double* __restrict__ src, double*
         ms_tile<S, false, OFF32, NT, IN, OUT, false, DEPTH>(src, dst, g.nx, g.ny, folded(r), x0, ys, ye);
 }
 
+__device__ __forceinline__ void mp_strip(const double* __restrict__ src, double* __restrict__ dst,
+                                         const Geo& g, const Rates& r, int ly, int nstrips,
+                                         MpTwo (*row)[6][64], MpTwo (*pre)[6][64]) {
+    const unsigned t = xcd_remap(blockIdx.x, gridDim.x);
+    const int strip = (int)(t % (unsigned)nstrips);
+    const int seg = (int)(t / (unsigned)nstrips);
+    const int ys = seg * ly, ye = min(ys + ly, g.ny), x0 = strip * MP_WIDTH;
+    if (seg & 1)
+        mp_tile<true>(src, dst, g.nx, g.ny, folded(r), x0, ys, ye, row, pre);
+    else
+        mp_tile<false>(src, dst, g.nx, g.ny, folded(r), x0, ys, ye, row, pre);
+}
+
 // Two waves per SIMD: the register budget (256 per wave) holds S = 8.
 // RIN / WOUT: the source / the result is in the reduced form that the passes of
-// this grid hand to one another (pass_form).  4096^2, 8 steps: 379 us a launch with
-// the 7 planes of FORM_TWIN, 348 us with the 6 of FORM_MOM (1.61 GB algorithmic).
+// this grid hand to one another (pass_form).  The pass between two others goes by the
+// two-wave march (pair_fits; other grids by k_steps_d2q9_seam).  4096^2, 8 steps:
+// 379 us a launch with the 7 planes of FORM_TWIN, 349 us with the 6 of FORM_MOM
+// (1.61 GB algorithmic), 321 us by the two-wave march.
+// The two-wave march moves a lane's two columns as 16 bytes: even rows, so that a pair
+// lies in one chunk and starts on 16 bytes, and buffers that do.  It is taken on grids
+// beyond the Infinity Cache, us for 8 steps by one and two waves: 1600^2 65.8 and 65.5,
+// 2048^2 97.7 and 97.5, 2500^2 150 and 136, 6000^2 728 and 660, 8000 x 7000 1128 and
+// 1022; below, where a segment has few rows, its longer fill loses: 1000^2 28.6 and
+// 40.1, 1448^2 53.7 and 57.7.
+inline bool pair_fits(const Geo& g, const double* src, const double* dst) {
+    return g.nx % 2 == 0 && ((uintptr_t)src | (uintptr_t)dst) % 16 == 0;
+}
+constexpr bool pair_pass(int s, bool off32, bool rin, bool wout) {
+    return s == MP_STEPS && off32 && rin && wout;
+}
 template <int S, bool OFF32, bool RIN, bool WOUT>
-__global__ void __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ void __launch_bounds__(pair_pass(S, OFF32, RIN, WOUT) ? MP_THREADS : MS_THREADS)
+    __attribute__((amdgpu_waves_per_eu(2)))
 k_steps_d2q9(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rates r, int ly,
              int nstrips) {
     constexpr int REDUCED = OFF32 ? FORM_MOM : FORM_TWIN;
+    if constexpr (pair_pass(S, OFF32, RIN, WOUT)) {
+        __shared__ MpTwo row[2][6][64], pre[2][6][64];
+        return mp_strip(src, dst, g, r, ly, nstrips, row, pre);
+    }
     ms_strip<S, OFF32, true, RIN ? REDUCED : FORM_FULL, WOUT ? REDUCED : FORM_FULL>(src, dst, g, r,
                                                                                     ly, nstrips);
 }
@@ -55,7 +87,7 @@ k_steps_d2q9_half(const double* __restrict__ src, double* __restrict__ dst, Geo 
     ms_strip<S, true, NT, IN, OUT, 2>(src, dst, g, r, ly, nstrips);
 }
 
-// The passes at the seams, under 4 GiB: the first of a call on a state that an
+// The one-wave passes that the kernels above leave, under 4 GiB: odd rows, and the first of a call on a state that an
 // earlier call left (its twins are equal, so 7 planes are read), and the one before
 // a single step, which reads populations.
 template <int S, bool NT, int IN, int OUT>
@@ -91,8 +123,18 @@ hipError_t launch_steps_t(const Geo& g, const Rates& r, const double* src, doubl
             } else if (half && S == MAX_STEPS_PER_PASS) {
                 hipLaunchKernelGGL((k_steps_d2q9_half<MAX_STEPS_PER_PASS, true, IN, OUT>), grid, block, 0, st, src,
                                    dst, g, r, ly, nstrips);
-            } else if constexpr (IN == FORM_TWIN || OUT == FORM_TWIN) {
-                if (cached)
+            } else if (pair_pass(S, true, RI, WO) && IN == FORM_MOM && OUT == FORM_MOM && !cached &&
+                       pair_fits(g, src, dst)) {
+                const int np = (g.nx + MP_WIDTH - 1) / MP_WIDTH;
+                const int lp = steps_rows(g, np, kMinRows, 4 * compute_units());
+                const dim3 gp((unsigned)((int64_t)np * ((g.ny + lp - 1) / lp)));
+                hipLaunchKernelGGL((k_steps_d2q9<S, true, RI, WO>), gp, dim3(MP_THREADS), 0, st, src,
+                                   dst, g, r, lp, np);
+            } else if constexpr (IN == FORM_TWIN || OUT == FORM_TWIN || pair_pass(S, true, RI, WO)) {
+                if (cached && IN == FORM_MOM && OUT == FORM_MOM)
+                    hipLaunchKernelGGL((k_steps_d2q9_cached<S, true, RI, WO>), grid, block, 0, st, src,
+                                       dst, g, r, ly, nstrips);
+                else if (cached)
                     hipLaunchKernelGGL((k_steps_d2q9_seam<S, false, IN, OUT>), grid, block, 0, st,
                                        src, dst, g, r, ly, nstrips);
                 else

@@ -288,7 +288,8 @@ __device__ __forceinline__ void ms_tile(const double* __restrict__ src, double* 
 constexpr int kMinRows = 8;
 constexpr int kMinRowsSegment = 3;
 
-int steps_rows(const Geo& g, int nstrips, int min_rows);
+// slots: blocks of one round, 0 for those of the one-wave march.
+int steps_rows(const Geo& g, int nstrips, int min_rows, int slots = 0);
 // The same for a plain pass of nsteps, which may leave half of the round empty.
 int pass_rows(const Geo& g, int nstrips, int min_rows, int nsteps, bool* half);
 

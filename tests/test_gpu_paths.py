@@ -203,3 +203,26 @@ def test_d2q9_adjoint_tiles_equal_single_steps(grid, limit, m):
         assert torch.equal(w[:7], s.from_layout(st[j])[:7]), j
         assert bool(torch.isnan(w[7:]).all()), j
     s.close()
+
+
+@pytest.mark.parametrize("grid", [(2048, 2049), (4096, 1040), (3998, 1111), (112, 50001),
+                                  (30002, 131), (2050, 1987), (2001, 2048)])
+def test_d2q9_two_wave_marches_equal_single_steps(grid):
+    """The two-wave march between two other passes (even rows beyond the Infinity
+    Cache, ragged last strips and segments; odd rows go by one wave), against
+    lb_step_buffers single steps, bit for bit."""
+    _say("D2Q9 two-wave march", grid)
+    s, ref = _solver(grid, 0.31), _solver(grid, 0.31)
+    th0 = _rough(grid, 9)
+    s.init(th0, None)
+    ref.init(th0, None)
+    s.step(33)
+    cur = 0
+    for _ in range(33):
+        ref.step_buffers(ref.bufs[cur], ref.bufs[1 - cur])
+        cur ^= 1
+    if cur:
+        ref.bufs[0].copy_(ref.bufs[1])
+    assert torch.equal(s.get_state(), ref.get_state()), grid
+    s.close()
+    ref.close()
