@@ -18,8 +18,8 @@ namespace {
 // 545 us).  Same arithmetic a node, so bitwise single steps.
 //
 // Bounds: memory.  4096^2, 8 steps: 349 us by one wave, which issues vector
-// instructions three quarters of the time at a clock of 1.9 GHz; 321 us here, 5.9 TB/s
-// with the halos.  Two rows ahead: no change.
+// instructions three quarters of the time at a clock of 1.9 GHz; 312-321 us here, about
+// 5.6 TB/s with the halos.  Two rows ahead: no change.
 // ---------------------------------------------------------------------------
 constexpr int MP_THREADS = 128, MP_STEPS = 8, MP_STAGES = 4;
 constexpr int MP_COLUMNS = 128, MP_WIDTH = MP_COLUMNS - 2 * MP_STEPS;
