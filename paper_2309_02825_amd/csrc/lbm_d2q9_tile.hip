@@ -288,20 +288,21 @@ k_tile_adjoint_d2q9(const double* __restrict__ src, double* __restrict__ dst,
 #pragma unroll
         for (int i = 0; i < 9; ++i) lam[q][i] = get(src, i, at[q + 1]);
     auto owned = [&](int q) { return top + q >= S && top + q < rin - S; };
-    // f^{N-j} of row q, before the lane shifts.  A row that the block does not own
-    // gets an empty buffer, which reads nothing: behind a branch the loads of the next
-    // step would be waited for where the branch ends.
+    // f^{N-j} of row q, before the lane shifts.  A row that the block does not own, and
+    // every row after the last step, reads nothing (tile_read): behind a branch the
+    // loads of the next step would be waited for where the branch ends.
     double f[R][9];
     const unsigned bytes = (unsigned)(9 * CHUNK * 8 * ((g.nx * g.ny + CHUNK - 1) / CHUNK));
     auto load_f = [&](int j, int q) {
-        const bool last = j == S && ckpt != nullptr;
-        const double* fs = last ? ckpt : ftop - (int64_t)(j - 1) * stride;
+        const TileRead rd = tile_read(j, S, owned(q));
+        const bool last = rd.step == S && ckpt != nullptr;
+        const double* fs = last ? ckpt : ftop - (int64_t)(rd.step - 1) * stride;
         const int p7 = last ? 7 : 5, p8 = last ? 8 : 6;
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<double*>(fs), (short)0, j <= S && owned(q) ? (int)bytes : 0, 0x00020000);
+            const_cast<double*>(fs), (short)0, (int)bytes, 0x00020000);
         auto fetch = [&](int plane, unsigned off) {
             return __builtin_bit_cast(
-                double, __builtin_amdgcn_raw_buffer_load_b64(rs, off, plane * (int)CHUNK * 8, 0));
+                double, __builtin_amdgcn_raw_buffer_load_b64(rs, off | rd.skip, plane * (int)CHUNK * 8, 0));
         };
         f[q][0] = fetch(0, at[q + 1]);
         f[q][1] = fetch(1, at[q + 1]);

@@ -98,6 +98,20 @@ hipError_t launch_tile_adjoint(int nsteps, const Geo& g, const Rates& r, const d
                                double* lam_out, const double* ftop, int64_t stride,
                                const double* ckpt, double* partials, int64_t ntab,
                                hipStream_t st);
+// What the loads of the state for step j of a tile's S adjoint steps address: the state
+// of step `step` at the lane's offset or'ed with `skip`.  The loads run a step ahead, so
+// those of j = S + 1 have no state, and rows that the block does not own need none: they
+// address a state that there is at an offset past its end (states of tile grids are far
+// under 2 GiB), which the bounds check of a buffer load turns into no access.  (A buffer
+// of no records in front of the caller's memory would leave that to the check of its
+// size less the scalar offset of the plane, which is then negative.)
+struct TileRead {
+    int step;
+    unsigned skip;
+};
+__host__ __device__ constexpr TileRead tile_read(int j, int S, bool owned) {
+    return TileRead{j < S ? j : S, j <= S && owned ? 0u : 0x80000000u};
+}
 // nsteps (2) D3Q19 steps in one pass; a block of MS3_TX x MS3_TY threads
 // produces a tile of tile_width3 x tile_height3 columns and marches along z.
 constexpr int MS3_TX = 64, MS3_TY = 8;
