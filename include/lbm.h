@@ -171,7 +171,8 @@ lb_status lb_theta_from_velocity(lb_solver* s, const double* u0, double* theta0,
  * call reads twins from their partners too unless the state came from lb_init
  * or lb_set_state: a caller that changes the current buffer in place must go
  * through lb_set_state.  After an LB_ERR_HIP return (a launch that failed)
- * the current state is unspecified and must be set again. */
+ * the current state is unspecified and must be set again; where it was left
+ * between two passes, calls that need a state return LB_ERR_STATE until then. */
 lb_status lb_step(lb_solver* s, int64_t nsteps);
 
 /* LB_FLAG_BOUNDED solvers: advance nsteps >= 0 time steps on the interval.
@@ -402,7 +403,9 @@ lb_status lb_batch_autotune(lb_batch* b, int32_t steps_per_trial, int32_t* best_
  * first waits for the batch's stream and clears the cache) and replayed with a
  * single hipGraphLaunch.  Launches hand the state on as in lb_step: only the last
  * launch of a call stores all populations, and the first reads twins from their
- * partners unless the pool came from lb_batch_init. */
+ * partners unless the pool came from lb_batch_init.  After an LB_ERR_HIP return the
+ * pool is unspecified; once two launches have gone out, lb_batch_step and
+ * lb_batch_macro return LB_ERR_STATE until lb_batch_init. */
 lb_status lb_batch_step(lb_batch* b, int64_t nsteps, int32_t use_graph);
 
 /* theta (packed V_b per instance) and u (packed 2 x V_b per instance, at

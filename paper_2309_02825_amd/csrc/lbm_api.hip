@@ -469,19 +469,21 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
                                             : lbm::pass_form(s->d, s->g);
             const double* src = s->buf[s->cur];
             double* dst = s->buf[1 - s->cur];
+            hipError_t e;
             if (steps == 1)
-                LB_HIP(lbm::launch_step(s->d, s->g, s->r, src, dst, s->stream,
-                                        in == lbm::FORM_TWIN, out == lbm::FORM_TWIN),
-                       "step launch");
+                e = lbm::launch_step(s->d, s->g, s->r, src, dst, s->stream, in == lbm::FORM_TWIN,
+                                     out == lbm::FORM_TWIN);
             else if (tiles)
-                LB_HIP(lbm::launch_tile(steps, s->g, s->r, src, dst, s->stream, in, out),
-                       "multi-step launch");
+                e = lbm::launch_tile(steps, s->g, s->r, src, dst, s->stream, in, out);
             else if (s->d == 2)
-                LB_HIP(lbm::launch_steps(steps, s->g, s->r, src, dst, s->stream, in, out),
-                       "multi-step launch");
+                e = lbm::launch_steps(steps, s->g, s->r, src, dst, s->stream, in, out);
             else
-                LB_HIP(lbm::launch_steps3(steps, s->g, s->r, src, dst, s->stream, in, out),
-                       "multi-step launch");
+                e = lbm::launch_steps3(steps, s->g, s->r, src, dst, s->stream, in, out);
+            if (e != hipSuccess) {
+                // no other call reads FORM_MOM
+                if (form == lbm::FORM_MOM) s->inited = false;
+                return hip_fail(e, steps == 1 ? "step launch" : "multi-step launch");
+            }
             form = out == lbm::FORM_FULL ? lbm::FORM_TWIN : out;
             s->cur ^= 1;
             s->steps += steps;
@@ -1091,10 +1093,12 @@ static int64_t batch_launches(const lb_batch* b, int64_t nsteps) {
 // from their partners' planes when the state came from a collision
 // (b->twin_ok), every later launch does, and only the last launch stores the
 // twins, so that the pool a call leaves holds a complete state.
+// *launched: the launches enqueued, also where one fails.
 static lb_status batch_launch_plain(lb_batch* b, int64_t nsteps, hipStream_t st, int cur,
-                                    int* cur_out) {
+                                    int* cur_out, int64_t* launched) {
     const int64_t total = batch_launches(b, nsteps);
     int64_t launch = 0;
+    *launched = 0;
     const int in_first = b->twin_ok ? lbm::FORM_TWIN : lbm::FORM_FULL;
     int in = in_first, out = in_first;
     // in / out: the forms of the launch; between: what a launch leaves to the next
@@ -1113,6 +1117,7 @@ static lb_status batch_launch_plain(lb_batch* b, int64_t nsteps, hipStream_t st,
                                            b->pool[1 - cur], b->off32, mode_one_wave(b->tx), st,
                                            in, out),
                    "batch multi-step launch");
+            *launched = launch;
             cur ^= 1;
         }
         for (; n < nsteps; ++n) {
@@ -1121,6 +1126,7 @@ static lb_status batch_launch_plain(lb_batch* b, int64_t nsteps, hipStream_t st,
                                           b->pool[1 - cur], st, in == lbm::FORM_TWIN,
                                           out == lbm::FORM_TWIN),
                    "batch step launch");
+            *launched = launch;
             cur ^= 1;
         }
     } else {
@@ -1130,6 +1136,7 @@ static lb_status batch_launch_plain(lb_batch* b, int64_t nsteps, hipStream_t st,
                                           b->pool[cur], b->pool[1 - cur], st,
                                           in == lbm::FORM_TWIN, out == lbm::FORM_TWIN),
                    "batch step launch");
+            *launched = launch;
             cur ^= 1;
         }
     }
@@ -1144,8 +1151,13 @@ lb_status lb_batch_step(lb_batch* b, int64_t nsteps, int32_t use_graph) {
     if (nsteps == 0) return LB_OK;
     int next = b->cur;
     if (!use_graph) {
-        lb_status st = batch_launch_plain(b, nsteps, b->stream, b->cur, &next);
-        if (st != LB_OK) return st;
+        int64_t launched;
+        lb_status st = batch_launch_plain(b, nsteps, b->stream, b->cur, &next, &launched);
+        if (st != LB_OK) {
+            // the second launch writes the pool that the first read
+            if (launched > 1) b->inited = false;
+            return st;
+        }
     } else {
         auto key = std::make_tuple(nsteps, b->cur, b->twin_ok);
         auto it = b->graphs.find(key);
@@ -1158,7 +1170,8 @@ lb_status lb_batch_step(lb_batch* b, int64_t nsteps, int32_t use_graph) {
             hipGraph_t graph = nullptr;
             LB_HIP(hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal),
                    "hipStreamBeginCapture");
-            lb_status st = batch_launch_plain(b, nsteps, b->capture, b->cur, nullptr);
+            int64_t launched;  // captured, so the pools are as they were
+            lb_status st = batch_launch_plain(b, nsteps, b->capture, b->cur, nullptr, &launched);
             hipError_t e = hipStreamEndCapture(b->capture, &graph);
             if (st != LB_OK) {
                 if (graph) (void)hipGraphDestroy(graph);

@@ -1,0 +1,67 @@
+"""What the library asks of a HIP runtime, on one that runs on the host: launches,
+allocations and failures that a GPU machine does not show."""
+import os
+import sys
+
+import pytest
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+
+from host_runtime import run
+
+
+@pytest.mark.parametrize("grid,after", [((2048, 2048), 2), ((320, 320), 2), ((256, 256, 256), 2),
+                                        ((320, 320), 1), ((64, 64, 64, 64), 2)])
+def test_failed_launch_between_passes_leaves_no_state(grid, after):
+    """A launch that fails after others of the same call: the buffer may then hold the
+    reduced form that only the next pass reads, so every call that needs a state is
+    refused until one is set; a state in populations can be stepped on."""
+    out = run(f'''
+h = solver({grid!r})
+L.lb_init(h, C, None)
+fail_launch({after})
+codes = []
+def code(f, *a):
+    try:
+        f(*a)
+        codes.append(0)
+    except L.LBError as e:
+        codes.append(e.status)
+code(L.lb_step, h, 40)
+calls()
+code(L.lb_step, h, 8)
+first = (kernels() or [None])[0]
+code(L.lb_macro, h, C)
+L.lb_set_state(h, C, 0)
+code(L.lb_step, h, 8)
+out = [codes, first]
+''')
+    codes, first = out
+    assert codes[0] == -5 and codes[3] == 0
+    if len(grid) == 4:  # single steps hand on populations
+        assert codes[1:3] == [0, 0] and first == "k_step<4, true, true, true>"
+    else:
+        assert codes[1:3] == [-6, -6] and first is None
+
+
+@pytest.mark.parametrize("tile", [(-8, 64), (-24, 32), (0, 0)])
+@pytest.mark.parametrize("after", [0, 1, 2, 3])
+def test_failed_batch_launch_leaves_no_state(tile, after):
+    """The same for a batch: its pool is intact until the second launch."""
+    out = run(f'''
+cfgs = [L.make_config((70, 50), 1 / 70, 0.2 / 70 ** 2 / 0.02, 0.02) for _ in range(3)]
+h = L.lb_batch_create(cfgs, 0, A, B)
+L.lb_batch_set_tile(h, *{tile!r})
+L.lb_batch_init(h, C, None)
+fail_launch({after})
+codes = []
+for f in (lambda: L.lb_batch_step(h, 40, False), lambda: L.lb_batch_step(h, 8, False),
+          lambda: L.lb_batch_macro(h, C)):
+    try:
+        f()
+        codes.append(0)
+    except L.LBError as e:
+        codes.append(e.status)
+out = codes
+''')
+    assert out == ([-5, 0, 0] if after < 2 else [-5, -6, -6])
