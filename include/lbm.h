@@ -19,8 +19,10 @@
  *     torch tensors).  A solver borrows the pointers given to it and must be
  *     destroyed before they are freed.  The library owns only its host-side
  *     solver object and a few small device tables (parameters, reduction
- *     partials), allocated at creation (lb_adjoint_segment grows a table
- *     of per-launch partials on demand) and freed by lb_destroy.
+ *     partials), allocated at creation and freed by lb_destroy.  Three calls
+ *     allocate: lb_adjoint_segment grows a table of per-launch partials on
+ *     demand, lb_theta_from_velocity its workspace, and lb_set_option four
+ *     bytes of pinned host memory with a solver's first check interval.
  *   - Work is enqueued asynchronously on the HIP stream given at creation
  *     (NULL = the default stream); the host returns before the GPU finishes.
  *   - One solver or batch object must not be used from two host threads at
@@ -208,8 +210,9 @@ lb_status lb_step_bounded(lb_solver* s, int64_t nsteps, const double* walls);
  * or not positive (a diverged run, or a corrupted state: the Cole-Hopf
  * velocity divides by theta, Sec. II), lb_step returns LB_ERR_NONFINITE at
  * once; the state and step counter are those after that launch.  A check
- * reads the state once and synchronises the stream.  Bounded solvers
- * (lb_step_bounded) are not checked. */
+ * reads the state once and synchronises the stream.  Setting the first interval
+ * allocates the pinned flag that the checks use (LB_ERR_HIP if that fails, with the
+ * interval as it was).  Bounded solvers (lb_step_bounded) are not checked. */
 enum { LB_OPT_STEPS_PER_PASS = 1, LB_OPT_CHECK_INTERVAL = 2 };
 lb_status lb_set_option(lb_solver* s, int32_t option, int32_t value);
 

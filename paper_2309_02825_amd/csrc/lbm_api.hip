@@ -201,7 +201,7 @@ struct lb_solver {
     double* partials;
     int64_t npartials;
     int* flag;
-    int* check_flag;  // LB_OPT_CHECK_INTERVAL: pinned host memory, allocated by the first check
+    int* check_flag;  // LB_OPT_CHECK_INTERVAL: pinned host memory, allocated with the first interval
     int steps_per_pass;  // LB_OPT_STEPS_PER_PASS: 1, 2, 4 or 8
     int64_t check_interval;  // LB_OPT_CHECK_INTERVAL: 0 (off) or steps between state checks
     int64_t since_check;     // steps lb_step has run since the last state check
@@ -356,10 +356,6 @@ static lb_status after_steps(lb_solver* s, int64_t steps) {
     // the kernel sets a flag in pinned host memory, so that a check costs a launch
     // and a wait (with a flag in device memory, cleared and copied back, the
     // stream stood still for 57 us a check)
-    if (!s->check_flag)
-        LB_HIP(hipHostMalloc((void**)&s->check_flag, sizeof(int),
-                             hipHostMallocMapped | hipHostMallocCoherent),
-               "hipHostMalloc check flag");
     *(volatile int*)s->check_flag = 0;  // no launch that sets it is in flight
     LB_HIP(lbm::launch_check_state(s->d, s->g, s->buf[s->cur], s->check_flag, s->stream),
            "check_state launch");
@@ -534,6 +530,10 @@ lb_status lb_set_option(lb_solver* s, int32_t option, int32_t value) {
         }
         case LB_OPT_CHECK_INTERVAL:
             if (value < 0) return fail(LB_ERR_INVALID_ARG, "the check interval must be >= 0");
+            if (value > 0 && !s->check_flag)  // here, so that lb_step allocates nothing
+                LB_HIP(hipHostMalloc((void**)&s->check_flag, sizeof(int),
+                                     hipHostMallocMapped | hipHostMallocCoherent),
+                       "hipHostMalloc check flag");
             s->check_interval = value;
             s->since_check = 0;
             return LB_OK;

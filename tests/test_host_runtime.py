@@ -65,3 +65,25 @@ for f in (lambda: L.lb_batch_step(h, 40, False), lambda: L.lb_batch_step(h, 8, F
 out = codes
 ''')
     assert out == ([-5, 0, 0] if after < 2 else [-5, -6, -6])
+
+
+def test_steps_allocate_nothing_also_with_checks():
+    """The flag of the checks is allocated with the interval, not by a step."""
+    before, steps, again, end = run('''
+h = solver((320, 320))
+L.lb_init(h, C, None)
+calls()
+L.lb_set_option(h, L.LB_OPT_CHECK_INTERVAL, 4)
+before = calls()
+L.lb_step(h, 20)
+steps = calls()
+L.lb_set_option(h, L.LB_OPT_CHECK_INTERVAL, 0)
+L.lb_set_option(h, L.LB_OPT_CHECK_INTERVAL, 5)
+again = calls()
+L.lb_destroy(h)
+out = [before, steps, again, calls()]
+''')
+    assert [c.split()[0] for c in before] == ["hostmalloc"]
+    assert "launch k_check_state<2>" in steps and "sync" in steps
+    assert not [c for c in steps if "malloc" in c or "free" in c]
+    assert again == [] and end.count("hostfree") == 1
