@@ -150,9 +150,9 @@ lb_status lb_init(lb_solver* s, const double* theta0, const double* grad_theta0,
  * rule dx (-u_{j-1} + 13 u_j + 13 u_{j+1} - u_{j+2})/24 (fourth order);
  * grad theta0 = -u0 theta0/(2 nu) exactly.  u0 must be a periodic gradient
  * field (the potential symmetry of Sec. II) whose line integrals over a
- * period vanish; otherwise theta0 is not periodic.  The first call allocates a
- * workspace of about V doubles, which the solver keeps; every call synchronises
- * the stream. */
+ * period vanish; otherwise theta0 is not periodic.  Allocates a workspace of
+ * about V doubles: up to 64 MiB the first call does and the solver keeps it, a
+ * larger one is freed before the call returns.  Synchronises the stream. */
 lb_status lb_theta_from_velocity(lb_solver* s, const double* u0, double* theta0, double* grad);
 
 /* Advance nsteps >= 0 time steps (evolution equation of Sec. III.A: collide in

@@ -210,7 +210,7 @@ struct lb_solver {
     double* wall_now;    // bounded: theta at the two end nodes at the current time
     double* seg_partials;  // lb_adjoint_segment: one partials table per launch
     int64_t seg_cap;       // doubles seg_partials holds
-    double* potential;     // lb_theta_from_velocity's workspace, allocated by its first call
+    double* potential;     // lb_theta_from_velocity's workspace, where it is small enough to be kept
     double* scratch;       // this device's copy of `scratch` (lb_adjoint_segment_static)
 };
 
@@ -619,13 +619,21 @@ lb_status lb_theta_from_velocity(lb_solver* s, const double* u0, double* theta0,
     if (!s || !u0 || !theta0) return fail(LB_ERR_INVALID_ARG, "NULL argument");
     lb_status st = not_bounded(s, "lb_theta_from_velocity is periodic only");
     if (st != LB_OK) return st;
-    if (!s->potential)  // kept for the next call, freed with the solver
-        LB_HIP(hipMalloc((void**)&s->potential,
-                         sizeof(double) * (size_t)lbm::potential_workspace(s->d, s->g)),
-               "hipMalloc potential workspace");
-    hipError_t e = lbm::launch_theta_from_velocity(s->d, s->g, s->cfg.dx, s->cfg.nu, u0,
-                                                   s->potential, theta0, grad, s->stream);
+    // A workspace of up to kKeptPotential bytes stays with the solver: an allocation and
+    // its release take 270 us (2048^2, 34 MB: 70 us a call without).  A larger one is given
+    // back, so that no more memory stays behind a call that programs make once (4096^2
+    // 240 us kept, 500 so; 512^3, 1 GiB, 2.1 and 2.4 ms).
+    constexpr size_t kKeptPotential = (size_t)64 << 20;
+    const size_t bytes = sizeof(double) * (size_t)lbm::potential_workspace(s->d, s->g);
+    double* work = s->potential;
+    if (!work) {
+        LB_HIP(hipMalloc((void**)&work, bytes), "hipMalloc potential workspace");
+        if (bytes <= kKeptPotential) s->potential = work;
+    }
+    hipError_t e = lbm::launch_theta_from_velocity(s->d, s->g, s->cfg.dx, s->cfg.nu, u0, work,
+                                                   theta0, grad, s->stream);
     hipError_t e2 = hipStreamSynchronize(s->stream);
+    if (work != s->potential) (void)hipFree(work);
     if (e != hipSuccess) return hip_fail(e, "theta_from_velocity launch");
     if (e2 != hipSuccess) return hip_fail(e2, "hipStreamSynchronize");
     return LB_OK;

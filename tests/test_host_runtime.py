@@ -87,3 +87,27 @@ out = [before, steps, again, calls()]
     assert "launch k_check_state<2>" in steps and "sync" in steps
     assert not [c for c in steps if "malloc" in c or "free" in c]
     assert again == [] and end.count("hostfree") == 1
+
+
+@pytest.mark.parametrize("grid,kept", [((2048, 2048), True), ((64, 64, 64), True),
+                                       ((512, 512, 512), False), ((3000, 3000), False)])
+def test_velocity_workspace_is_kept_up_to_a_bound(grid, kept):
+    """A small workspace of the front end serves the solver's later calls and goes with
+    it; a large one is given back by every call."""
+    first, second, end = run(f'''
+h = solver({grid!r})
+calls()
+L.lb_theta_from_velocity(h, C, D)
+first = calls()
+L.lb_theta_from_velocity(h, C, D)
+second = calls()
+L.lb_destroy(h)
+out = [first, second, calls()]
+''')
+    count = lambda lines, what: sum(c.split()[0] == what for c in lines)
+    size = [int(c.split()[1]) for c in first if c.startswith("malloc")]
+    assert len(size) == 1 and (size[0] <= 64 << 20) == kept
+    assert count(first, "free") == (0 if kept else 1)
+    assert [count(second, "malloc"), count(second, "free")] == ([0, 0] if kept else [1, 1])
+    assert first[-1] != "free" or first[-2] == "sync"
+    assert count(end, "free") == (3 if kept else 2)
