@@ -193,6 +193,7 @@ struct lb_solver {
     int d, q;
     Geo g;
     Rates r;
+    lbm::Plan3 plan3;  // D3Q19
     hipStream_t stream;
     double* buf[2];
     int cur;
@@ -283,6 +284,7 @@ lb_status lb_create(const lb_config* cfg, void* hip_stream, double* f_a, double*
     s->q = q_of(cfg->dim);
     s->g = make_geo(cfg);
     s->r = make_rates(cfg->dim, cfg->dx, cfg->dt, cfg->nu);
+    if (s->d == 3) s->plan3 = lbm::plan3(s->g);
     s->stream = (hipStream_t)hip_stream;
     s->buf[0] = f_a;
     s->buf[1] = f_b;
@@ -411,8 +413,8 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
     }
     // Launch plan: on D2Q9 grids of one round of tiles (tile_rows) the fewest
     // passes within the limit, of equal lengths; on larger D2Q9 grids passes
-    // of 8, 4 and 2 steps (within the limit); on D3Q19 passes of 2 where passes3 has them, then single steps, as runs (steps per launch,
-    // launches).  Between two launches the buffer holds no more than the
+    // of 8, 4 and 2 steps (within the limit); on D3Q19 passes of 2 where plan3 has them, then single
+    // steps, as runs (steps per launch, launches).  Between two launches the buffer holds no more than the
     // next one needs (FORM_*, lbm_lattice.h): the collision's 6 or 10
     // quantities before a pass, the independent populations before a single
     // step.  The last launch, and any launch whose state is checked
@@ -438,7 +440,7 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
                 n += k * pass;
             }
         } else if (s->d == 3 && s->steps_per_pass >= lbm::MAX_STEPS_PER_PASS_3D &&
-                   lbm::passes3(s->g)) {
+                   s->plan3.passes) {
             const int pass = lbm::MAX_STEPS_PER_PASS_3D;
             const int64_t k = (nsteps - n) / pass;
             if (k > 0) runs.emplace_back(pass, k);
@@ -474,7 +476,7 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
             else if (s->d == 2)
                 e = lbm::launch_steps(steps, s->g, s->r, src, dst, s->stream, in, out);
             else
-                e = lbm::launch_steps3(steps, s->g, s->r, src, dst, s->stream, in, out);
+                e = lbm::launch_steps3(steps, s->g, s->r, src, dst, s->stream, in, out, s->plan3);
             if (e != hipSuccess) {
                 // no other call reads FORM_MOM
                 if (form == lbm::FORM_MOM) s->inited = false;

@@ -268,10 +268,9 @@ bool march3_fits(const Geo& g) {
 
 template <int S>
 static hipError_t launch_steps3_t(const Geo& g, const Rates& r, const double* src, double* dst,
-                                  hipStream_t st, int in, int out) {
+                                  hipStream_t st, int in, int out, int lz) {
     const int ntx = (g.nx + tile_width3(S) - 1) / tile_width3(S);
     const int nty = (g.ny + tile_height3(S) - 1) / tile_height3(S);
-    const int lz = segment_planes(g.nz, (int64_t)ntx * nty);
     const int64_t nseg = (g.nz + lz - 1) / lz;  // every segment non-empty
     const int64_t nb = (int64_t)ntx * nty * nseg;
     if (nb > (int64_t)UINT32_MAX) return hipErrorInvalidValue;
@@ -300,13 +299,13 @@ static int64_t march3_tiles(const Geo& g) {
 // k_march_d3q19; the first launch of a call, which reads 19 or 13 planes, and every
 // launch on z-planes of 2 GiB on the 8-row tiles.
 hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
-                         hipStream_t st, int in, int out) {
-    if (g.nw != 1 || nsteps != 2) return hipErrorInvalidValue;
+                         hipStream_t st, int in, int out, const Plan3& plan) {
+    if (g.nw != 1 || nsteps != 2 || plan.lz_first < 1 || plan.lz < 1) return hipErrorInvalidValue;
     if (in == FORM_MOM) {
         if (!march3_fits(g)) return hipErrorInvalidValue;  // pass_form
-        return launch_march3(g, r, src, dst, st, segment_planes(g.nz, march3_tiles(g)), out);
+        return launch_march3(g, r, src, dst, st, plan.lz, out);
     }
-    return launch_steps3_t<2>(g, r, src, dst, st, in, out);
+    return launch_steps3_t<2>(g, r, src, dst, st, in, out, plan.lz_first);
 }
 
 // Whether a run on this grid takes passes of two steps: below some 200 thousand
@@ -315,12 +314,17 @@ hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double*
 // alone on its CU); a single step one per 18 thousand nodes or 40 thousand threads
 // of its launch grid, the larger (40^3: 5.2 a step in single steps, 10.4 in passes;
 // 64^3 12.6 and 10.8).
-bool passes3(const Geo& g) {
+Plan3 plan3(const Geo& g) {
+    const int64_t first = (int64_t)((g.nx + tile_width3(2) - 1) / tile_width3(2)) *
+                          ((g.ny + tile_height3(2) - 1) / tile_height3(2));
+    Plan3 p;
     double planes;
-    (void)segment_planes(g.nz, march3_tiles(g), &planes);
+    p.lz_first = segment_planes(g.nz, first);
+    p.lz = segment_planes(g.nz, march3_tiles(g), &planes);
     const double threads = (double)launch_shape(3, g).nblocks * 256.0;
     const double single = std::max((double)g.V / 18000.0, threads / 40000.0);
-    return 5.0 + 1.95 * planes < 2.0 * single;
+    p.passes = 5.0 + 1.95 * planes < 2.0 * single;
+    return p;
 }
 
 }  // namespace lbm

@@ -118,9 +118,15 @@ constexpr int MS3_TX = 64, MS3_TY = 8;
 constexpr int MAX_STEPS_PER_PASS_3D = 2;
 __host__ __device__ constexpr int tile_width3(int nsteps) { return MS3_TX - 2 * nsteps; }
 __host__ __device__ constexpr int tile_height3(int nsteps) { return MS3_TY - 2 * nsteps; }
+// How runs on a D3Q19 grid go, worked out once per solver (the search over segment
+// lengths takes 0.13 ms of host time at 65,535 planes).
+struct Plan3 {
+    bool passes = false;         // passes of two steps rather than single ones
+    int lz_first = 0, lz = 0;    // planes per segment: first pass of a call, later ones
+};
+Plan3 plan3(const Geo& g);
 hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
-                         hipStream_t st, int in, int out);
-bool passes3(const Geo& g);  // whether runs on this grid take passes of two steps
+                         hipStream_t st, int in, int out, const Plan3& plan);
 // The same two steps from FORM_MOM on taller tiles, segments of lz planes; z-planes
 // under 2 GiB.
 constexpr int MARCH3_W = 60, MARCH3_H = 8;

@@ -111,3 +111,24 @@ out = [first, second, calls()]
     assert [count(second, "malloc"), count(second, "free")] == ([0, 0] if kept else [1, 1])
     assert first[-1] != "free" or first[-2] == "sync"
     assert count(end, "free") == (3 if kept else 2)
+
+
+def test_d3q19_plan_is_not_searched_per_launch():
+    """Host time of a pass does not grow with the planes of the grid: 1 x 1 x 65535
+    against 64^3 (with the search of segment lengths in every launch, 30 times)."""
+    t = run('''
+import time
+out = []
+for grid in ((64, 64, 64), (1, 1, 65535)):
+    h = solver(grid)
+    L.lb_init(h, C, None)
+    best = 1e9
+    for _ in range(5):
+        rt.host_log_clear()
+        t0 = time.perf_counter()
+        L.lb_step(h, 400)
+        best = min(best, time.perf_counter() - t0)
+    out.append([best, sum("march" in k for k in kernels())])
+''')
+    assert t[0][1] == t[1][1] == 199
+    assert t[1][0] < 5 * t[0][0], t
