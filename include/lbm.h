@@ -191,9 +191,9 @@ lb_status lb_step_bounded(lb_solver* s, int64_t nsteps, const double* walls);
  * one pass over the state in HBM (temporal blocking: the intermediate steps
  * stay on chip).  D2Q9: where one workgroup per CU holds the grid in register
  * tiles, a run of nsteps is split into the fewest passes within the limit, of
- * equal lengths; on larger grids greedily into passes of 8, 4 and 2 steps
- * (within the limit) and single steps, where one wave marches down a
- * strip of columns, neighbouring columns exchange populations by lane shifts
+ * equal lengths; on larger grids, and where passes of up to four steps take as
+ * few launches so, greedily into passes of 8, 4 and 2 steps (within the limit)
+ * and single steps, where one wave marches down a strip of columns, neighbouring columns exchange populations by lane shifts
  * and rows are delayed in registers.  D3Q19: passes of 2 steps (x-y tiles
  * marching along z, populations exchanged through LDS) and a single step for
  * an odd remainder, when the limit is 2 or more and the grid is large enough

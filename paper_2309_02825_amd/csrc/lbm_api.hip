@@ -411,9 +411,9 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
         s->steps += nsteps;
         return after_steps(s, nsteps);
     }
-    // Launch plan: on D2Q9 grids of one round of tiles (tile_rows) the fewest
-    // passes within the limit, of equal lengths; on larger D2Q9 grids passes
-    // of 8, 4 and 2 steps (within the limit); on D3Q19 passes of 2 where plan3 has them, then single
+    // Launch plan: on D2Q9 where tile_plan says tiles the fewest passes within
+    // the limit, of equal lengths, else passes of 8, 4 and 2 steps (within the
+    // limit); on D3Q19 passes of 2 where plan3 has them, then single
     // steps, as runs (steps per launch, launches).  Between two launches the buffer holds no more than the
     // next one needs (FORM_*, lbm_lattice.h): the collision's 6 or 10
     // quantities before a pass, the independent populations before a single
@@ -423,7 +423,9 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
     // reads the independent populations of it unless the state came from
     // lb_init or lb_set_state.
     std::vector<std::pair<int, int64_t>> runs;
-    const bool tiles = s->d == 2 && s->steps_per_pass > 1 && lbm::tile_rows(s->g) > 0;
+    const lbm::TilePlan plan = s->d == 2 ? lbm::tile_plan(s->g, nsteps, s->steps_per_pass)
+                                         : lbm::TilePlan{false, lbm::pass_form(s->d, s->g)};
+    const bool tiles = plan.tiles;
     {
         int64_t n = 0;
         if (tiles) {
@@ -464,7 +466,7 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
                                          : steps == 1;
             const int out = last || checked ? lbm::FORM_FULL
                             : next_single   ? lbm::FORM_TWIN
-                                            : lbm::pass_form(s->d, s->g);
+                                            : plan.form;
             const double* src = s->buf[s->cur];
             double* dst = s->buf[1 - s->cur];
             hipError_t e;

@@ -410,6 +410,33 @@ int tile_rows(const Geo& g) {
     return rows <= kMaxRows ? rows : 0;
 }
 
+// How a run of `nsteps` in passes of up to `limit` goes.
+//
+// Tiles of kTall rows and more lose to the march in passes of at most four steps, unless
+// they save a launch (us a call, tiles and march: 512^2, 23 rows, 2 steps 8.6 and 8.0,
+// 4 steps 10.5 and 10.1, but 3 steps 9.7 and 13.5; 700^2 2 steps 13.5 and 11.3, 4 steps
+// 16.7 and 13.2; 450^2, 18 rows, 7.2 and 7.5, 9.1 and 9.7).
+//
+// Passes hand on FORM_MOM, with which a run of three launches and more takes three
+// kernels, the first reading FORM_TWIN.  Where a launch takes little more than to fetch
+// its kernel, runs of three to five hand on FORM_TWIN, which takes two kernels, and so do
+// those of the march (us a call, FORM_MOM and FORM_TWIN: tiles, 17 steps, 256^2 21.7 and
+// 20.3, 512^2 42.2 and 36.0, 600^2, 32 rows, 47.1 and 44.4; 650^2, 37 rows, 48.1 and
+// 49.3, 40^2 14.9 and 15.3; 320^2, 6400 steps, no difference but the bytes).
+TilePlan tile_plan(const Geo& g, int64_t nsteps, int limit) {
+    constexpr int kShort = 5, kTall = 20, kTallest = 36;
+    TilePlan p{false, pass_form(2, g)};
+    const int rows = limit > 1 && nsteps > 1 ? tile_rows(g) : 0;
+    if (rows == 0) return p;
+    const int log2 = __builtin_ctz((unsigned)limit);
+    const int64_t passes = (nsteps + limit - 1) >> log2;
+    const int64_t march = (nsteps >> log2) + __builtin_popcount((unsigned)(nsteps & (limit - 1)));
+    p.tiles = rows < kTall || passes * 4 < nsteps || passes < march;
+    if (rows >= kShort && rows < kTallest && (!p.tiles || (passes >= 3 && passes <= 5)))
+        p.form = FORM_TWIN;
+    return p;
+}
+
 // Tile shape of a launch: rows per wave, waves and blocks.
 struct TileShape {
     int R, waves, nstrips;

@@ -76,6 +76,13 @@ int compute_units();  // of the current device
 // nsteps (1..8) D2Q9 steps in one pass of workgroup tiles held in registers, on
 // grids with tile_rows(g) > 0; bitwise equal too.
 int tile_rows(const Geo& g);
+// How a run of nsteps D2Q9 steps in passes of up to `limit` (1, 2, 4 or 8) goes: by
+// tiles or by the march, and the form between two passes.
+struct TilePlan {
+    bool tiles;
+    int form;
+};
+TilePlan tile_plan(const Geo& g, int64_t nsteps, int limit);
 hipError_t launch_tile(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
                        hipStream_t st, int in, int out);
 // The same passes keeping every intermediate state: step j of the pass

@@ -10,8 +10,8 @@ sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 from host_runtime import run
 
 
-@pytest.mark.parametrize("grid,after", [((2048, 2048), 2), ((320, 320), 2), ((256, 256, 256), 2),
-                                        ((320, 320), 1), ((64, 64, 64, 64), 2)])
+@pytest.mark.parametrize("grid,after", [((2048, 2048), 2), ((700, 700), 2), ((256, 256, 256), 2),
+                                        ((700, 700), 1), ((64, 64, 64, 64), 2)])
 def test_failed_launch_between_passes_leaves_no_state(grid, after):
     """A launch that fails after others of the same call: the buffer may then hold the
     reduced form that only the next pass reads, so every call that needs a state is
@@ -132,3 +132,47 @@ for grid in ((64, 64, 64), (1, 1, 65535)):
 ''')
     assert t[0][1] == t[1][1] == 199
     assert t[1][0] < 5 * t[0][0], t
+
+
+def _run_kernels(grid, calls, limit=8):
+    """Kernels of lb_step(n) for each n of `calls`, from a state that an earlier call
+    left."""
+    return run(f'''
+h = solver({grid!r})
+L.lb_init(h, C, None)
+L.lb_set_option(h, L.LB_OPT_STEPS_PER_PASS, {limit})
+L.lb_step(h, 2)
+calls()
+out = []
+for n in {list(calls)!r}:
+    L.lb_step(h, n)
+    out.append([k.split("<")[0] + "<" + k.split("<")[1] for k in kernels()])
+''')
+
+
+FULL, TWIN, MOM = 0, 1, 2
+
+
+@pytest.mark.parametrize("grid,rows", [((512, 512), 23), ((700, 700), 42), ((100, 4000), 48)])
+def test_short_passes_of_tall_tiles_go_by_the_march(grid, rows):
+    two, three, four, eight = _run_kernels(grid, (2, 3, 4, 8))
+    assert [k.split("<")[0] for k in two + four] == ["k_steps_d2q9_half"] * 2 or \
+        all(k.startswith("k_steps_d2q9") for k in two + four) and len(two + four) == 2
+    assert len(three) == len(eight) == 1  # one tile pass, where the march takes two launches
+    assert three[0].startswith("k_tile_d2q9") and eight[0].startswith("k_tile_d2q9")
+    for calls, limit in (((9, 20, 40), 4), ((6, 20), 2)):
+        for run_kernels in _run_kernels(grid, calls, limit):
+            assert not [k for k in run_kernels if "tile" in k]
+
+
+@pytest.mark.parametrize("grid,steps,forms", [
+    ((512, 512), 17, [(TWIN, TWIN), (TWIN, TWIN), (TWIN, FULL)]),
+    ((256, 256), 40, [(TWIN, TWIN)] * 4 + [(TWIN, FULL)]),
+    ((512, 512), 16, [(TWIN, MOM), (MOM, FULL)]),
+    ((512, 512), 48, [(TWIN, MOM)] + [(MOM, MOM)] * 4 + [(MOM, FULL)]),
+    ((40, 40), 24, [(TWIN, MOM), (MOM, MOM), (MOM, FULL)]),
+    ((650, 650), 24, [(TWIN, MOM), (MOM, MOM), (MOM, FULL)])])
+def test_short_runs_of_tiles_take_two_kernels(grid, steps, forms):
+    (kernels,) = _run_kernels(grid, (steps,))
+    assert all(k.startswith("k_tile_d2q9<") for k in kernels)
+    assert [tuple(int(v) for v in k[12:-1].split(", ")[1:]) for k in kernels] == forms
