@@ -298,8 +298,9 @@ lb_status lb_adjoint_step(lb_solver* s, const double* state_n, const double* lam
  * on entry and dL/df^{n0} on return; lambda_tmp is a second state buffer
  * used as the ping-pong partner.  lambda on return is bitwise that of m
  * lb_adjoint_step calls.  On D2Q9 the reverse sweep runs in passes: where the
- * grid goes by register tiles, of up to LB_OPT_STEPS_PER_PASS adjoint steps
- * (fewer where a tile of that many does not fit), else of up to
+ * grid goes by register tiles and these take less, of up to
+ * LB_OPT_STEPS_PER_PASS adjoint steps (fewer where a tile of that many does not
+ * fit), else of up to
  * min(4, LB_OPT_STEPS_PER_PASS) (the forward passes' one-wave march with every
  * velocity reversed); the eps parts are summed in a fixed order, so *g_eps is
  * deterministic but rounded differently from the single calls.  Other lattices take one adjoint step per launch

@@ -701,11 +701,11 @@ static SegmentPlan march_plan(const lb_solver* s, int64_t m) {
     return p;
 }
 
-// `march` is march_plan(s, m).  Where the grid goes by tiles, all m steps go in the
+// `march` is march_plan(s, m).  Where the segment goes by tiles, all m steps go in the
 // fewest tile passes, of equal lengths, unless their tables would not fit the fixed
 // scratch array and the march's do: the two entry points then choose alike.
 static SegmentPlan segment_plan(const lb_solver* s, int64_t m, const SegmentPlan& march) {
-    const int most = s->d == 2 ? lbm::tile_adjoint_steps(s->g, s->steps_per_pass) : 0;
+    const int most = s->d == 2 ? lbm::tile_adjoint_steps(s->g, s->steps_per_pass, m) : 0;
     if (most == 0) return march;
     SegmentPlan p;
     p.tiles = true;
@@ -732,6 +732,9 @@ static lb_status run_segment(lb_solver* s, const SegmentPlan& plan, const double
     // any state and is read whole.
     const double* prev = ckpt;
     int64_t j = 1;  // next state to produce
+    // the reverse step after it goes through the checkpoint, the state and two lambdas
+    // (cached stores of the state then, m = 2: 1024^2 107 us, non-temporal 100)
+    constexpr int kTouched = 4;
     if (plan.tiles) {
         const int64_t passes = (m - 1 + s->steps_per_pass - 1) / s->steps_per_pass;
         for (int64_t k = 0; k < passes; ++k) {
@@ -756,7 +759,8 @@ static lb_status run_segment(lb_solver* s, const SegmentPlan& plan, const double
     }
     for (; j < m; ++j) {
         double* nxt = work + (j - 1) * se;
-        LB_HIP(lbm::launch_step(s->d, s->g, s->r, prev, nxt, s->stream, prev != ckpt, true),
+        LB_HIP(lbm::launch_step(s->d, s->g, s->r, prev, nxt, s->stream, prev != ckpt, true,
+                                kTouched),
                "step launch");
         prev = nxt;
     }

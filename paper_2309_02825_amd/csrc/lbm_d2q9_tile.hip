@@ -513,16 +513,27 @@ hipError_t launch_tile_all(int nsteps, const Geo& g, const Rates& r, const doubl
     });
 }
 
-// Wherever the grid goes by tiles and TILE_ADJOINT_ROWS rows a wave hold at least two
-// steps: us a step of forward and backward, march and tiles of up to 8 steps: 40^2
-// 6.60 and 4.04, 256^2 8.15 and 5.92, 512^2 15.85 and 12.75, 600^2 19.8 and 16.0; at
-// 700^2, where three steps fit, 27.5 and 24.8.
-int tile_adjoint_steps(const Geo& g, int limit) {
+// Tiles where TILE_ADJOINT_ROWS rows a wave hold five steps (us a step of forward and
+// backward, march and tiles of up to 8 steps: 40^2 6.60 and 4.04, 256^2 8.15 and 5.92,
+// 512^2 15.85 and 12.75, 600^2 19.8 and 16.0). Otherwise the march, in us a segment of m
+// steps, march and tiles:
+// - one or two steps, and three on short tiles, which take no more launches by single
+//   steps (m = 2: 320^2 20.6 and 24.1, 512^2 32.8 and 36.0; m = 3: 256^2 20.1 and 21.3,
+//   but 700^2 66.6 and 60.8);
+// - passes of two steps, unless the tiles are short (limit 2, m = 45: 400^2, 15 rows, 435
+//   and 493; 256^2, 7 rows, 314 and 275; no limit, 720^2, where two steps fit, 803 and 995);
+// - long segments of passes of three or four steps on rows of whole 64-byte lines, which
+//   the march's strips start on (m = 45: 2000 x 250 780 and 826, 4000 x 120 729 and 752,
+//   but 710^2 960 and 864; m = 17: 318 and 305, 297 and 289).
+int tile_adjoint_steps(const Geo& g, int limit, int64_t m) {
+    constexpr int kShort = 12, kThree = 15, kLong = 20;
     const int rows = tile_rows(g);
-    if (rows == 0) return 0;
-    int most = limit < MAX_STEPS_PER_PASS ? limit : MAX_STEPS_PER_PASS;
-    while (most > 1 && tile_shape(g, rows, most).R > TILE_ADJOINT_ROWS) --most;
-    return most > 1 ? most : 0;
+    if (rows == 0 || m < (rows < kThree ? 4 : 3)) return 0;
+    int fit = MAX_STEPS_PER_PASS;
+    while (fit > 1 && tile_shape(g, rows, fit).R > TILE_ADJOINT_ROWS) --fit;
+    const int most = std::min(limit, fit);
+    if (most < 3) return most == 2 && rows < kShort ? 2 : 0;
+    return fit >= 5 || g.nx % 8 != 0 || m <= kLong ? most : 0;
 }
 
 int64_t tile_adjoint_table(const Geo& g) {

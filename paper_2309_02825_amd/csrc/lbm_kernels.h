@@ -36,12 +36,13 @@ struct Geo {
     int64_t V;          // nx * ny * nz * nw
 };
 
-// Whether both state buffers fit in the 256 MB Infinity Cache: the next launch then
-// finds what a launch stored through the caches there; otherwise non-temporal stores
-// are faster.
+// Whether the `states` state-sized buffers that a launch and the next one touch (the
+// two of a solver) fit in the 256 MB Infinity Cache: the next launch then finds what a
+// launch stored through the caches there; otherwise non-temporal stores are faster.
 constexpr uint64_t kInfinityCacheBytes = 256ull << 20;
-inline bool states_fit_cache(int d, const Geo& g) {
-    return 2ull * (1 + 2 * d * d) * (uint64_t)chunks_of(g.V) * CHUNK * sizeof(double) <=
+inline bool states_fit_cache(int d, const Geo& g, int states = 2) {
+    return (uint64_t)states * (1 + 2 * d * d) * (uint64_t)chunks_of(g.V) * CHUNK *
+               sizeof(double) <=
            kInfinityCacheBytes;
 }
 
@@ -55,9 +56,10 @@ Launch launch_shape(int d, const Geo& g);
 // rin: src was written by a collision, so each twin population (twin<D>,
 // lbm_lattice.h) is read from the plane of the one it equals; wout: twins
 // are not stored, and dst may then only be read with rin.  Neither changes
-// the result.  The defaults read and write every population.
+// the result.  The defaults read and write every population.  states: as for
+// states_fit_cache.
 hipError_t launch_step(int d, const Geo& g, const Rates& r, const double* src, double* dst,
-                       hipStream_t st, bool rin = false, bool wout = false);
+                       hipStream_t st, bool rin = false, bool wout = false, int states = 2);
 // nsteps (2, 4 or 8) D2Q9 steps in one pass over HBM (temporal blocking);
 // bitwise equal to nsteps launch_step calls.  A block of MS_THREADS threads
 // (one wave) produces a strip of strip_width(nsteps) columns.
@@ -98,8 +100,8 @@ hipError_t launch_tile_all(int nsteps, const Geo& g, const Rates& r, const doubl
 // with f^{N-j} at ftop - (j-1) stride (twins in their partners' planes) or, for
 // j = nsteps, whole at ckpt if that is not NULL; writes ntab eps partials, at least
 // tile_adjoint_table(g).  tile_adjoint_steps: the most steps of a pass within `limit`,
-// 0 where the grid does not go by tiles.
-int tile_adjoint_steps(const Geo& g, int limit);
+// 0 where a segment of m steps does not go by tiles.
+int tile_adjoint_steps(const Geo& g, int limit, int64_t m);
 int64_t tile_adjoint_table(const Geo& g);
 hipError_t launch_tile_adjoint(int nsteps, const Geo& g, const Rates& r, const double* lam_in,
                                double* lam_out, const double* ftop, int64_t stride,

@@ -564,11 +564,11 @@ Launch launch_shape(int d, const Geo& g) {
     })
 
 hipError_t launch_step(int d, const Geo& g, const Rates& r, const double* src, double* dst,
-                       hipStream_t st, bool rin, bool wout) {
+                       hipStream_t st, bool rin, bool wout, int states) {
     return dispatch(d, [&](auto dc) {
         constexpr int DD = decltype(dc)::value;
         const Launch L = launch_shape(DD, g);
-        const bool nt = !states_fit_cache(DD, g);
+        const bool nt = !states_fit_cache(DD, g, states);
         if constexpr (DD == 1) {  // D1Q3 has no twins
             return dispatch_io(nt, false, [&](auto n, auto) {
                 hipLaunchKernelGGL((k_step<1, false, false, decltype(n)::value>), L.grid, L.block,

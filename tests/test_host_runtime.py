@@ -176,3 +176,26 @@ def test_short_runs_of_tiles_take_two_kernels(grid, steps, forms):
     (kernels,) = _run_kernels(grid, (steps,))
     assert all(k.startswith("k_tile_d2q9<") for k in kernels)
     assert [tuple(int(v) for v in k[12:-1].split(", ")[1:]) for k in kernels] == forms
+
+
+@pytest.mark.parametrize("grid,limit,m,tiles", [
+    ((512, 512), 8, 1, False), ((512, 512), 8, 2, False), ((512, 512), 8, 3, True),
+    ((256, 256), 8, 3, False), ((256, 256), 8, 4, True), ((40, 40), 8, 45, True),
+    ((400, 400), 2, 45, False), ((256, 256), 2, 45, True), ((512, 512), 4, 45, True),
+    ((650, 650), 8, 45, True),  # tiles of five steps
+    ((2000, 250), 8, 45, False), ((2000, 250), 8, 17, True), ((705, 705), 8, 45, True),
+    ((720, 721), 8, 45, False), ((720, 721), 8, 4, False), ((1024, 1024), 8, 45, False)])
+def test_adjoint_segments_by_tiles_where_they_pay(grid, limit, m, tiles):
+    """And the fixed-array form of the call goes the same way."""
+    one, other = run(f'''
+h = solver({grid!r})
+L.lb_set_option(h, L.LB_OPT_STEPS_PER_PASS, {limit})
+out = []
+for f in (L.lb_adjoint_segment, L.lb_adjoint_segment_static):
+    calls()
+    f(h, A, {m}, B, C, D, A)
+    out.append(kernels())
+''')
+    assert one == other
+    assert any(k.startswith("k_tile_adjoint") for k in one) == tiles
+    assert any(k.startswith("k_adjoint_step") for k in one) != tiles
