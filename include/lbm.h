@@ -182,7 +182,7 @@ lb_status lb_step(lb_solver* s, int64_t nsteps);
  * (left end, right end) at t + dt, t + 2 dt, ..., t + nsteps dt, where t is
  * the current time; the last pair is kept as the boundary theta of the new
  * current time (used by lb_macro and lb_get_state).  Grids of up to 2048
- * nodes run all steps in one launch with the state in LDS.  LB_ERR_STATE on a
+ * nodes run all steps in one launch with the state in registers.  LB_ERR_STATE on a
  * periodic solver or before lb_init / lb_set_state. */
 lb_status lb_step_bounded(lb_solver* s, int64_t nsteps, const double* walls);
 

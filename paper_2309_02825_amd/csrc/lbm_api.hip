@@ -501,7 +501,12 @@ lb_status lb_step_bounded(lb_solver* s, int64_t nsteps, const double* walls) {
     if (!s->inited) return fail(LB_ERR_STATE, "lb_step_bounded before lb_init/lb_set_state");
     if (nsteps == 0) return LB_OK;
     if (!walls) return fail(LB_ERR_INVALID_ARG, "walls is NULL");
-    if (s->g.nx <= lbm::RESIDENT_MAX_1D) {
+    if (nsteps == 1) {  // a block for 256 nodes (2048 nodes: 4.0 us, the one of k_run1 6.0)
+        LB_HIP(lbm::launch_step_wall1(s->g, s->r, s->buf[s->cur], s->buf[1 - s->cur],
+                                      s->wall_now, s->wall_now, walls, s->stream),
+               "step launch");
+        s->cur ^= 1;
+    } else if (s->g.nx <= lbm::RESIDENT_MAX_1D) {
         const int dst = s->cur ^ (int)(nsteps & 1);
         LB_HIP(lbm::launch_step_resident1(s->g, s->r, s->buf[s->cur], s->buf[dst], nsteps, walls,
                                           s->wall_now, s->stream),
@@ -511,7 +516,7 @@ lb_status lb_step_bounded(lb_solver* s, int64_t nsteps, const double* walls) {
         for (int64_t n = 0; n < nsteps; ++n) {
             const double* wall = n == 0 ? s->wall_now : walls + 2 * (n - 1);
             LB_HIP(lbm::launch_step_wall1(s->g, s->r, s->buf[s->cur], s->buf[1 - s->cur], wall,
-                                          s->stream),
+                                          nullptr, nullptr, s->stream),
                    "step launch");
             s->cur ^= 1;
         }

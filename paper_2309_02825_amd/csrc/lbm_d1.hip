@@ -16,7 +16,7 @@ namespace {
 // x = n-1.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void wall_pull1(const double* __restrict__ src, int x, int n,
-                                           const double* __restrict__ wall, double (&f)[3]) {
+                                           const double* wall, double (&f)[3]) {
     f[0] = src[slot<3>(0, x)];
     f[1] = x > 0 ? src[slot<3>(1, x - 1)] : 0.0;
     f[2] = x < n - 1 ? src[slot<3>(2, x + 1)] : 0.0;
@@ -24,13 +24,18 @@ __device__ __forceinline__ void wall_pull1(const double* __restrict__ src, int x
     if (x == n - 1) f[2] = wall[1] - (f[0] + f[1]);
 }
 
+// next != NULL: the boundary theta after the step, which wall (the solver's, only read
+// by the end nodes' threads) takes.
 __global__ void __launch_bounds__(256) k_step_wall1(const double* __restrict__ src,
                                                     double* __restrict__ dst, int n, Rates r,
-                                                    const double* __restrict__ wall) {
+                                                    const double* wall, double* wall_now,
+                                                    const double* next) {
     const int x = (int)(blockIdx.x * blockDim.x + threadIdx.x);
     if (x >= n) return;
     double f[3];
     wall_pull1(src, x, n, wall, f);
+    if (next && x == 0) wall_now[0] = next[0];
+    if (next && x == n - 1) wall_now[1] = next[1];
     collide<1>(f, r);
 #pragma unroll
     for (int i = 0; i < 3; ++i) __builtin_nontemporal_store(f[i], dst + slot<3>(i, x));
@@ -347,9 +352,12 @@ hipError_t launch_step_resident1(const Geo& g, const Rates& r, const double* src
 static dim3 grid_1d(int n) { return dim3((unsigned)((n + 255) / 256)); }
 
 hipError_t launch_step_wall1(const Geo& g, const Rates& r, const double* src, double* dst,
-                             const double* wall, hipStream_t st) {
+                             const double* wall, double* wall_now, const double* next,
+                             hipStream_t st) {
     if (g.nx < 2 || g.ny != 1 || g.nz != 1 || g.nw != 1 || !wall) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_step_wall1, grid_1d(g.nx), dim3(256), 0, st, src, dst, g.nx, r, wall);
+    if (next && wall_now != wall) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_step_wall1, grid_1d(g.nx), dim3(256), 0, st, src, dst, g.nx, r, wall,
+                       wall_now, next);
     return hipGetLastError();
 }
 

@@ -151,9 +151,11 @@ hipError_t launch_step_resident1(const Geo& g, const Rates& r, const double* src
                                 int64_t nsteps, const double* walls, double* wall_now,
                                 hipStream_t st);
 // 1-D interval whose end nodes carry a given theta (2 doubles at wall: left,
-// right, of the time the step starts from); n >= 2.
+// right, of the time the step starts from); n >= 2.  next != NULL: wall_now (then the
+// same as wall) receives the two doubles at next.
 hipError_t launch_step_wall1(const Geo& g, const Rates& r, const double* src, double* dst,
-                             const double* wall, hipStream_t st);
+                             const double* wall, double* wall_now, const double* next,
+                             hipStream_t st);
 hipError_t launch_macro_wall1(const Geo& g, const Rates& r, const double* state, double* theta,
                               double* u, double* grad, const double* wall, hipStream_t st);
 hipError_t launch_get_state_wall1(const Geo& g, const double* state, double* dense,

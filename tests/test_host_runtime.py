@@ -199,3 +199,20 @@ for f in (L.lb_adjoint_segment, L.lb_adjoint_segment_static):
     assert one == other
     assert any(k.startswith("k_tile_adjoint") for k in one) == tiles
     assert any(k.startswith("k_adjoint_step") for k in one) != tiles
+
+
+@pytest.mark.parametrize("n", [2, 321, 2048, 3000])
+def test_single_bounded_steps_spread_over_blocks(n):
+    """One step of a bounded interval is one launch of a block per 256 nodes."""
+    one, two = run(f'''
+h = solver(({n},), 0.3, L.LB_FLAG_BOUNDED)
+L.lb_init(h, C, D)
+out = []
+for k in (1, 2):
+    rt.host_log_clear()
+    L.lb_step_bounded(h, k, C)
+    out.append([l for l in rt.host_log().decode().split("\\n") if l])
+''')
+    assert len(one) == 1 and "k_step_wall1" in one[0]
+    assert int(one[0].split()[2]) == (n + 255) // 256
+    assert ("k_run1" in two[0]) == (n <= 2048)
