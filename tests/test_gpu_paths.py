@@ -226,3 +226,97 @@ def test_d2q9_two_wave_marches_equal_single_steps(grid):
     assert torch.equal(s.get_state(), ref.get_state()), grid
     s.close()
     ref.close()
+
+
+sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
+from plan_grids import CACHED_2D, FLAT_3D
+
+
+class _Single:
+    """lb_step_buffers single steps, which read and write every population."""
+
+    def __init__(self, grid, eps):
+        self.s, self.cur = _solver(grid, eps), 0
+
+    def step(self, n):
+        for _ in range(n):
+            self.s.step_buffers(self.s.bufs[self.cur], self.s.bufs[1 - self.cur])
+            self.cur ^= 1
+
+    def state(self):
+        if self.cur:  # lb_get_state reads the buffer of lb_init
+            self.s.bufs[0].copy_(self.s.bufs[1])
+            self.cur = 0
+        return self.s.get_state()
+
+
+@pytest.mark.parametrize("grid", CACHED_2D)
+@pytest.mark.parametrize("limit", [2, 4, 8])
+def test_d2q9_cached_marches_equal_single_steps(grid, limit):
+    """Full-round marches whose states stay in the Infinity Cache: first, middle and last
+    passes and the one before a single step, from the initial state and from the states
+    that calls leave, bit for bit."""
+    _say("D2Q9 cached march", grid, limit)
+    s, ref = _solver(grid, 0.31), _Single(grid, 0.31)
+    s.set_steps_per_pass(limit)
+    th0 = _rough(grid, 10)
+    s.init(th0, None)
+    ref.s.init(th0, None)
+    for n in (3 * limit + 1, limit, 4 * limit):
+        s.step(n)
+        ref.step(n)
+        assert torch.equal(s.get_state(), ref.state()), (grid, limit, n)
+    s.close()
+    ref.s.close()
+
+
+@pytest.mark.parametrize("grid", FLAT_3D)
+def test_d3q19_passes_of_flat_grids_equal_single_steps(grid):
+    """Passes where a tile's halo wraps around an axis more than once, through lb_init,
+    lb_set_state and checks in the middle of a run, bit for bit."""
+    _say("D3Q19 flat grid", grid)
+    s, ref = _solver(grid, 0.11), _Single(grid, 0.11)
+    th0 = _rough(grid, 11)
+    s.init(th0, None)
+    ref.s.init(th0, None)
+    for n in (6, 7, 2):
+        s.step(n)
+        ref.step(n)
+        assert torch.equal(s.get_state(), ref.state()), (grid, n)
+    f = ref.state()
+    s.set_state(f, 0)
+    s.set_check_interval(4)
+    for n in (9, 8):  # checks after 4 and 8 steps: complete states between passes
+        s.step(n)
+        ref.step(n)
+        assert torch.equal(s.get_state(), ref.state()), (grid, n)
+    s.close()
+    ref.s.close()
+
+
+@pytest.mark.parametrize("shift_a,shift_b", [(1, 0), (0, 1), (1, 1)])
+def test_d2q9_march_of_buffers_off_16_bytes(shift_a, shift_b):
+    """State buffers that start on 8 bytes only (the two-wave march moves 16) go by the
+    one-wave march, bit for bit."""
+    from paper_2309_02825_amd import lbm as L
+    grid = (2048, 2048)
+    _say("D2Q9 unaligned buffers", grid, shift_a, shift_b)
+    dx, nu = 1.0 / 2048, 0.02
+    cfg = L.make_config(grid, dx, 0.31 * dx * dx / nu, nu)
+    n = L.lb_state_elements(cfg)
+    bufs = [torch.zeros(n + 1, dtype=torch.float64, device=_dev())[k:k + n]
+            for k in (shift_a, shift_b)]
+    assert [b.data_ptr() % 16 for b in bufs] == [8 * shift_a, 8 * shift_b]
+    h = L.lb_create(cfg, torch.cuda.current_stream().cuda_stream, *bufs)
+    ref = _Single(grid, 0.31)
+    th0 = _rough(grid, 12)
+    L.lb_init(h, th0, None)
+    ref.s.init(th0, None)
+    L.lb_step(h, 32)
+    ref.step(32)
+    got = torch.empty((9, 2048, 2048), dtype=torch.float64, device=_dev())
+    L.lb_get_state(h, got)
+    assert torch.equal(got, ref.state())
+    torch.cuda.synchronize()
+    L.lb_destroy(h)
+    ref.s.close()

@@ -216,3 +216,44 @@ for k in (1, 2):
     assert len(one) == 1 and "k_step_wall1" in one[0]
     assert int(one[0].split()[2]) == (n + 255) // 256
     assert ("k_run1" in two[0]) == (n <= 2048)
+
+
+# Grids of test_gpu_paths.py that the plan has to send to the kernels that their tests
+# are there for: comparisons of single steps with single steps cannot fail.
+from plan_grids import CACHED_2D, CACHED_2D_HALF, FLAT_3D
+
+
+@pytest.mark.parametrize("grid", CACHED_2D)
+@pytest.mark.parametrize("limit", [2, 4, 8])
+def test_grids_of_the_cached_marches(grid, limit):
+    (kernels,) = _run_kernels(grid, (3 * limit + 1,), limit)
+    if (grid, limit) in CACHED_2D_HALF:
+        assert [k.split("<")[0] for k in kernels[:3]] == ["k_steps_d2q9_half"] * 3
+    else:
+        assert kernels[:3] == [f"k_steps_d2q9_seam<{limit}, false, {TWIN}, {MOM}>",
+                               f"k_steps_d2q9_cached<{limit}, true, true, true>",
+                               f"k_steps_d2q9_seam<{limit}, false, {MOM}, {TWIN}>"]
+    assert kernels[3:] == ["k_step<2, true, false, false>"]
+
+
+@pytest.mark.parametrize("grid", FLAT_3D)
+def test_grids_of_the_flat_d3q19_passes(grid):
+    (kernels,) = _run_kernels(grid, (7,))
+    assert kernels[:3] == [f"k_steps_d3q19<2, {TWIN}, {MOM}, true>", f"k_march_d3q19<{MOM}>",
+                           f"k_march_d3q19<{TWIN}>"]
+    assert [k.split("<")[0] for k in kernels[3:]] == ["k_step"]
+
+
+def test_two_wave_march_needs_aligned_buffers():
+    aligned, state_a, state_b, odd_rows = run('''
+out = []
+for a, b, grid in ((A, B, (2048, 2048)), (A + 8, B, (2048, 2048)), (A, B + 8, (2048, 2048)),
+                   (A, B, (2047, 2048))):
+    h = solver(grid, a=a, b=b)
+    L.lb_init(h, C, None)
+    calls()
+    L.lb_step(h, 24)
+    out.append(kernels()[1])
+''')
+    assert aligned == "k_steps_d2q9<8, true, true, true>"
+    assert state_a == state_b == odd_rows == f"k_steps_d2q9_seam<8, true, {MOM}, {MOM}>"
