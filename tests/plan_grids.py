@@ -8,4 +8,4 @@ CACHED_2D_HALF = [((13043, 123), 4)]
 
 # D3Q19 passes on grids with an axis shorter than a tile's halo
 FLAT_3D = [(600, 600, 1), (512, 512, 2), (301, 299, 3), (3, 300, 300), (1, 700, 200),
-           (300, 3, 300), (61, 1, 9000), (4, 4, 20000), (2, 1, 30000), (1, 1, 9000)]
+           (300, 3, 300), (60, 2, 9000), (4, 4, 20000), (2, 1, 30000), (1, 1, 9000)]
