@@ -111,7 +111,7 @@ __global__ void k_wall_from_dense1(const double* __restrict__ dense, int n, doub
 // started): every load of src happens before the first store to dst, so the
 // pointers carry no __restrict__.
 // ---------------------------------------------------------------------------
-constexpr int RUN1_MAX_WAVES = 4;  // one per SIMD: more never came out faster
+constexpr int RUN1_MAX_WAVES = 4;  // one per SIMD (run1_shape): more never came out faster
 
 __device__ __forceinline__ double lane_value(double x, int lane) {
     const long long b = __double_as_longlong(x);
@@ -271,7 +271,7 @@ k_run1(const double* src, double* dst, int n, int own, int halo, int64_t nsteps,
 }  // namespace
 
 // Shape of k_run1 for n nodes: nodes per lane, waves, nodes owned by a wave and
-// halo.  The cost of a step is modelled in cycles as the issue of a SIMD's waves
+// halo.  The cost of a step is modelled in cycles as the issue of a SIMD's one wave
 // (32 per node of a lane and 16 for the lane moves, at least kLatency, the
 // length of one step's dependent chain) plus a share of the exchange; the
 // constants only order the shapes (n = 321: 4 waves of 2 nodes a lane).
@@ -296,10 +296,9 @@ static Run1Shape run1_shape(int n, bool bounded) {
             if (halo > 64) halo = 64 / per * per;
             if (halo < per) continue;
             if ((int64_t)(waves - 1) * own >= n && waves > 1) continue;  // an idle wave
-            const int simd = (waves + 3) / 4;
-            const int issue = std::max(kLatency, simd * (32 * per + 16));
+            const int issue = std::max(kLatency, 32 * per + 16);
             const int64_t cost = (int64_t)issue * 1024 +
-                                 (int64_t)(kExchange + kExchangePer * per * simd) * 1024 / halo;
+                                 (int64_t)(kExchange + kExchangePer * per) * 1024 / halo;
             if (cost < best_cost) {
                 best_cost = cost;
                 best = Run1Shape{per, waves, own, halo};

@@ -47,7 +47,10 @@ __device__ __forceinline__ void mp_strip(const double* __restrict__ src, double*
 // beyond the Infinity Cache, us for 8 steps by one and two waves: 1600^2 65.8 and 65.5,
 // 2048^2 97.7 and 97.5, 2500^2 150 and 136, 6000^2 728 and 660, 8000 x 7000 1128 and
 // 1022; below, where a segment has few rows, its longer fill loses: 1000^2 28.6 and
-// 40.1, 1448^2 53.7 and 57.7.
+// 40.1, 1448^2 53.7 and 57.7.  Oblong grids just beyond it have segments of 18
+// to 22 rows (one wave and 7 planes, and two waves: 4096 x 512 60.8 and 58.5, 8192 x 256
+// 62.1 and 57.5, 3278 x 609 59.2 and 56.1, 16384 x 128 61.5 and 58.0); half a round
+// (pass_rows) is weighed against the one-wave march only.
 inline bool pair_fits(const Geo& g, const double* src, const double* dst) {
     return g.nx % 2 == 0 && ((uintptr_t)src | (uintptr_t)dst) % 16 == 0;
 }
@@ -87,9 +90,10 @@ k_steps_d2q9_half(const double* __restrict__ src, double* __restrict__ dst, Geo 
     ms_strip<S, true, NT, IN, OUT, 2>(src, dst, g, r, ly, nstrips);
 }
 
-// The one-wave passes that the kernels above leave, under 4 GiB: odd rows, and the first of a call on a state that an
-// earlier call left (its twins are equal, so 7 planes are read), and the one before
-// a single step, which reads populations.
+// The one-wave passes that the kernels above leave, under 4 GiB: odd rows, the first
+// of a call on a state that an earlier call left (its twins are equal, so 7 planes are
+// read), the one before a single step, which reads populations, and short runs
+// (tile_plan).
 template <int S, bool NT, int IN, int OUT>
 __global__ void __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(2)))
 k_steps_d2q9_seam(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rates r, int ly,
@@ -113,15 +117,19 @@ hipError_t launch_steps_t(const Geo& g, const Rates& r, const double* src, doubl
         return dispatch_form(out, [&](auto fo) {
             constexpr int IN = decltype(fi)::value, OUT = decltype(fo)::value;
             constexpr bool RI = IN != FORM_FULL, WO = OUT != FORM_FULL;
+            if constexpr (S == MAX_STEPS_PER_PASS) {  // pass_rows: no shorter ones
+                if (off32 && half && !cached) {
+                    hipLaunchKernelGGL((k_steps_d2q9_half<S, true, IN, OUT>), grid, block, 0, st,
+                                       src, dst, g, r, ly, nstrips);
+                    return hipGetLastError();
+                }
+            }
             if (!off32) {
                 if (IN == FORM_MOM || OUT == FORM_MOM) return hipErrorInvalidValue;  // pass_form
                 hipLaunchKernelGGL((k_steps_d2q9<S, false, RI, WO>), grid, block, 0, st, src, dst,
                                    g, r, ly, nstrips);
             } else if (half && cached) {
                 hipLaunchKernelGGL((k_steps_d2q9_half<S, false, IN, OUT>), grid, block, 0, st, src,
-                                   dst, g, r, ly, nstrips);
-            } else if (half && S == MAX_STEPS_PER_PASS) {
-                hipLaunchKernelGGL((k_steps_d2q9_half<MAX_STEPS_PER_PASS, true, IN, OUT>), grid, block, 0, st, src,
                                    dst, g, r, ly, nstrips);
             } else if (pair_pass(S, true, RI, WO) && IN == FORM_MOM && OUT == FORM_MOM && !cached &&
                        pair_fits(g, src, dst)) {

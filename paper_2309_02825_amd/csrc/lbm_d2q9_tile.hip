@@ -8,7 +8,7 @@ namespace lbm {
 namespace {
 
 // ---------------------------------------------------------------------------
-// S steps (1 <= S <= 8) of one tile.  The block's waves own R consecutive rows of
+// S steps (2 <= S <= 8) of one tile.  The block's waves own R consecutive rows of
 // 64 columns each, one above the other: rin = rows + 2S rows and 64 columns with
 // a halo of S on every side, of which the inner `rows` x (64 - 2S) are stored.
 // All rows advance together, one step at a time: x neighbours come from DPP lane
@@ -146,23 +146,19 @@ k_tile_d2q9(const double* __restrict__ src, double* __restrict__ dst, Geo g, Rat
     tile_publish<R, TWINS>(a, xch, wave);
     __syncthreads();
     constexpr bool MOM = OUT == FORM_MOM;
-    if (S == 1) {
-        if (needed(1)) tile_step<R, TWINS, MOM>(a, b, xch, wave, waves, fr);
-    } else {
-        if (needed(1)) {
-            tile_step<R, TWINS, false>(a, b, xch, wave, waves, fr);
-            tile_publish<R, true>(b, xch + half, wave);
-        }
-        for (int s = 2; s < S; ++s) {
-            __syncthreads();
-            if (needed(s)) {
-                tile_step<R, true, false>(b, b, xch + ((s & 1) ? 0 : half), wave, waves, fr);
-                tile_publish<R, true>(b, xch + ((s & 1) ? half : 0), wave);
-            }
-        }
-        __syncthreads();
-        if (needed(S)) tile_step<R, true, MOM>(b, b, xch + ((S & 1) ? 0 : half), wave, waves, fr);
+    if (needed(1)) {
+        tile_step<R, TWINS, false>(a, b, xch, wave, waves, fr);
+        tile_publish<R, true>(b, xch + half, wave);
     }
+    for (int s = 2; s < S; ++s) {
+        __syncthreads();
+        if (needed(s)) {
+            tile_step<R, true, false>(b, b, xch + ((s & 1) ? 0 : half), wave, waves, fr);
+            tile_publish<R, true>(b, xch + ((s & 1) ? half : 0), wave);
+        }
+    }
+    __syncthreads();
+    if (needed(S)) tile_step<R, true, MOM>(b, b, xch + ((S & 1) ? 0 : half), wave, waves, fr);
     const int x = x0 - S + lane;
     if (lane >= S && lane < 64 - S && x < g.nx) {
 #pragma unroll
@@ -458,7 +454,7 @@ static TileShape tile_shape(const Geo& g, int rows, int nsteps) {
 hipError_t launch_tile(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
                        hipStream_t st, int in, int out) {
     const int rows = tile_rows(g);
-    if (nsteps < 1 || nsteps > MAX_STEPS_PER_PASS || rows == 0) return hipErrorInvalidValue;
+    if (nsteps < 2 || nsteps > MAX_STEPS_PER_PASS || rows == 0) return hipErrorInvalidValue;
     const TileShape s = tile_shape(g, rows, nsteps);
     return dispatch_form(in, [&](auto fi) {
         return dispatch_form(out, [&](auto fo) {

@@ -75,7 +75,7 @@ hipError_t launch_steps(int nsteps, const Geo& g, const Rates& r, const double* 
 // states of 4 GiB and D3Q19 z-planes of 2 GiB and more, and for D4Q33).
 int pass_form(int d, const Geo& g);
 int compute_units();  // of the current device
-// nsteps (1..8) D2Q9 steps in one pass of workgroup tiles held in registers, on
+// nsteps (2..8) D2Q9 steps in one pass of workgroup tiles held in registers, on
 // grids with tile_rows(g) > 0; bitwise equal too.
 int tile_rows(const Geo& g);
 // How a run of nsteps D2Q9 steps in passes of up to `limit` (1, 2, 4 or 8) goes: by
