@@ -229,6 +229,8 @@ def test_grids_of_the_cached_marches(grid, limit):
     (kernels,) = _run_kernels(grid, (3 * limit + 1,), limit)
     if (grid, limit) in CACHED_2D_HALF:
         assert [k.split("<")[0] for k in kernels[:3]] == ["k_steps_d2q9_half"] * 3
+    elif grid[1] <= 16:  # tile_plan: the halo's rows outnumber the grid's
+        assert kernels[:3] == [f"k_steps_d2q9_seam<{limit}, false, {TWIN}, {TWIN}>"] * 3
     else:
         assert kernels[:3] == [f"k_steps_d2q9_seam<{limit}, false, {TWIN}, {MOM}>",
                                f"k_steps_d2q9_cached<{limit}, true, true, true>",
