@@ -193,7 +193,8 @@ struct lb_solver {
     int d, q;
     Geo g;
     Rates r;
-    lbm::Plan3 plan3;  // D3Q19
+    lbm::Plan3 plan3;     // D3Q19
+    lbm::Run1Shape run1;  // D1Q3, up to RESIDENT_MAX_1D nodes
     hipStream_t stream;
     double* buf[2];
     int cur;
@@ -285,6 +286,8 @@ lb_status lb_create(const lb_config* cfg, void* hip_stream, double* f_a, double*
     s->g = make_geo(cfg);
     s->r = make_rates(cfg->dim, cfg->dx, cfg->dt, cfg->nu);
     if (s->d == 3) s->plan3 = lbm::plan3(s->g);
+    if (s->d == 1 && s->g.nx <= lbm::RESIDENT_MAX_1D)
+        s->run1 = lbm::run1_shape(s->g.nx, (cfg->flags & LB_FLAG_BOUNDED) != 0);
     s->stream = (hipStream_t)hip_stream;
     s->buf[0] = f_a;
     s->buf[1] = f_b;
@@ -405,7 +408,7 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
         // ping-pong would have left it
         const int dst = s->cur ^ (int)(nsteps & 1);
         LB_HIP(lbm::launch_step_resident1(s->g, s->r, s->buf[s->cur], s->buf[dst], nsteps,
-                                          nullptr, nullptr, s->stream),
+                                          s->run1, nullptr, nullptr, s->stream),
                "resident step launch");
         s->cur = dst;
         s->steps += nsteps;
@@ -508,8 +511,8 @@ lb_status lb_step_bounded(lb_solver* s, int64_t nsteps, const double* walls) {
         s->cur ^= 1;
     } else if (s->g.nx <= lbm::RESIDENT_MAX_1D) {
         const int dst = s->cur ^ (int)(nsteps & 1);
-        LB_HIP(lbm::launch_step_resident1(s->g, s->r, s->buf[s->cur], s->buf[dst], nsteps, walls,
-                                          s->wall_now, s->stream),
+        LB_HIP(lbm::launch_step_resident1(s->g, s->r, s->buf[s->cur], s->buf[dst], nsteps,
+                                          s->run1, walls, s->wall_now, s->stream),
                "resident step launch");
         s->cur = dst;
     } else {

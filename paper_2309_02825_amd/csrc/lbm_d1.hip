@@ -275,10 +275,7 @@ k_run1(const double* src, double* dst, int n, int own, int halo, int64_t nsteps,
 // (32 per node of a lane and 16 for the lane moves, at least kLatency, the
 // length of one step's dependent chain) plus a share of the exchange; the
 // constants only order the shapes (n = 321: 4 waves of 2 nodes a lane).
-struct Run1Shape {
-    int per, waves, own, halo;
-};
-static Run1Shape run1_shape(int n, bool bounded) {
+Run1Shape run1_shape(int n, bool bounded) {
     constexpr int kPer[] = {1, 2, 3, 4, 6, 8, 10};
     constexpr int kLatency = 60, kExchange = 350, kExchangePer = 24;
     Run1Shape best{0, 0, 0, 0};
@@ -309,8 +306,8 @@ static Run1Shape run1_shape(int n, bool bounded) {
 }
 
 hipError_t launch_step_resident1(const Geo& g, const Rates& r, const double* src, double* dst,
-                                int64_t nsteps, const double* walls, double* wall_now,
-                                hipStream_t st) {
+                                int64_t nsteps, const Run1Shape& s, const double* walls,
+                                double* wall_now, hipStream_t st) {
     if (g.nx > RESIDENT_MAX_1D || g.ny != 1 || g.nz != 1 || g.nw != 1) return hipErrorInvalidValue;
     if (walls && (!wall_now || g.nx < 2)) return hipErrorInvalidValue;
     const int n = g.nx;
@@ -323,7 +320,6 @@ hipError_t launch_step_resident1(const Geo& g, const Rates& r, const double* src
                                nsteps, r, walls, wall_now);
         return hipGetLastError();
     }
-    const Run1Shape s = run1_shape(n, walls != nullptr);
     const dim3 block(64 * s.waves);
     switch (s.per) {
 #define LBM_RUN1(PER)                                                                             \

@@ -145,11 +145,18 @@ hipError_t launch_march3(const Geo& g, const Rates& r, const double* src, double
 // 1-D grids up to this many nodes run all their steps in one launch, the state in
 // registers (halos through 3 populations x 8 B x 2048 = 48 KiB of LDS).
 constexpr int RESIDENT_MAX_1D = 2048;
+// Shape of such a launch: nodes per lane, waves, nodes owned by a wave and halo; worked
+// out once per solver (0.2 us of host time).
+struct Run1Shape {
+    int per = 0, waves = 0, own = 0, halo = 0;
+};
+Run1Shape run1_shape(int n, bool bounded);
+// s = run1_shape(g.nx, walls != NULL).
 // walls != NULL: bounded interval (see launch_step_wall1); wall_now holds the
 // boundary theta of the current time and receives the last pair of walls.
 hipError_t launch_step_resident1(const Geo& g, const Rates& r, const double* src, double* dst,
-                                int64_t nsteps, const double* walls, double* wall_now,
-                                hipStream_t st);
+                                int64_t nsteps, const Run1Shape& s, const double* walls,
+                                double* wall_now, hipStream_t st);
 // 1-D interval whose end nodes carry a given theta (2 doubles at wall: left,
 // right, of the time the step starts from); n >= 2.  next != NULL: wall_now (then the
 // same as wall) receives the two doubles at next.

@@ -44,7 +44,11 @@ void host_fail_launch(long n) { g_fail = n; }
 /* kernels by the address of their host stub */
 #define MAX_KERNELS 4096
 static struct { const void* stub; char name[240]; } g_kernels[MAX_KERNELS];
-static int g_nkernels;
+static unsigned slot_of(const void* stub) {
+    unsigned i = (unsigned)((size_t)stub >> 4) % MAX_KERNELS;
+    while (g_kernels[i].stub && g_kernels[i].stub != stub) i = (i + 1) % MAX_KERNELS;
+    return i;
+}
 void** __hipRegisterFatBinary(const void* data) {
     static void* handle;
     (void)data;
@@ -54,10 +58,9 @@ void __hipUnregisterFatBinary(void** m) { (void)m; }
 void __hipRegisterFunction(void** m, const void* stub, char* dev, const char* name, unsigned limit,
                            void* tid, void* bid, void* bdim, void* gdim, int* wsize) {
     (void)m, (void)dev, (void)limit, (void)tid, (void)bid, (void)bdim, (void)gdim, (void)wsize;
-    if (g_nkernels < MAX_KERNELS) {
-        g_kernels[g_nkernels].stub = stub;
-        snprintf(g_kernels[g_nkernels++].name, sizeof g_kernels[0].name, "%s", name);
-    }
+    const unsigned i = slot_of(stub);
+    g_kernels[i].stub = stub;
+    snprintf(g_kernels[i].name, sizeof g_kernels[i].name, "%s", name);
 }
 void __hipRegisterVar(void** m, void* var, char* host, char* name, int ext, size_t size, int c,
                       int global) {
@@ -77,10 +80,7 @@ hipError_t hipLaunchKernel(const void* stub, dim3_t grid, dim3_t block, void** a
                            void* stream) {
     (void)args, (void)stream;
     if (g_fail >= 0 && g_fail-- == 0) return g_last = 719;
-    const char* name = "?";
-    for (int i = 0; i < g_nkernels; ++i)
-        if (g_kernels[i].stub == stub) name = g_kernels[i].name;
-    put("launch %s %u %u %zu", name, grid.x * grid.y * grid.z, block.x * block.y * block.z, lds);
+    put("launch %s %u %u %zu", g_kernels[slot_of(stub)].name, grid.x * grid.y * grid.z, block.x * block.y * block.z, lds);
     return 0;
 }
 hipError_t hipGetLastError(void) {
