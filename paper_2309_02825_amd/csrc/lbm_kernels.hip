@@ -593,7 +593,10 @@ hipError_t launch_init(int d, const Geo& g, const Rates& r, const double* theta0
     return dispatch(d, [&](auto dc) {
         constexpr int DD = decltype(dc)::value;
         const Launch L = launch_shape(DD, g);
-        return dispatch_io(grad != nullptr, !states_fit_cache(DD, g), [&](auto gr, auto nt) {
+        // one state: the next call reads it, also where two do not fit (us, init to fields
+        // around eight steps, non-temporal and cached: 1400 x 1350 157 and 145, 118^3, 250 MB,
+        // 522 and 499; 2048^2, 302 MB, 323 and 322, without steps 192 and 200)
+        return dispatch_io(grad != nullptr, !states_fit_cache(DD, g, 1), [&](auto gr, auto nt) {
             hipLaunchKernelGGL((k_init<DD, decltype(gr)::value, decltype(nt)::value>), L.grid,
                                L.block, 0, st, theta0, grad, dst, g, r);
             return hipGetLastError();

@@ -259,3 +259,17 @@ for a, b, grid in ((A, B, (2048, 2048)), (A + 8, B, (2048, 2048)), (A, B + 8, (2
 ''')
     assert aligned == "k_steps_d2q9<8, true, true, true>"
     assert state_a == state_b == odd_rows == f"k_steps_d2q9_seam<8, true, {MOM}, {MOM}>"
+
+
+@pytest.mark.parametrize("grid,cached", [((1448, 1448), True), ((1600, 1600), True),
+                                         ((2177, 1573), True), ((2048, 2048), False),
+                                         ((118, 118, 118), True), ((128, 128, 128), False),
+                                         ((28, 28, 28, 28), True), ((9000000,), True)])
+def test_initial_state_stays_in_the_cache_where_it_fits(grid, cached):
+    (kernel,) = run(f'''
+h = solver({grid!r})
+calls()
+L.lb_init(h, C, D)
+out = kernels()
+''')
+    assert kernel == f"k_init<{len(grid)}, true, {'false' if cached else 'true'}>"
