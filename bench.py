@@ -84,17 +84,49 @@ def log(*a):
 
 
 def d2_kernel(steps: int, nodes: int) -> str:
-    """Name of the D2Q9 pass kernel: the variant with cached stores runs when both
+    """Name of the D2Q9 pass kernel of a full round: the variant with cached stores runs when both
     state buffers fit in the 256 MB Infinity Cache, the one with 32-bit offsets
     when a state buffer is under 4 GiB.  The launches between the first and the
     last of an lb_step call read and write only the values that determine a node
-    (the last two template arguments).  Mid-size grids run the same march with one
-    wave per SIMD, which the trace shows as k_steps_d2q9_half."""
+    (the last two template arguments)."""
     state_bytes = 9 * ((nodes + 4095) // 4096) * 4096 * 8
     if 2 * state_bytes <= 256 << 20:
         return f"k_steps_d2q9_cached<{steps}, true, true, true>"
     return (f"k_steps_d2q9<{steps}, {'true' if state_bytes <= 0xFFFFFFFF else 'false'}, "
             "true, true>")
+
+
+CUS = 256  # compute units of an MI355X
+
+
+def d2_pass_kernel(steps: int, grid, cus: int = CUS) -> str:
+    """Name of the kernel that the D2Q9 passes of `steps` steps between the first and the
+    last of a long lb_step call run, on a grid that goes by marches: half a round where the
+    library's pass_rows takes it, otherwise a full one (odd rows without the two-wave
+    march)."""
+    nx, ny = grid
+    full = d2_kernel(steps, nx * ny)
+    if ", false, true, true>" in full:
+        return full  # 64-bit offsets: full rounds only
+    cached = "cached" in full
+    strips = -(-nx // (64 - 2 * steps))
+
+    def rows(slots):
+        per_round = max(1, slots // strips)
+        nseg = per_round
+        while -(-ny // nseg) > 512:
+            nseg += per_round
+        return min(max(-(-ny // nseg), 8), ny)
+
+    two = rows(8 * cus)
+    nseg = max(1, 4 * cus // strips)
+    one = min(ny, -(-ny // nseg))
+    if (one > two and nseg * strips <= 4 * cus and 0.83 * (one + steps) < 1.47 * (two + steps)
+            and (steps == D2_STEPS_PER_PASS or cached)):
+        return f"k_steps_d2q9_half<{steps}, {'false' if cached else 'true'}, 2, 2>"
+    if steps == D2_STEPS_PER_PASS and not cached and nx % 2:
+        return f"k_steps_d2q9_seam<{steps}, true, 2, 2>"
+    return full
 
 
 def kernel_source_hash() -> str:
@@ -245,8 +277,8 @@ def form_heat1d(torch, SV, W, dev):
 
 def form_example1(torch, SV, W, dev):
     """Example 1 (1-D interval, theta prescribed at the end nodes), eps = 0.5,
-    levels 0-3 to t = 2: time per solve (init, all steps in one LDS-resident
-    launch, macro) and the RMSEs against the exact solution beside Table 1's
+    levels 0-3 to t = 2: time per solve (init, all steps in one launch with the
+    state in registers, macro) and the RMSEs against the exact solution beside Table 1's
     printed values (level 0: 7.8613e-4 / 1.9827e-5)."""
     import numpy as np
     printed = {0: (7.8613e-4, 1.9827e-5), 1: (4.8926e-5, 1.1821e-6),
@@ -335,19 +367,24 @@ def form_batched(torch, SV, W, dev):
             "lu_equivalent_gbs": round(mlups * 144 / 1e3, 1)}
 
 
-def d2_tile_adjoint_steps(grid, cus: int, spp: int = D2_STEPS_PER_PASS) -> int:
-    """Adjoint steps of a register-tile pass on this grid, 0 where the segment goes by
-    the march (tile_rows and tile_adjoint_steps of lbm_d2q9_tile.hip)."""
+def d2_tile_adjoint_steps(grid, m: int, cus: int = CUS, spp: int = D2_STEPS_PER_PASS) -> int:
+    """The most adjoint steps of a register-tile pass of a segment of m steps, 0 where it
+    goes by the march: tile_rows and tile_adjoint_steps of the library."""
     strips = -(-grid[0] // 48)
     if strips > cus:
         return 0
     rows = max(2, -(-grid[1] // (cus // strips)))
-    steps = min(spp, (6 * 8 - rows) // 2)
-    return steps if rows <= 48 and steps > 1 else 0
+    if rows > 48 or m < (4 if rows < 15 else 3):
+        return 0
+    fit = max(1, min(D2_STEPS_PER_PASS, (6 * 8 - rows) // 2))
+    most = min(spp, fit)
+    if most < 3:
+        return 2 if most == 2 and rows < 12 else 0
+    return most if fit >= 5 or grid[0] % 8 != 0 or m <= 20 else 0
 
 
 def adjoint_backward_bytes(V: int, starts, nsteps: int, spp: int = D2_STEPS_PER_PASS,
-                           max_reverse: int = 4, tile_steps: int = 0) -> int:
+                           max_reverse: int = 4, tile_steps=lambda m: 0) -> int:
     """Algorithmic HBM bytes of the D2Q9 backward sweep, following the launch
     plan of lb_adjoint_segment.  A checkpoint and lambda are complete (9
     populations, 72 B per node); the recomputed states are post-collision
@@ -356,8 +393,8 @@ def adjoint_backward_bytes(V: int, starts, nsteps: int, spp: int = D2_STEPS_PER_
     of a segment) and writes all S states; a reverse pass of S steps reads
     and writes lambda once and reads the S states it needs; single steps read
     one state and write one, single adjoint steps read one state and lambda
-    and write lambda.  With tile_steps > 0 the segment goes by register tiles:
-    passes of equal lengths of up to spp recomputed and tile_steps adjoint steps,
+    and write lambda.  Where tile_steps(m) > 0 the segment goes by register tiles:
+    passes of equal lengths of up to spp recomputed and tile_steps(m) adjoint steps,
     the last reverse pass with the checkpoint.  The seed (lb_macro_adjoint:
     state and g_u read, lambda written) and the adjoint of the initialisation
     (lambda read, theta0 read, g_theta0 written) are included."""
@@ -366,10 +403,11 @@ def adjoint_backward_bytes(V: int, starts, nsteps: int, spp: int = D2_STEPS_PER_
     ends = list(starts[1:]) + [nsteps]
     for b, e in zip(starts, ends):
         m = e - b
-        if tile_steps > 0:
+        tile = tile_steps(m)
+        if tile > 0:
             passes = -(-(m - 1) // spp)
             total += (full + red * (passes - 1) if passes else 0) + red * (m - 1)
-            total += 2 * full * -(-m // tile_steps) + red * (m - 1) + full
+            total += 2 * full * -(-m // tile) + red * (m - 1) + full
             continue
         j = 1
         p = spp
@@ -445,7 +483,8 @@ def form_adjoint(torch, SV, W, dev, n: int = 512, lb_steps: int = 2000):
     starts = SV.checkpoint_segments(N)
     cus = torch.cuda.get_device_properties(dev).multi_processor_count
     bwd_bytes = adjoint_backward_bytes(V, starts, N,
-                                       tile_steps=d2_tile_adjoint_steps(gue.grid, cus))
+                                       tile_steps=lambda m: d2_tile_adjoint_steps(gue.grid, m,
+                                                                                  cus))
     bwd_gbs = bwd_bytes / t_b / 1e9
     counted = traffic_for(f"adjoint_{n}", N)
     return {"grid": list(gue.grid), "lb_steps": N, "checkpoints": len(starts),
@@ -576,7 +615,7 @@ def main():
     # a launch reads and writes the state once (2 q 8 bytes per node), which is
     # what the roofline fraction is taken against
     per_launch = {2: D2_STEPS_PER_PASS, 3: D3_STEPS_PER_PASS}.get(d, 1)
-    kernel = {2: d2_kernel(D2_STEPS_PER_PASS, V),
+    kernel = {2: d2_pass_kernel(D2_STEPS_PER_PASS, wl.grid) if d == 2 else None,
               3: "k_march_d3q19<2>"}.get(d, f"k_step<{d}, true, true>")
     pr = pass_roofline(d, V, per_launch, kms * 1e3)
     launch_us = pr["kernel_us_per_launch"]
@@ -635,7 +674,7 @@ def main():
                 ms = kernel_only(torch, SV, W, wl, 400, dev, steps_per_pass=spp)
                 ml = V / (ms / 1e3) / 1e6
                 sweep[f"steps_per_pass_{spp}"] = {
-                    "kernel": "k_step<2, true, true>" if spp == 1 else d2_kernel(spp, V),
+                    "kernel": "k_step<2, true, true>" if spp == 1 else d2_pass_kernel(spp, wl.grid),
                     "kernel_us_per_step": round(ms * 1e3, 2), "mlups": round(ml, 1),
                     "lb_steps_timed": 400, **pass_roofline(2, V, spp, ms * 1e3)}
             forms[wl.name + "_steps_per_pass"] = sweep
@@ -650,7 +689,7 @@ def main():
             ml = w2.nodes / (ms / 1e3) / 1e6
             spl = {2: D2_STEPS_PER_PASS, 3: D3_STEPS_PER_PASS}.get(w2.d, 1)
             forms[name] = {"lattice": {2: "D2Q9", 3: "D3Q19", 4: "D4Q33"}[w2.d],
-                           "kernel": {2: d2_kernel(D2_STEPS_PER_PASS, w2.nodes),
+                           "kernel": {2: d2_pass_kernel(D2_STEPS_PER_PASS, w2.grid) if w2.d == 2 else None,
                                       3: "k_march_d3q19<2>"}.get(
                                           w2.d, f"k_step<{w2.d}, true, true>"),
                            "lb_steps_per_launch": spl,

@@ -43,13 +43,22 @@ out = None
 '''
 
 
-def run(code: str):
-    with tempfile.TemporaryDirectory() as tmp:
-        lib = os.path.join(tmp, "host_runtime.so")
-        subprocess.run(["gcc", "-O1", "-std=c11", "-Wall", "-shared", "-fPIC", "-o", lib,
+_tmp = None  # holds the built runtime while the tests run
+
+
+def _runtime() -> str:
+    global _tmp
+    if _tmp is None:
+        _tmp = tempfile.TemporaryDirectory()
+        subprocess.run(["gcc", "-O1", "-std=c11", "-Wall", "-shared", "-fPIC", "-o",
+                        os.path.join(_tmp.name, "host_runtime.so"),
                         os.path.join(HERE, "host_runtime.c")], check=True)
-        binding = os.path.join(ROOT, "paper_2309_02825_amd", "lbm.py")
-        src = _PRELUDE.format(runtime=lib, binding=binding) + code + "\nprint(json.dumps(out))\n"
-        r = subprocess.run([sys.executable, "-c", src], capture_output=True, text=True, timeout=120)
+    return os.path.join(_tmp.name, "host_runtime.so")
+
+
+def run(code: str):
+    binding = os.path.join(ROOT, "paper_2309_02825_amd", "lbm.py")
+    src = _PRELUDE.format(runtime=_runtime(), binding=binding) + code + "\nprint(json.dumps(out))\n"
+    r = subprocess.run([sys.executable, "-c", src], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
     return json.loads(r.stdout.strip().split("\n")[-1])

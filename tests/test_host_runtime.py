@@ -273,3 +273,44 @@ L.lb_init(h, C, D)
 out = kernels()
 ''')
     assert kernel == f"k_init<{len(grid)}, true, {'false' if cached else 'true'}>"
+
+
+sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+
+
+@pytest.mark.parametrize("grid", [(1024, 1024), (1280, 1280), (1448, 1448), (1600, 1600),
+                                  (4096, 4096), (4096, 512), (3001, 3001), (8192, 7400),
+                                  (6350, 269), (1000, 1000), (2048, 1024)])
+@pytest.mark.parametrize("steps", [2, 4, 8])
+def test_bench_names_the_kernel_that_runs(grid, steps):
+    import bench
+    (kernels,) = run(f'''
+h = solver({grid!r})
+L.lb_set_option(h, L.LB_OPT_STEPS_PER_PASS, {steps})
+L.lb_init(h, C, None)
+calls()
+L.lb_step(h, {8 * steps})
+out = [kernels()]
+''')
+    assert kernels[3] == bench.d2_pass_kernel(steps, grid)
+
+
+@pytest.mark.parametrize("grid", [(512, 512), (256, 256), (40, 40), (650, 650), (705, 705),
+                                  (2000, 250), (720, 721), (1024, 1024)])
+@pytest.mark.parametrize("limit", [2, 4, 8])
+def test_bench_knows_the_plan_of_a_segment(grid, limit):
+    import bench
+    lengths = (1, 2, 3, 4, 19, 45)
+    launches = run(f'''
+h = solver({grid!r})
+L.lb_set_option(h, L.LB_OPT_STEPS_PER_PASS, {limit})
+calls()
+out = []
+for m in {lengths!r}:
+    L.lb_adjoint_segment(h, A, m, B, C, D, A)
+    out.append(kernels())
+''')
+    for m, kernels in zip(lengths, launches):
+        tiles = sum(k.startswith("k_tile_adjoint") for k in kernels)
+        most = bench.d2_tile_adjoint_steps(grid, m, spp=limit)
+        assert tiles == (-(-m // most) if most else 0), (grid, limit, m)
