@@ -568,7 +568,12 @@ hipError_t launch_step(int d, const Geo& g, const Rates& r, const double* src, d
     return dispatch(d, [&](auto dc) {
         constexpr int DD = decltype(dc)::value;
         const Launch L = launch_shape(DD, g);
-        const bool nt = !states_fit_cache(DD, g, states);
+        // two 1-D states that fit in the L2s are not stored through them: a step is short
+        // enough there for the write-back at its end to count (us for 40 steps, cached and
+        // not: 600,000 nodes 194 and 163, 1,000,000 331 and 368)
+        constexpr uint64_t kL2Bytes = 32ull << 20;
+        const bool nt = !states_fit_cache(DD, g, states) ||
+                        (DD == 1 && 2ull * 3 * (uint64_t)g.V * sizeof(double) <= kL2Bytes);
         if constexpr (DD == 1) {  // D1Q3 has no twins
             return dispatch_io(nt, false, [&](auto n, auto) {
                 hipLaunchKernelGGL((k_step<1, false, false, decltype(n)::value>), L.grid, L.block,

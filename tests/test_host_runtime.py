@@ -314,3 +314,16 @@ for m in {lengths!r}:
         tiles = sum(k.startswith("k_tile_adjoint") for k in kernels)
         most = bench.d2_tile_adjoint_steps(grid, m, spp=limit)
         assert tiles == (-(-m // most) if most else 0), (grid, limit, m)
+
+
+@pytest.mark.parametrize("n,cached", [(3000, False), (600000, False), (1000000, True),
+                                      (9000000, False)])
+def test_1d_steps_are_stored_through_the_caches_where_that_pays(n, cached):
+    (kernel,) = run(f'''
+h = solver(({n},), 0.3)
+L.lb_init(h, C, D)
+calls()
+L.lb_step(h, 1)
+out = kernels()
+''')
+    assert kernel == f"k_step<1, false, false, {'false' if cached else 'true'}>"
