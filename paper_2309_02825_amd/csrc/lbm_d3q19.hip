@@ -94,8 +94,7 @@ __device__ __forceinline__ void m3_load_plane(double (&pre)[19], const double* s
         }
 }
 
-// x shift by DPP (pull from lane tx - e_x), then y shift through LDS.  BUF:
-// the input planes come through m3_load_plane (FORM_TWIN only).
+// The planes of FORM_MOM.
 __device__ __forceinline__ void m3_planes(const Mom3& m, double (&p)[19]) {
     p[0] = m.th;
     p[1] = m.jx;
@@ -109,6 +108,8 @@ __device__ __forceinline__ void m3_planes(const Mom3& m, double (&p)[19]) {
     p[9] = m.Pyz;
 }
 
+// One iteration k of the march.  x shift by DPP (pull from lane tx - e_x), then y shift
+// through LDS.  BUF: the input planes come through m3_load_plane (FORM_TWIN only).
 template <int S, int P, int IN, int OUT, bool BUF = false>
 __device__ __forceinline__ void ms3_plane(Ms3State<S>& st, double* lds, int k,
                                           const double* __restrict__ src, double* __restrict__ dst,
@@ -238,9 +239,9 @@ __global__ void __launch_bounds__(M3_THREADS) k_steps_d3q19(const double* __rest
 // Planes per segment of a D3Q19 pass over `tiles` (x, y) tiles: a block marches its
 // planes one after the other, four more than it stores, and the chip runs one block
 // per CU at a time, so the cost of a choice is rounds x (planes + 4), with whole
-// rounds while there are few.  At most 64 planes (512^3: 64 planes 2,797 us a step,
-// 128 2,829).  100^3, 12 planes (one round) against the 16 of a rule without rounds:
-// 24.7 and 30.1 us a step.
+// rounds while there are few.  At most 64 planes (512^3, with planes 19 apart: 64 planes
+// 2,797 us a step, 128 2,829).  100^3, 12 planes (one round) against the 16 of a rule
+// without rounds: 24.7 and 30.1 us a step.
 static int segment_planes(int nz, int64_t tiles, double* plane_rounds = nullptr) {
     const int cus = compute_units();
     int best = nz;
