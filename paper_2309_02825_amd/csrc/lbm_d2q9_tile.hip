@@ -421,21 +421,27 @@ int tile_rows(const Geo& g) {
 // those of the march (us a call, FORM_MOM and FORM_TWIN: tiles, 17 steps, 256^2 21.7 and
 // 20.3, 512^2 42.2 and 36.0, 600^2, 32 rows, 47.1 and 44.4; 650^2, 37 rows, 48.1 and
 // 49.3, 40^2 14.9 and 15.3).  So do marches in the
-// Infinity Cache of no more rows than the 16 of halo that a wave expands for them (us a
-// call: 16323 x 7, 200 steps 358 and 351; 13000 x 12, 25 steps 66.9 and 64.3).
+// Infinity Cache of no more rows than the 16 of halo that a wave expands for them, longer
+// runs on small grids only (us a call: 16323 x 7, 200 steps 358 and 351; 13000 x 12, 25
+// steps 66.9 and 64.3; 40000 x 16, 25 steps 91.2 and 88.2, 200 steps 592 and 609).
 TilePlan tile_plan(const Geo& g, int64_t nsteps, int limit) {
     constexpr int kShort = 5, kTall = 20, kTallest = 36;
+    constexpr int64_t kSmall = (int64_t)1 << 18;
     TilePlan p{false, pass_form(2, g)};
-    const int rows = limit > 1 && nsteps > 1 ? tile_rows(g) : 0;
-    if (rows == 0) {
-        if (g.ny <= 2 * MAX_STEPS_PER_PASS && d2q9_cached_stores(g)) p.form = FORM_TWIN;
-        return p;
-    }
+    if (limit < 2 || nsteps < 2) return p;
+    const int rows = tile_rows(g);
     const int log2 = __builtin_ctz((unsigned)limit);
     const int64_t passes = (nsteps + limit - 1) >> log2;
     const int64_t march = (nsteps >> log2) + __builtin_popcount((unsigned)(nsteps & (limit - 1)));
+    auto few = [](int64_t launches) { return launches >= 3 && launches <= 5; };
+    if (rows == 0) {
+        if (g.ny <= 2 * MAX_STEPS_PER_PASS && d2q9_cached_stores(g) &&
+            (g.V <= kSmall || few(march)))
+            p.form = FORM_TWIN;
+        return p;
+    }
     p.tiles = rows < kTall || passes * 4 < nsteps || passes < march;
-    if (rows >= kShort && rows < kTallest && (!p.tiles || (passes >= 3 && passes <= 5)))
+    if (rows >= kShort && rows < kTallest && (!p.tiles || few(passes)))
         p.form = FORM_TWIN;
     return p;
 }
