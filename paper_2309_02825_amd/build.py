@@ -19,9 +19,11 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "liblbm_hip.so")
 # the slowest to compile first
 SOURCES = [os.path.join(CSRC, n) for n in
-           ("lbm_d2q9.hip", "lbm_batch.hip", "lbm_d2q9_adjoint.hip", "lbm_d2q9_s4.hip",
+           ("lbm_d2q9_s8_mom.hip", "lbm_d2q9_s8_full.hip", "lbm_d2q9_s8_twin.hip",
+            "lbm_batch.hip", "lbm_d2q9_adjoint.hip", "lbm_d2q9_s4.hip",
             "lbm_d2q9_s2.hip", "lbm_d2q9_tile.hip", "lbm_d3q19.hip",
-            "lbm_d3q19_march.hip", "lbm_kernels.hip", "lbm_d1.hip", "lbm_api.hip")]
+            "lbm_d3q19_march.hip", "lbm_kernels.hip", "lbm_d1.hip", "lbm_api.hip",
+            "lbm_d2q9.hip")]
 ARCH = os.environ.get("LBM_OFFLOAD_ARCH", "gfx950")
 
 

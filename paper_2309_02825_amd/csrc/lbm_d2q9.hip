@@ -1,4 +1,4 @@
-// D2Q9 passes of several steps: eight per pass, and the choice of a pass.
+// D2Q9 passes of several steps: the choice of a pass.
 #include <algorithm>
 #include <atomic>
 
@@ -67,6 +67,15 @@ int pass_form(int d, const Geo& g) {
     return (d == 2 && ms_off32(g)) || (d == 3 && march3_fits(g)) ? FORM_MOM : FORM_TWIN;
 }
 
+extern template hipError_t launch_steps_from<8, FORM_FULL>(const Geo&, const Rates&,
+                                                           const double*, double*, hipStream_t,
+                                                           int);
+extern template hipError_t launch_steps_from<8, FORM_TWIN>(const Geo&, const Rates&,
+                                                           const double*, double*, hipStream_t,
+                                                           int);
+extern template hipError_t launch_steps_from<8, FORM_MOM>(const Geo&, const Rates&,
+                                                          const double*, double*, hipStream_t,
+                                                          int);
 extern template hipError_t launch_steps_t<2>(const Geo&, const Rates&, const double*, double*,
                                              hipStream_t, int, int);
 extern template hipError_t launch_steps_t<4>(const Geo&, const Rates&, const double*, double*,

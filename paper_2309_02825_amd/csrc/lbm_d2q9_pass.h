@@ -1,4 +1,4 @@
-// The D2Q9 pass of S steps, compiled for one S per source.
+// The D2Q9 pass of S steps, compiled for one S per source, or one S and input form.
 #pragma once
 
 #include "lbm_pair.h"
@@ -103,9 +103,11 @@ k_steps_d2q9_seam(const double* __restrict__ src, double* __restrict__ dst, Geo 
 
 }  // namespace
 
-template <int S>
-hipError_t launch_steps_t(const Geo& g, const Rates& r, const double* src, double* dst,
-                          hipStream_t st, int in, int out) {
+// A pass from buffers in form IN (a source of its own for each at eight steps, whose
+// kernels take minutes to compile).
+template <int S, int IN>
+hipError_t launch_steps_from(const Geo& g, const Rates& r, const double* src, double* dst,
+                             hipStream_t st, int out) {
     const int w = strip_width(S);
     const int nstrips = (g.nx + w - 1) / w;
     bool half;
@@ -113,50 +115,64 @@ hipError_t launch_steps_t(const Geo& g, const Rates& r, const double* src, doubl
     const int nseg = (g.ny + ly - 1) / ly;
     const dim3 grid((unsigned)((int64_t)nstrips * nseg)), block(MS_THREADS);
     const bool off32 = ms_off32(g), cached = d2q9_cached_stores(g);
-    return dispatch_form(in, [&](auto fi) {
-        return dispatch_form(out, [&](auto fo) {
-            constexpr int IN = decltype(fi)::value, OUT = decltype(fo)::value;
-            constexpr bool RI = IN != FORM_FULL, WO = OUT != FORM_FULL;
-            if constexpr (S == MAX_STEPS_PER_PASS) {  // pass_rows: no shorter ones
-                if (off32 && half && !cached) {
-                    hipLaunchKernelGGL((k_steps_d2q9_half<S, true, IN, OUT>), grid, block, 0, st,
-                                       src, dst, g, r, ly, nstrips);
-                    return hipGetLastError();
-                }
-            }
-            if (!off32) {
-                if (IN == FORM_MOM || OUT == FORM_MOM) return hipErrorInvalidValue;  // pass_form
+    return dispatch_form(out, [&](auto fo) {
+        constexpr int OUT = decltype(fo)::value;
+        constexpr bool RI = IN != FORM_FULL, WO = OUT != FORM_FULL;
+        constexpr bool MOM = IN == FORM_MOM || OUT == FORM_MOM;
+        if (!off32) {
+            if constexpr (MOM)
+                return hipErrorInvalidValue;  // pass_form
+            else
                 hipLaunchKernelGGL((k_steps_d2q9<S, false, RI, WO>), grid, block, 0, st, src, dst,
                                    g, r, ly, nstrips);
-            } else if (half && cached) {
-                hipLaunchKernelGGL((k_steps_d2q9_half<S, false, IN, OUT>), grid, block, 0, st, src,
+            return hipGetLastError();
+        }
+        if (half && cached) {
+            hipLaunchKernelGGL((k_steps_d2q9_half<S, false, IN, OUT>), grid, block, 0, st, src,
+                               dst, g, r, ly, nstrips);
+            return hipGetLastError();
+        }
+        if constexpr (S == MAX_STEPS_PER_PASS) {  // pass_rows: no shorter ones
+            if (half) {
+                hipLaunchKernelGGL((k_steps_d2q9_half<S, true, IN, OUT>), grid, block, 0, st, src,
                                    dst, g, r, ly, nstrips);
-            } else if (pair_pass(S, true, RI, WO) && IN == FORM_MOM && OUT == FORM_MOM && !cached &&
-                       pair_fits(g, src, dst)) {
+                return hipGetLastError();
+            }
+        }
+        if constexpr (IN == FORM_TWIN || OUT == FORM_TWIN) {
+            if (cached)
+                hipLaunchKernelGGL((k_steps_d2q9_seam<S, false, IN, OUT>), grid, block, 0, st,
+                                   src, dst, g, r, ly, nstrips);
+            else
+                hipLaunchKernelGGL((k_steps_d2q9_seam<S, true, IN, OUT>), grid, block, 0, st,
+                                   src, dst, g, r, ly, nstrips);
+        } else if (cached) {  // both states fit in 256 MB, so under 4 GiB
+            hipLaunchKernelGGL((k_steps_d2q9_cached<S, true, RI, WO>), grid, block, 0, st, src,
+                               dst, g, r, ly, nstrips);
+        } else if constexpr (pair_pass(S, true, RI, WO)) {  // FORM_MOM to FORM_MOM
+            if (pair_fits(g, src, dst)) {
                 const int np = (g.nx + MP_WIDTH - 1) / MP_WIDTH;
                 const int lp = steps_rows(g, np, kMinRows, 4 * compute_units());
                 const dim3 gp((unsigned)((int64_t)np * ((g.ny + lp - 1) / lp)));
-                hipLaunchKernelGGL((k_steps_d2q9<S, true, RI, WO>), gp, dim3(MP_THREADS), 0, st, src,
-                                   dst, g, r, lp, np);
-            } else if constexpr (IN == FORM_TWIN || OUT == FORM_TWIN || pair_pass(S, true, RI, WO)) {
-                if (cached && IN == FORM_MOM && OUT == FORM_MOM)
-                    hipLaunchKernelGGL((k_steps_d2q9_cached<S, true, RI, WO>), grid, block, 0, st, src,
-                                       dst, g, r, ly, nstrips);
-                else if (cached)
-                    hipLaunchKernelGGL((k_steps_d2q9_seam<S, false, IN, OUT>), grid, block, 0, st,
-                                       src, dst, g, r, ly, nstrips);
-                else
-                    hipLaunchKernelGGL((k_steps_d2q9_seam<S, true, IN, OUT>), grid, block, 0, st,
-                                       src, dst, g, r, ly, nstrips);
-            } else if (cached) {  // both states fit in 256 MB, so under 4 GiB
-                hipLaunchKernelGGL((k_steps_d2q9_cached<S, true, RI, WO>), grid, block, 0, st, src,
-                                   dst, g, r, ly, nstrips);
+                hipLaunchKernelGGL((k_steps_d2q9<S, true, RI, WO>), gp, dim3(MP_THREADS), 0, st,
+                                   src, dst, g, r, lp, np);
             } else {
-                hipLaunchKernelGGL((k_steps_d2q9<S, true, RI, WO>), grid, block, 0, st, src, dst,
-                                   g, r, ly, nstrips);
+                hipLaunchKernelGGL((k_steps_d2q9_seam<S, true, IN, OUT>), grid, block, 0, st,
+                                   src, dst, g, r, ly, nstrips);
             }
-            return hipGetLastError();
-        });
+        } else {
+            hipLaunchKernelGGL((k_steps_d2q9<S, true, RI, WO>), grid, block, 0, st, src, dst,
+                               g, r, ly, nstrips);
+        }
+        return hipGetLastError();
+    });
+}
+
+template <int S>
+hipError_t launch_steps_t(const Geo& g, const Rates& r, const double* src, double* dst,
+                          hipStream_t st, int in, int out) {
+    return dispatch_form(in, [&](auto fi) {
+        return launch_steps_from<S, decltype(fi)::value>(g, r, src, dst, st, out);
     });
 }
 
