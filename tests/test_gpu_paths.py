@@ -320,3 +320,22 @@ def test_d2q9_march_of_buffers_off_16_bytes(shift_a, shift_b):
     torch.cuda.synchronize()
     L.lb_destroy(h)
     ref.s.close()
+
+
+@pytest.mark.parametrize("grid", [(513, 511), (599, 600), (700, 700), (300, 1500), (100, 4000)])
+@pytest.mark.parametrize("limit", [4, 8])
+def test_d2q9_short_passes_of_tall_tiles_equal_single_steps(grid, limit):
+    """Runs that leave tiles of many rows to the march, short runs that hand on
+    populations and longer ones that do not, one after the other, bit for bit."""
+    _say("D2Q9 tall tiles", grid, limit)
+    s, ref = _solver(grid, 0.31), _Single(grid, 0.31)
+    s.set_steps_per_pass(limit)
+    th0 = _rough(grid, 13)
+    s.init(th0, None)
+    ref.s.init(th0, None)
+    for n in (2, 4, 3, 8, 9, 12, 20, 21, 49):
+        s.step(n)
+        ref.step(n)
+        assert torch.equal(s.get_state(), ref.state()), (grid, limit, n)
+    s.close()
+    ref.s.close()

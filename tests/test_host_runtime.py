@@ -1,5 +1,5 @@
 """What the library asks of a HIP runtime, on one that runs on the host: launches,
-allocations and failures that a GPU machine does not show."""
+allocations and failures that runs on a GPU do not show."""
 import os
 import sys
 
