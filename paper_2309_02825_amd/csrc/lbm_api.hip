@@ -427,7 +427,7 @@ lb_status lb_step(lb_solver* s, int64_t nsteps) {
     // lb_init or lb_set_state.
     std::vector<std::pair<int, int64_t>> runs;
     const lbm::TilePlan plan = s->d == 2 ? lbm::tile_plan(s->g, nsteps, s->steps_per_pass)
-                                         : lbm::TilePlan{false, lbm::pass_form(s->d, s->g)};
+                                         : lbm::TilePlan{false, s->plan3.form};
     const bool tiles = plan.tiles;
     {
         int64_t n = 0;

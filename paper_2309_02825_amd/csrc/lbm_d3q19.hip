@@ -309,22 +309,33 @@ hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double*
     return launch_steps3_t<2>(g, r, src, dst, st, in, out, plan.lz_first);
 }
 
-// Whether a run on this grid takes passes of two steps: below some 200 thousand
-// nodes a pass is a few blocks that march eight planes each, and two launches of
-// one step take less.  In us: a pass 5 and 1.95 for a plane of the march (a block
-// alone on its CU); a single step one per 18 thousand nodes or 40 thousand threads
-// of its launch grid, the larger (40^3: 5.2 a step in single steps, 10.4 in passes;
-// 64^3 12.6 and 10.8).
+// How a run goes, by an estimate in us of two steps.  A pass takes 4 and 2.1 for a plane
+// of the march (a block alone on its CU), or 2.3 for a plane of the 8-row tiles and 1 for
+// the ends of segments.  Those are faster where they march no more planes, on few planes
+// and on rows of columns, while what they move (FORM_TWIN) stays in the Infinity Cache (us
+// for 24 steps, 8-row tiles and march: 322 x 154 x 4 224 and 250, 303 x 154 x 3 185 and
+// 221; 337 x 185 x 4, two rounds of 8-row tiles, 408 and 269; 1000 x 4 x 1000, beyond the
+// cache, 2,647 and 2,479).  Two single steps take 7, one for 42 thousand nodes and one for
+// 40 thousand threads of their launch grids, at least one for 480 blocks, and beyond the
+// cache one for 10 thousand nodes (two steps, single and in passes: 40^3 9.9 and 20.9,
+// 64^3 19.5 and 21.6, 72^3 28.8 and 26.4, 2 x 76 x 232 37.6 and 33.3, 1 x 1 x 65535 123
+// and 481).
 Plan3 plan3(const Geo& g) {
     const int64_t first = (int64_t)((g.nx + tile_width3(2) - 1) / tile_width3(2)) *
                           ((g.ny + tile_height3(2) - 1) / tile_height3(2));
+    const bool cached = states_fit_cache(3, g);
     Plan3 p;
-    double planes;
-    p.lz_first = segment_planes(g.nz, first);
+    double planes_first, planes;
+    p.lz_first = segment_planes(g.nz, first, &planes_first);
     p.lz = segment_planes(g.nz, march3_tiles(g), &planes);
-    const double threads = (double)launch_shape(3, g).nblocks * 256.0;
-    const double single = std::max((double)g.V / 18000.0, threads / 40000.0);
-    p.passes = 5.0 + 1.95 * planes < 2.0 * single;
+    p.form = cached && planes_first <= planes ? (int)FORM_TWIN : pass_form(3, g);
+    const double pass = p.form == FORM_TWIN ? 2.3 * planes_first + (p.lz_first < g.nz)
+                                            : 4.0 + 2.1 * planes;
+    const double blocks = (double)launch_shape(3, g).nblocks;
+    double single = std::max(7.0 + (double)g.V / 42000.0 + blocks * 256.0 / 40000.0,
+                             blocks / 480.0);
+    if (!cached) single = std::max(single, (double)g.V / 10000.0);
+    p.passes = pass < single;
     return p;
 }
 

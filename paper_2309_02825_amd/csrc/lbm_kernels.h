@@ -131,6 +131,7 @@ __host__ __device__ constexpr int tile_height3(int nsteps) { return MS3_TY - 2 *
 // lengths takes 0.13 ms of host time at 65,535 planes).
 struct Plan3 {
     bool passes = false;         // passes of two steps rather than single ones
+    int form = FORM_TWIN;        // what one pass hands to the next
     int lz_first = 0, lz = 0;    // planes per segment: first pass of a call, later ones
 };
 Plan3 plan3(const Geo& g);

@@ -229,7 +229,7 @@ def test_d2q9_two_wave_marches_equal_single_steps(grid):
 
 
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
-from plan_grids import CACHED_2D, FLAT_3D
+from plan_grids import CACHED_2D, FLAT_3D, FLAT_3D_8_ROWS
 
 
 class _Single:
@@ -270,7 +270,7 @@ def test_d2q9_cached_marches_equal_single_steps(grid, limit):
     ref.s.close()
 
 
-@pytest.mark.parametrize("grid", FLAT_3D)
+@pytest.mark.parametrize("grid", FLAT_3D + FLAT_3D_8_ROWS)
 def test_d3q19_passes_of_flat_grids_equal_single_steps(grid):
     """Passes where a tile's halo wraps around an axis more than once, through lb_init,
     lb_set_state and checks in the middle of a run, bit for bit."""

@@ -114,12 +114,12 @@ out = [first, second, calls()]
 
 
 def test_d3q19_plan_is_not_searched_per_launch():
-    """Host time of a pass does not grow with the planes of the grid: 1 x 1 x 65535
-    against 64^3 (with the search of segment lengths in every launch, 30 times)."""
+    """Host time of a pass does not grow with the planes of the grid: 1 x 8 x 65535
+    against 72^3 (with the search of segment lengths in every launch, 30 times)."""
     t = run('''
 import time
 out = []
-for grid in ((64, 64, 64), (1, 1, 65535)):
+for grid in ((72, 72, 72), (1, 8, 65535)):
     h = solver(grid)
     L.lb_init(h, C, None)
     best = 1e9
@@ -220,7 +220,7 @@ for k in (1, 2):
 
 # Grids of test_gpu_paths.py that the plan has to send to the kernels that their tests
 # are there for: comparisons of single steps with single steps cannot fail.
-from plan_grids import CACHED_2D, CACHED_2D_HALF, FLAT_3D
+from plan_grids import CACHED_2D, CACHED_2D_HALF, FLAT_3D, FLAT_3D_8_ROWS, SINGLE_3D
 
 
 @pytest.mark.parametrize("grid", CACHED_2D)
@@ -244,6 +244,23 @@ def test_grids_of_the_flat_d3q19_passes(grid):
     assert kernels[:3] == [f"k_steps_d3q19<2, {TWIN}, {MOM}, true>", f"k_march_d3q19<{MOM}>",
                            f"k_march_d3q19<{TWIN}>"]
     assert [k.split("<")[0] for k in kernels[3:]] == ["k_step"]
+
+
+@pytest.mark.parametrize("grid", FLAT_3D_8_ROWS)
+def test_d3q19_passes_of_8_rows(grid):
+    """Where the tall tiles march no fewer planes, the first pass's kernel takes the others
+    too (303 x 154 x 3: 185 us for 24 steps, tall tiles 221)."""
+    (kernels,) = _run_kernels(grid, (7,))
+    assert kernels[:3] == [f"k_steps_d3q19<2, {TWIN}, {TWIN}, true>"] * 3
+    assert [k.split("<")[0] for k in kernels[3:]] == ["k_step"]
+
+
+@pytest.mark.parametrize("grid", SINGLE_3D)
+def test_d3q19_single_steps(grid):
+    """Grids whose launch has many threads without a node (1 x 1 x 65535: 1,471 us for 24
+    steps, in passes 5,777)."""
+    (kernels,) = _run_kernels(grid, (7,))
+    assert [k.split("<")[0] for k in kernels] == ["k_step"] * 7
 
 
 def test_two_wave_march_needs_aligned_buffers():
