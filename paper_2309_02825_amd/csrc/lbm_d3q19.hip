@@ -296,9 +296,9 @@ static int64_t march3_tiles(const Geo& g) {
     return (int64_t)((g.nx + MARCH3_W - 1) / MARCH3_W) * ((g.ny + MARCH3_H - 1) / MARCH3_H);
 }
 
-// Two steps: from FORM_MOM, the passes of a run, on the taller tiles of
-// k_march_d3q19; the first launch of a call, which reads 19 or 13 planes, and every
-// launch on z-planes of 2 GiB on the 8-row tiles.
+// Two steps: from FORM_MOM on the taller tiles of k_march_d3q19; from 19 or 13 planes,
+// the first launch of a call and every one where passes hand on FORM_TWIN (plan3), on the
+// 8-row tiles.
 hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
                          hipStream_t st, int in, int out, const Plan3& plan) {
     if (g.nw != 1 || nsteps != 2 || plan.lz_first < 1 || plan.lz < 1) return hipErrorInvalidValue;

@@ -24,7 +24,7 @@ namespace {
 // 8 outputs, against 8 for 4 in k_steps_d3q19: a quarter less is computed and
 // loaded per output.  What bounds it: at 512^3 memory (21.5 GB algorithmic in
 // 4.91 ms, 4.4 TB/s, with a halo of half as much again in the reads); on small grids
-// the 1.95 us of a plane: 192 VALU instructions a wave and 32 LDS accesses, two
+// the 2.1 us of a plane: 192 VALU instructions a wave and 32 LDS accesses, two
 // barriers.  us a step, 8-row tiles of 13 populations and these of 10 quantities: 512^3
 // 3,413 and 2,455, 256^3 444 and 314, 100^3 42.2 and 25 (with these tiles and 13
 // planes' strides 512^3 took 2,797).  Two rows per thread (16-row tiles) spilled 41

@@ -70,9 +70,9 @@ __host__ __device__ constexpr int strip_width(int nsteps) { return MS_THREADS - 
 // pass_form allows it.
 hipError_t launch_steps(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
                         hipStream_t st, int in, int out);
-// The form in which the passes of lattice d hand the state to one another: the
-// smallest that the kernels of this grid read (FORM_MOM; FORM_TWIN for D2Q9
-// states of 4 GiB and D3Q19 z-planes of 2 GiB and more, and for D4Q33).
+// The smallest form in which the kernels of this grid read what a pass of lattice d left
+// (FORM_MOM; FORM_TWIN for D2Q9 states of 4 GiB and D3Q19 z-planes of 2 GiB and more, and
+// for D4Q33); tile_plan and plan3 hand on FORM_TWIN on some more grids.
 int pass_form(int d, const Geo& g);
 int compute_units();  // of the current device
 // nsteps (2..8) D2Q9 steps in one pass of workgroup tiles held in registers, on
@@ -132,7 +132,7 @@ __host__ __device__ constexpr int tile_height3(int nsteps) { return MS3_TY - 2 *
 struct Plan3 {
     bool passes = false;         // passes of two steps rather than single ones
     int form = FORM_TWIN;        // what one pass hands to the next
-    int lz_first = 0, lz = 0;    // planes per segment: first pass of a call, later ones
+    int lz_first = 0, lz = 0;    // planes per segment: on the 8-row tiles, on the tall ones
 };
 Plan3 plan3(const Geo& g);
 hipError_t launch_steps3(int nsteps, const Geo& g, const Rates& r, const double* src, double* dst,
